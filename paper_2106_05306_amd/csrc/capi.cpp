@@ -28,8 +28,9 @@ hipError_t launch_region_grad(const double *dw, const double *base_w, const int3
 hipError_t launch_scatter_bend(const double *dw, const int32_t *centers, int n_edges, int n_bend, double *out,
                                hipStream_t st);
 hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t st);
-hipError_t launch_adj_assemble(const SimDev *d_sims, const int32_t *work, int nblocks, hipStream_t st);
-hipError_t launch_adj_factor_level(const SimDev *d_sims, const int32_t *work, int nblocks, int nmax, hipStream_t st);
+hipError_t launch_adj_assemble(const SimDev *d_sims, const int32_t *work, int nslots, int nnz, int m, hipStream_t st);
+hipError_t launch_adj_factor_level(const SimDev *d_sims, const int32_t *work, int nblocks, int nmax, int tiles, int bands,
+                                   hipStream_t st);
 hipError_t noalloc_scratch(void **out);
 hipError_t launch_forward_mw(const SimDev *d, int W, bool mixed, bool mesh, bool lw, size_t lds, int threads,
                              hipStream_t st);
@@ -85,7 +86,9 @@ struct sim {
     int af_cap = 0;                     // step factors allocated (direct adjoint)
     int n_ubuf_bwd = 0;                 // update-buffer doubles the backward kernel needs
     std::vector<std::vector<int32_t>> lvl_sn;   // supernodes of each elimination level (adjoint factor)
-    std::vector<int32_t> lvl_nmax;      // largest diagonal block (DoF) of each of those levels
+    std::vector<int32_t> lvl_nmax;      // largest diagonal block (DoF) of each of those levels,
+    std::vector<int32_t> lvl_tiles;     //   most Schur tiles of a chunk (0: no chunk of the level is updated)
+    std::vector<int32_t> lvl_bands;     //   and most row bands of a chunk's panel
     std::vector<int32_t> h_work;        // factorisation work lists (host copy)
     int32_t *d_work = nullptr;          // and their device copy
     size_t work_cap = 0;
@@ -1006,7 +1009,7 @@ void build_device(sim *s) {
                 const int t = chunk_of[arows[r0 + i]];
                 int j = i;
                 while (j < nr && chunk_of[arows[r0 + j]] == t) ++j;
-                ul[t].push_back(LuUpd{d, i, j, 0});
+                ul[t].push_back(LuUpd{d, i, j, 0, 0});
                 i = j;
             }
         }
@@ -1028,6 +1031,7 @@ void build_device(sim *s) {
                 for (int i = ud.i0; i < arptr[ud.d + 1] - arptr[ud.d]; ++i) {
                     const int node = arows[arptr[ud.d] + i];
                     relmap.push_back(i < ud.i1 ? node - ac0[t] : an[t] + pos_in_R(t, node));
+                    ud.mask |= uint64_t(1) << std::min(relmap.back() / kSchurNodes, 63);
                 }
                 upl.push_back(ud);
             }
@@ -1060,20 +1064,35 @@ void build_device(sim *s) {
                 }
             }
         }
-        // Delta P blocks: incidence entry (i, c) adds a_ci a_cl G_c to block (i, l)
-        std::vector<int32_t> dptr(1, 0), dks;
-        for (int i = 0; i < m; ++i) {
-            for (int p = ip[i]; p < ip[i + 1]; ++p) {
-                const int c = ic[p];
-                for (int q = cp[c]; q < cp[c + 1]; ++q) {
-                    const int l = cn[q];
+        // Delta P blocks: incidence entry (i, c) adds a_ci a_cl G_c to block (i, l);
+        // listed per block, in the row's incidence order
+        std::vector<int32_t> krow(kc.size()), dptr(kc.size() + 1, 0), dks, dcon;
+        std::vector<double> dcf;
+        for (int i = 0; i < m; ++i)
+            for (int e = kp[i]; e < kp[i + 1]; ++e) krow[e] = i;
+        for (int i = 0; i < m; ++i)
+            for (int p = ip[i]; p < ip[i + 1]; ++p)
+                for (int q = cp[ic[p]]; q < cp[ic[p] + 1]; ++q) {
                     const int *b = kc.data() + kp[i], *e = kc.data() + kp[i + 1];
-                    const int *it = std::lower_bound(b, e, l);
-                    if (it == e || *it != l) throw std::runtime_error("K_s pattern misses a constraint coupling");
+                    const int *it = std::lower_bound(b, e, cn[q]);
+                    if (it == e || *it != cn[q]) throw std::runtime_error("K_s pattern misses a constraint coupling");
                     dks.push_back((int32_t)(it - kc.data()));
+                    ++dptr[dks.back() + 1];
                 }
-                dptr.push_back((int32_t)dks.size());
-            }
+        for (size_t e = 0; e < kc.size(); ++e) dptr[e + 1] += dptr[e];
+        {
+            std::vector<int32_t> at(dptr.begin(), dptr.end() - 1);
+            dcon.resize(dks.size());
+            dcf.resize(2 * dks.size());
+            size_t t = 0;
+            for (int i = 0; i < m; ++i)
+                for (int p = ip[i]; p < ip[i + 1]; ++p)
+                    for (int q = cp[ic[p]]; q < cp[ic[p] + 1]; ++q) {
+                        const int o = at[dks[t++]]++;
+                        dcon[o] = ic[p];
+                        dcf[2 * o] = icf[p];
+                        dcf[2 * o + 1] = cc[q];
+                    }
         }
         // solve schedule by level: forward gathers (per node: the update-buffer
         // entries reaching it), backward gathers of x_{R_t}, and the block
@@ -1093,6 +1112,8 @@ void build_device(sim *s) {
         std::vector<std::vector<int64_t>> pf(3 * L);          // blocks read by each phase (prefetch)
         s->lvl_sn.assign(L, {});
         s->lvl_nmax.assign(L, 3);
+        s->lvl_tiles.assign(L, 0);
+        s->lvl_bands.assign(L, 0);
         for (int l = 0; l < L; ++l) {
             for (int t = 0; t < na; ++t) {
                 if (alevel[t] != l) continue;
@@ -1100,6 +1121,11 @@ void build_device(sim *s) {
                 const int N = 3 * q.n, R = 3 * q.r, t0 = 3 * q.c0;
                 s->lvl_sn[l].push_back(t);
                 s->lvl_nmax[l] = std::max(s->lvl_nmax[l], N);
+                s->lvl_bands[l] = std::max(s->lvl_bands[l], (R + kBandRows - 1) / kBandRows);
+                if (up_ptr[t + 1] > up_ptr[t]) {
+                    const int ND = (q.n + kSchurNodes - 1) / kSchurNodes, PT = (q.n + q.r + kSchurNodes - 1) / kSchurNodes;
+                    s->lvl_tiles[l] = std::max(s->lvl_tiles[l], ND * PT + (PT - ND) * ND);
+                }
                 for (int c = ac0[t]; c < ac0[t] + an[t]; ++c) ri.push_back(RowItem{3 * c, aup[c], aup[c + 1], 0});
                 for (int k = 0; k < q.r; ++k) gat.push_back(GatherItem{q.uoff + 3 * k, 3 * arows[q.rptr + k]});
                 const int64_t offB = q.off + (int64_t)N * q.ldn, offV = offB + (int64_t)N * q.ldr;
@@ -1139,8 +1165,10 @@ void build_device(sim *s) {
         D.lu_relmap = upload(s, relmap);
         D.ks_dst = upload(s, kdst);
         D.ks_ld = upload(s, kld);
+        D.ks_row = upload(s, krow);
         D.dp_ptr = upload(s, dptr);
-        D.dp_ks = upload(s, dks);
+        D.dp_con = upload(s, dcon);
+        D.dp_coef = upload(s, dcf);
         D.lu_lvl = upload(s, lvl);
         D.lu_gat = upload(s, gat);
         D.adj_items = upload(s, aitems);
@@ -1859,9 +1887,9 @@ int prepare_backward(sim *s, const double *dL_dxT, const double *dL_dvT, const d
 
 // Direct adjoint factorisation of the (handle, slot) pairs listed in `pairs`
 // (handle = index into hs and into the device descriptor array d_descs): one
-// assembly launch, then one launch per elimination level with a workgroup per
-// (handle, slot, supernode).  The work lists go through owner's buffers; the
-// previous use of them is waited for first.
+// assembly, then three launches per elimination level (Schur updates, inverses,
+// panel products).  The work lists go through owner's buffers; the previous use
+// of them is waited for first.
 int factor_pairs(sim *owner, const SimDev *d_descs, const std::vector<sim *> &hs, const std::vector<int32_t> &pairs,
                  hipStream_t st) {
     if (pairs.empty()) return SIM_OK;
@@ -1869,10 +1897,17 @@ int factor_pairs(sim *owner, const SimDev *d_descs, const std::vector<sim *> &hs
     if (rc) return rc;
     int L = 0;
     for (sim *h : hs) L = std::max(L, (int)h->lvl_sn.size());
-    std::vector<int> nmax(L, 3);
+    std::vector<int> nmax(L, 3), tiles(L, 0), bands(L, 0);
+    int nnz = 0, mmax = 0;
     for (size_t p = 0; p < pairs.size(); p += 2) {
         const sim *h = hs[pairs[p]];
-        for (size_t l = 0; l < h->lvl_nmax.size(); ++l) nmax[l] = std::max(nmax[l], h->lvl_nmax[l]);
+        nnz = std::max(nnz, (int)h->hm.ks_col.size());
+        mmax = std::max(mmax, h->hm.m);
+        for (size_t l = 0; l < h->lvl_nmax.size(); ++l) {
+            nmax[l] = std::max(nmax[l], h->lvl_nmax[l]);
+            tiles[l] = std::max(tiles[l], h->lvl_tiles[l]);
+            bands[l] = std::max(bands[l], h->lvl_bands[l]);
+        }
     }
     std::vector<int32_t> &buf = owner->h_work;
     buf = pairs;
@@ -1898,10 +1933,10 @@ int factor_pairs(sim *owner, const SimDev *d_descs, const std::vector<sim *> &hs
         owner->work_cap = buf.size();
     }
     rc = hip_err(hipMemcpyAsync(owner->d_work, buf.data(), buf.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    if (!rc) rc = hip_err(launch_adj_assemble(d_descs, owner->d_work, (int)pairs.size() / 2, st));
+    if (!rc) rc = hip_err(launch_adj_assemble(d_descs, owner->d_work, (int)pairs.size() / 2, nnz, mmax, st));
     for (int l = 0; l < L && !rc; ++l)
         rc = hip_err(launch_adj_factor_level(d_descs, owner->d_work + loff[l], (int)((loff[l + 1] - loff[l]) / 3),
-                                             nmax[l], st));
+                                             nmax[l], tiles[l], bands[l], st));
     return rc;
 }
 

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -1717,31 +1718,38 @@ __device__ __forceinline__ auto slot_ws(const SimDev &S, int slot) {
 }
 __device__ __forceinline__ int64_t ws_anorm(const SimDev &S) { return 9 * (int64_t)S.m + 4 * (int64_t)max(S.nca, 1); }
 
-// Assembly of one step's A into its factor slot, one workgroup per (handle,
-// slot) pair of work (NULL: handle 0, slot = block index); slot k holds step
-// af_step0 + k.  The blocks are stored transposed (see capi: ks_dst).
-__global__ __launch_bounds__(kFacBlock) void k_adj_assemble(const SimDev *__restrict__ sims,
-                                                            const int32_t *__restrict__ work) {
-    const int hidx = work ? work[2 * blockIdx.x] : 0;
-    const int slot = work ? work[2 * blockIdx.x + 1] : (int)blockIdx.x;
-    const SimDev &S = sims[hidx];
-    const int tid = threadIdx.x, bd = blockDim.x;
+// Assembly of the steps' A into their factor slots: three launches over
+// (slot, part) grids.  work lists the (handle, slot) pairs (NULL: handle 0,
+// slot = block index); slot k holds step af_step0 + k.  The blocks are stored
+// transposed (see capi: ks_dst).  One workgroup per slot took 1.0 - 1.2 ms at
+// 40 x 40 (16 MB zeroed by one workgroup, and every block read and rewritten in
+// memory once per constraint); spread over the chip a block is summed in
+// registers, in the same order.
+struct AsmSlot {
+    int hidx, slot;
+    __device__ AsmSlot(const int32_t *work)
+        : hidx(work ? work[2 * blockIdx.x] : 0), slot(work ? work[2 * blockIdx.x + 1] : (int)blockIdx.x) {}
+};
+
+// Zeroes the slot; projection Jacobians and contact blocks of the step.
+__global__ __launch_bounds__(kFacBlock) void k_adj_prepare(const SimDev *__restrict__ sims,
+                                                           const int32_t *__restrict__ work) {
+    const AsmSlot w(work);
+    const SimDev &S = sims[w.hidx];
+    const int64_t tid = (int64_t)blockIdx.y * kFacBlock + threadIdx.x, nt = (int64_t)gridDim.y * kFacBlock;
     const int m = S.m;
     const double hh = S.h * S.h;
-    const int rs = S.af_step0 + slot - S.rec_step0;
+    const int rs = S.af_step0 + w.slot - S.rec_step0;
     const auto x0 = G(S.rec_x) + (int64_t)rs * 3 * m;
     const auto x1 = x0 + 3 * m;
     const auto mode = G(S.rec_mode) + (int64_t)rs * m;
     const auto obst = G(S.rec_obst) + (int64_t)rs * m;
     const auto ubr = G(S.rec_ubar) + (int64_t)rs * 3 * m;
-    const auto F = G(S.af) + (int64_t)slot * S.af_size;
-    const auto ws = slot_ws(S, slot);
-    const auto Tb = ws;
+    const auto F2 = (GLOBAL v2d *)(G(S.af) + (int64_t)w.slot * S.af_size);   // af_size is even
+    const auto ws = slot_ws(S, w.slot);
     const auto Gc = ws + 9 * (int64_t)m;
-    __shared__ double red[kFacBlock / 64];
-
-    for (int64_t e = tid; e < S.af_size; e += bd) F[e] = 0.0;
-    for (int c = tid; c < S.nca; c += bd) {           // projection Jacobians at x_{n+1}
+    for (int64_t e = tid; e < S.af_size / 2; e += nt) F2[e] = v2d{0.0, 0.0};
+    for (int64_t c = tid; c < S.nca; c += nt) {       // projection Jacobians at x_{n+1}
         double q0 = 0, q1 = 0, q2 = 0;
         for (int p = G(S.c_ptr)[c]; p < G(S.c_ptr)[c + 1]; ++p) {
             const int j = G(S.c_node)[p];
@@ -1757,80 +1765,124 @@ __global__ __launch_bounds__(kFacBlock) void k_adj_assemble(const SimDev *__rest
             Gc[4 * c + 1] = q0 / nq; Gc[4 * c + 2] = q1 / nq; Gc[4 * c + 3] = q2 / nq;
         }
     }
-    for (int i = tid; i < m; i += bd) {
+    for (int64_t i = tid; i < m; i += nt) {
         double T[9];
         contact_T(S, mode[i], obst[i], x0 + 3 * i, ubr + 3 * i, T);
-        for (int e = 0; e < 9; ++e) Tb[9 * (int64_t)i + e] = T[e];
+        for (int e = 0; e < 9; ++e) ws[9 * i + e] = T[e];
     }
-    __syncthreads();
-    // the thread of row i owns every block (i, j)
+    if (tid == 0) ws[ws_anorm(S)] = 0.0;
+}
+
+// One thread per 3 x 3 block (i, j) of the pattern of K_s: h^2 K_ij I minus the
+// projection Jacobians of the constraints holding both nodes (in the row's
+// incidence order), times T_j^T, plus the mass on the diagonal.
+__global__ __launch_bounds__(kFacBlock) void k_adj_blocks(const SimDev *__restrict__ sims,
+                                                          const int32_t *__restrict__ work) {
+    const AsmSlot w(work);
+    const SimDev &S = sims[w.hidx];
+    const int m = S.m;
+    const int e = (int)(blockIdx.y * kFacBlock + threadIdx.x);
+    if (e >= G(S.ks_ptr)[m]) return;
+    const double hh = S.h * S.h;
+    const int rs = S.af_step0 + w.slot - S.rec_step0;
+    const auto mode = G(S.rec_mode) + (int64_t)rs * m;
+    const auto F = G(S.af) + (int64_t)w.slot * S.af_size;
+    const auto ws = slot_ws(S, w.slot);
+    const auto Gc = ws + 9 * (int64_t)m;
+    const int i = G(S.ks_row)[e], j = G(S.ks_col)[e];
+    const double k = hh * G(S.ks_val)[e];
+    double b[9];
+    for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) b[3 * r + c] = r == c ? k : 0.0;
+    for (int p = G(S.dp_ptr)[e]; p < G(S.dp_ptr)[e + 1]; ++p) {
+        const int c = G(S.dp_con)[p];
+        const double sc = Gc[4 * c];
+        if (sc == 0.0) continue;
+        const double qh[3] = {Gc[4 * c + 1], Gc[4 * c + 2], Gc[4 * c + 3]};
+        const double ai = G(S.dp_coef)[2 * p] * sc;
+        const double f = ai * G(S.dp_coef)[2 * p + 1];
+        for (int r = 0; r < 3; ++r)
+            for (int cc = 0; cc < 3; ++cc) b[3 * r + cc] -= f * ((r == cc ? 1.0 : 0.0) - qh[r] * qh[cc]);
+    }
+    const uint8_t md = mode[j];
+    if (md == STICK) {
+        for (int q = 0; q < 9; ++q) b[q] = 0.0;
+    } else if (md == SLIP) {                          // H_ij T_j^T
+        const auto T = ws + 9 * (int64_t)j;
+        double o[9];
+        for (int r = 0; r < 3; ++r)
+            for (int c = 0; c < 3; ++c)
+                o[3 * r + c] = b[3 * r] * T[3 * c] + b[3 * r + 1] * T[3 * c + 1] + b[3 * r + 2] * T[3 * c + 2];
+        for (int q = 0; q < 9; ++q) b[q] = o[q];
+    }
+    if (i == j) {
+        const double mi = G(S.mass)[i];
+        b[0] += mi; b[4] += mi; b[8] += mi;
+    }
+    const auto d = F + G(S.ks_dst)[e];
+    const int ld = G(S.ks_ld)[e];
+    for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) d[c * ld + r] = b[3 * r + c];
+}
+
+// |A|_inf of each slot: a row of blocks per thread, in the row's order; the
+// maximum over workgroups by an integer maximum of the (non-negative) bits.
+__global__ __launch_bounds__(kFacBlock) void k_adj_norm(const SimDev *__restrict__ sims,
+                                                        const int32_t *__restrict__ work) {
+    const AsmSlot w(work);
+    const SimDev &S = sims[w.hidx];
+    __shared__ double red[kFacBlock / 64];
+    const int i = (int)(blockIdx.y * kFacBlock + threadIdx.x);
+    if ((int)(blockIdx.y * kFacBlock) >= S.m) return;
+    const auto F = G(S.af) + (int64_t)w.slot * S.af_size;
     double anorm = 0.0;
-    for (int i = tid; i < m; i += bd) {
+    if (i < S.m) {
         double rsum[3] = {0.0, 0.0, 0.0};
         for (int e = G(S.ks_ptr)[i]; e < G(S.ks_ptr)[i + 1]; ++e) {
             const auto d = F + G(S.ks_dst)[e];
             const int ld = G(S.ks_ld)[e];
-            const double k = hh * G(S.ks_val)[e];
             for (int r = 0; r < 3; ++r)
-                for (int c = 0; c < 3; ++c) d[c * ld + r] = r == c ? k : 0.0;
-        }
-        for (int p = G(S.inc_ptr)[i]; p < G(S.inc_ptr)[i + 1]; ++p) {
-            const int c = G(S.inc_con)[p];
-            const double sc = Gc[4 * c];
-            if (sc == 0.0) continue;
-            const double qh[3] = {Gc[4 * c + 1], Gc[4 * c + 2], Gc[4 * c + 3]};
-            const double ai = G(S.inc_coef)[p] * sc;
-            const int q0 = G(S.c_ptr)[c], q1 = G(S.c_ptr)[c + 1], e0 = G(S.dp_ptr)[p];
-            for (int q = q0; q < q1; ++q) {
-                const double f = ai * G(S.c_coef)[q];
-                const int e = G(S.dp_ks)[e0 + q - q0];
-                const auto d = F + G(S.ks_dst)[e];
-                const int ld = G(S.ks_ld)[e];
-                for (int r = 0; r < 3; ++r)
-                    for (int cc = 0; cc < 3; ++cc) d[cc * ld + r] -= f * ((r == cc ? 1.0 : 0.0) - qh[r] * qh[cc]);
-            }
-        }
-        for (int e = G(S.ks_ptr)[i]; e < G(S.ks_ptr)[i + 1]; ++e) {
-            const int j = G(S.ks_col)[e];
-            const uint8_t md = mode[j];
-            const auto d = F + G(S.ks_dst)[e];
-            const int ld = G(S.ks_ld)[e];
-            double b[9];
-            for (int r = 0; r < 3; ++r)
-                for (int c = 0; c < 3; ++c) b[3 * r + c] = d[c * ld + r];
-            if (md == STICK) {
-                for (int q = 0; q < 9; ++q) b[q] = 0.0;
-            } else if (md == SLIP) {                      // H_ij T_j^T
-                const auto T = Tb + 9 * (int64_t)j;
-                double o[9];
-                for (int r = 0; r < 3; ++r)
-                    for (int c = 0; c < 3; ++c)
-                        o[3 * r + c] = b[3 * r] * T[3 * c] + b[3 * r + 1] * T[3 * c + 1] + b[3 * r + 2] * T[3 * c + 2];
-                for (int q = 0; q < 9; ++q) b[q] = o[q];
-            }
-            if (i == j) {
-                const double mi = G(S.mass)[i];
-                b[0] += mi; b[4] += mi; b[8] += mi;
-            }
-            for (int r = 0; r < 3; ++r)
-                for (int c = 0; c < 3; ++c) {
-                    d[c * ld + r] = b[3 * r + c];
-                    rsum[r] += fabs(b[3 * r + c]);
-                }
+                for (int c = 0; c < 3; ++c) rsum[r] += fabs(d[c * ld + r]);
         }
         anorm = fmax(anorm, fmax(rsum[0], fmax(rsum[1], rsum[2])));
     }
     anorm = block_max(anorm, red);
-    if (tid == 0) ws[ws_anorm(S)] = anorm;
+    if (threadIdx.x == 0)
+        __hip_atomic_fetch_max((GLOBAL unsigned long long *)(slot_ws(S, w.slot) + ws_anorm(S)),
+                               (unsigned long long)__double_as_longlong(anorm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// wave-wide maximum (every lane), by data-parallel moves within rows of 16
+// lanes, then across rows; NaN operands are ignored
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, 0xf, 0xf, false);
+    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2));
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_move<0x128>(v));                  // rotate a row of 16 by 8, 4, 2, 1
+    v = fmax(v, dpp_move<0x124>(v));
+    v = fmax(v, dpp_move<0x122>(v));
+    v = fmax(v, dpp_move<0x121>(v));
+    v = fmax(v, __shfl_xor(v, 16, 64));
+    return fmax(v, __shfl_xor(v, 32, 64));
 }
 
 // Gauss-Jordan inverse in place of the N x N row-major block D (N <= 16 E,
 // 256 threads), held in registers: thread (ty, tx) owns entries
 // (ty + 16a, tx + 16b).  Pivot rows are chosen by magnitude among the rows not
-// used yet, without swapping rows (pivoting inside the block); with p_k the
-// pivot row of column k, the array ends as X with inverse[k][p_j] = X[p_k][j],
-// which the write-back applies.  Pivots below 1e-13 of the block's largest
-// entry are raised to that floor; returns how many.  Two barriers per column.
+// used yet (ties to the lowest row), without swapping rows (pivoting inside the
+// block); with p_k the pivot row of column k, the array ends as X with
+// inverse[k][p_j] = X[p_k][j], which the write-back applies.  Pivots below
+// 1e-13 of the block's largest entry are raised to that floor; returns how many.
+// Two barriers per column.  The kernel is bound by this serial chain of N
+// columns, so a column costs only its 2 E^2 multiply-adds: every register index
+// is a constant (the column's block is the unrolled outer loop, the pivot row's
+// a uniform switch) and the pivot row and column are overwritten after a
+// uniform update of all entries instead of being tested for entry by entry.
 constexpr int kGjMax = 128;           // largest block (degrees of freedom)
 struct GjShared {
     double col[2][kGjMax];
@@ -1850,67 +1902,72 @@ __device__ __forceinline__ int gj_inverse_regs(GLOBAL double *D, int N, int ld, 
             X[a][b] = (i < N && j < N) ? D[(int64_t)i * ld + j] : 0.0;
             dm = fmax(dm, fabs(X[a][b]));
         }
-    const double floor_ = 1e-13 * block_max(dm, red);
-    bool used0 = false, used1 = false;      // rows lane and lane + 64, tracked by every wave alike
-    int pert = 0;
-    for (int k = 0; k < N; ++k) {
-        double *colk = sh->col[k & 1];
-        const int bk = k >> 4;
-        if (tx == (k & 15)) {
-#pragma unroll
-            for (int a = 0; a < E; ++a) {
-                double v = 0.0;
-#pragma unroll
-                for (int b = 0; b < E; ++b) v = b == bk ? X[a][b] : v;
-                if (ty + 16 * a < N) colk[ty + 16 * a] = v;
-            }
-        }
-        __syncthreads();
-        double best = (lane < N && !used0) ? fabs(colk[lane]) : -1.0;
-        int bi = lane;
-        const double v1 = (lane + 64 < N && !used1) ? fabs(colk[lane + 64]) : -1.0;
-        if (v1 > best) { best = v1; bi = lane + 64; }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ob = __shfl_xor(best, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-        }
-        const int p = bi;
-        if (p == lane) used0 = true;
-        if (p == lane + 64) used1 = true;
-        double piv = colk[p];
-        if (!(fabs(piv) >= floor_)) {
-            piv = piv < 0.0 ? -floor_ : floor_;
-            if (!(piv != 0.0)) piv = 1e-300;
-            ++pert;
-        }
-        if (tid == 0) sh->pk[k] = p;
-        const int ap = p >> 4;
-        if (ty == (p & 15)) {
-#pragma unroll
-            for (int b = 0; b < E; ++b) {
-                double v = 0.0;
-#pragma unroll
-                for (int a = 0; a < E; ++a) v = a == ap ? X[a][b] : v;
-                if (tx + 16 * b < N) sh->row[tx + 16 * b] = v;
-            }
-        }
-        __syncthreads();
-        const double pinv = 1.0 / piv;
-#pragma unroll
-        for (int a = 0; a < E; ++a) {
-            const int i = ty + 16 * a;
-            const double f = i < N ? colk[i] : 0.0;
-#pragma unroll
-            for (int b = 0; b < E; ++b) {
-                const int j = tx + 16 * b;
-                if (i >= N || j >= N) continue;
-                if (i == p) X[a][b] = j == k ? pinv : X[a][b] * pinv;
-                else X[a][b] = j == k ? -f * pinv : X[a][b] - f * sh->row[j] * pinv;
-            }
-        }
+    for (int i = tid; i < kGjMax; i += (int)blockDim.x) {   // entries past N stay 0
+        sh->col[0][i] = sh->col[1][i] = sh->row[i] = 0.0;
+        sh->inv[i] = 0;
     }
+    const double floor_ = 1e-13 * block_max(dm, red);       // (its barriers also order the clears)
+    bool free0 = lane < N, free1 = lane + 64 < N;   // rows lane and lane + 64 not used yet, in every wave alike
+    int pert = 0;
+#pragma unroll
+    for (int bk = 0; bk < E; ++bk)
+        for (int kc = 0; kc < 16; ++kc) {
+            const int k = 16 * bk + kc;
+            if (k >= N) break;
+            double *colk = sh->col[k & 1];
+            if (tx == kc) {
+#pragma unroll
+                for (int a = 0; a < E; ++a) colk[ty + 16 * a] = X[a][bk];
+            }
+            __syncthreads();
+            // largest unused entry of the column; NaN entries only when nothing else is left
+            double c0 = fabs(colk[lane]), c1 = E > 4 ? fabs(colk[lane + 64]) : 0.0;
+            c0 = free0 && c0 >= 0.0 ? c0 : -1.0;
+            c1 = free1 && c1 >= 0.0 ? c1 : -1.0;
+            const double best = wave_max(fmax(c0, c1));
+            const bool any = best >= 0.0;
+            const uint64_t m0 = __ballot(any ? c0 == best : free0), m1 = __ballot(any ? c1 == best : free1);
+            const int p = __builtin_amdgcn_readfirstlane(m0 ? __builtin_ctzll(m0) : 64 + __builtin_ctzll(m1));
+            free0 = free0 && p != lane;
+            free1 = free1 && p != lane + 64;
+            double piv = colk[p];
+            if (!(fabs(piv) >= floor_)) {
+                piv = piv < 0.0 ? -floor_ : floor_;
+                if (!(piv != 0.0)) piv = 1e-300;
+                ++pert;
+            }
+            if (tid == 0) sh->pk[k] = p;
+            const int ap = p >> 4, pr = p & 15;
+#pragma unroll
+            for (int a = 0; a < E; ++a)
+                if (ap == a && ty == pr) {
+#pragma unroll
+                    for (int b = 0; b < E; ++b) sh->row[tx + 16 * b] = X[a][b];
+                }
+            __syncthreads();
+            const double pinv = 1.0 / piv;
+            double f[E], rw[E];
+#pragma unroll
+            for (int a = 0; a < E; ++a) f[a] = colk[ty + 16 * a];
+#pragma unroll
+            for (int b = 0; b < E; ++b) rw[b] = sh->row[tx + 16 * b];
+#pragma unroll
+            for (int a = 0; a < E; ++a)
+#pragma unroll
+                for (int b = 0; b < E; ++b) X[a][b] = __builtin_fma(-(f[a] * rw[b]), pinv, X[a][b]);
+            if (tx == kc) {
+#pragma unroll
+                for (int a = 0; a < E; ++a) X[a][bk] = -f[a] * pinv;
+            }
+#pragma unroll
+            for (int a = 0; a < E; ++a)
+                if (ap == a && ty == pr) {
+#pragma unroll
+                    for (int b = 0; b < E; ++b) X[a][b] = rw[b] * pinv;
+                    if (tx == kc) X[a][bk] = pinv;
+                }
+        }
+    __syncthreads();
     for (int i = tid; i < N; i += (int)blockDim.x) sh->inv[sh->pk[i]] = i;
     __syncthreads();
 #pragma unroll
@@ -1920,161 +1977,249 @@ __device__ __forceinline__ int gj_inverse_regs(GLOBAL double *D, int N, int ld, 
             const int i = ty + 16 * a, j = tx + 16 * b;
             if (i < N && j < N) D[(int64_t)sh->inv[i] * ld + sh->pk[j]] = X[a][b];
         }
-    __syncthreads();
     return pert;
 }
 
-// Schur update of supernode s by descendant d, as a tiled product: target rows
-// a and columns b of R_d (from 3 i0 on) with a or b in s, value -= sum_k
-// Bt_d[k][a] Vt_d[b][k].  64 x 64 output tiles, k in chunks of 16 staged in
-// LDS (tile: 2 x 16 x 64 doubles), a 4 x 4 block of outputs per thread.
-__device__ __forceinline__ void schur_update(const SimDev &S, GLOBAL double *F, const auto &q, const auto &ud,
-                                             double *tile) {
-    const int tid = threadIdx.x;
-    const auto &qd = G(S.lu_sup)[ud.d];
-    const int Nd = 3 * qd.n, Rd = 3 * qd.r, N = 3 * q.n, n = q.n;
-    const int ldnd = qd.ldn, ldrd = qd.ldr, ldn = q.ldn, ldr = q.ldr;
-    const auto Bd = F + qd.off + (int64_t)Nd * ldnd;        // Bt_d: Nd x Rd (row stride ldrd)
-    const auto Vd = Bd + (int64_t)Nd * ldrd;                // Vt_d: Rd x Nd (row stride ldnd)
+// The factorisation of one level of the factor's tree: the Schur updates of the
+// descendants reaching each chunk (finished by earlier levels), the inverse of
+// its diagonal block, then V; a launch each, since their useful parallelism
+// differs (panel tiles, one workgroup, row bands).  As one workgroup per chunk
+// the top levels' updates took 2 - 6 ms of a 72 x 72 step's level.  Blocks are
+// stored transposed: Dt = D^T, Bt = B^T (N x R), Ct = A(t, R_t)^T (R x N),
+// row-major.
+//
+// The products run on the float64 matrix cores: v_mfma_f64_16x16x4 adds its four
+// products one after another by fused multiply-adds, in k order (equal bit for
+// bit to the scalar chain on 5e5 random outputs), at the vector units' rate but
+// with a quarter of their operand traffic, so operands come straight from L2.
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// Schur updates of chunk sn, one workgroup per 63 x 63 tile of its panel (rows
+// and columns: the chunk's nodes, then R_s; kSchurNodes nodes a side; tiles with
+// neither side in the chunk are left out).  The tile's entries stay in registers
+// while the updaters that reach both its sides (a bit per panel tile) are taken
+// in order; updater d's share is sum_k Bt_d[k][a] Vt_d[b][k], formed on its own
+// and then subtracted.  Four wavefronts, 32 x 32 outputs each: rows a along the
+// lanes, so that reads of Bt and the tile's own accesses are contiguous.
+__global__ __launch_bounds__(kFacBlock) void k_adj_schur(const SimDev *__restrict__ sims,
+                                                         const int32_t *__restrict__ work) {
+    const int hidx = work[3 * blockIdx.x], slot = work[3 * blockIdx.x + 1], sn = work[3 * blockIdx.x + 2];
+    const SimDev &S = sims[hidx];
+    const auto &q = G(S.lu_sup)[sn];
+    const int n = q.n, P = n + q.r, ND = (n + kSchurNodes - 1) / kSchurNodes, PT = (P + kSchurNodes - 1) / kSchurNodes;
+    int ta, tb;                                       // row and column tile
+    {
+        const int y = (int)blockIdx.y, in_s = ND * PT;
+        if (y < in_s) { tb = y / PT; ta = y - tb * PT; }
+        else {
+            const int z = y - in_s, w = PT - ND;
+            if (w == 0 || z >= ND * w) return;
+            ta = z / w;
+            tb = ND + z - ta * w;
+        }
+    }
+    const int u_end = G(S.lu_upd_ptr)[sn + 1];
+    int u0 = G(S.lu_upd_ptr)[sn];
+    if (u0 == u_end) return;
+    __shared__ int list[kFacBlock], wcnt[kFacBlock / 64], src[2][kSchurNodes + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int a_w = 32 * (wave & 1), b_w = 32 * (wave >> 1);
+    const auto F = G(S.af) + (int64_t)slot * S.af_size;
+    const int N = 3 * n;
     const auto D = F + q.off;
-    const auto Bp = D + (int64_t)N * ldn;
-    const auto C = Bp + (int64_t)N * ldr;
-    const auto rel = G(S.lu_relmap) + ud.map;
-    const int a0 = 3 * ud.i0, a1 = 3 * ud.i1;
-    double *ta = tile, *tb = tile + 16 * 64;                // ta[k][a], tb[k][b]
-    const int tx = tid & 15, ty = tid >> 4;                  // outputs a = a_t + 4 tx + i, b = b_t + 4 ty + j
-    for (int at = a0; at < Rd; at += 64)
-        for (int bt = a0; bt < Rd; bt += 64) {
-            if (at >= a1 && bt >= a1) continue;             // rows and columns both beyond s
-            double acc[4][4];
+    const auto Bp = D + (int64_t)N * q.ldn;
+    const auto C = Bp + (int64_t)N * q.ldr;
+    // address of tile entry (a, b), null outside the chunk's blocks
+    auto entry = [&](int a, int b) -> GLOBAL double * {
+        if (a >= 3 * kSchurNodes || b >= 3 * kSchurNodes) return nullptr;
+        const int ra = 3 * kSchurNodes * ta + a, rb = 3 * kSchurNodes * tb + b;
+        if (ra >= 3 * P || rb >= 3 * P) return nullptr;
+        if (rb < N) return ra < N ? D + (int64_t)rb * q.ldn + ra : Bp + (int64_t)rb * q.ldr + (ra - N);
+        return ra < N ? C + (int64_t)(rb - N) * q.ldn + ra : nullptr;
+    };
+    v4d T[2][2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-            for (int k0 = 0; k0 < Nd; k0 += 16) {
-                for (int e = tid; e < 16 * 64; e += kFacBlock) {
-                    const int kk = e >> 6, c = e & 63, k = k0 + kk;
-                    ta[e] = (k < Nd && at + c < Rd) ? Bd[(int64_t)k * ldrd + at + c] : 0.0;
-                    const int bb = e >> 4, k2 = k0 + (e & 15);
-                    tb[(e & 15) * 64 + bb] = (k2 < Nd && bt + bb < Rd) ? Vd[(int64_t)(bt + bb) * ldnd + k2] : 0.0;
-                }
-                __syncthreads();
-#pragma unroll 4
-                for (int kk = 0; kk < 16; ++kk) {
-                    double va[4], vb[4];
+        for (int ai = 0; ai < 2; ++ai)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) va[i] = ta[kk * 64 + 4 * tx + i];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) vb[j] = tb[kk * 64 + 4 * ty + j];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[i][j] += va[i] * vb[j];
-                }
-                __syncthreads();
+            for (int r = 0; r < 4; ++r) {
+                const auto e = entry(a_w + 16 * ai + l16, b_w + 16 * bi + 4 * r + kq);
+                T[bi][ai][r] = e ? *e : 0.0;
             }
+    const uint64_t ma = uint64_t(1) << min(ta, 63), mb = uint64_t(1) << min(tb, 63);
+    bool touched = false;
+    for (; u0 < u_end; u0 += kFacBlock) {
+        // the updaters reaching both sides of the tile, in order
+        const uint64_t um = u0 + tid < u_end ? G(S.lu_upd)[u0 + tid].mask : 0;
+        const bool hit = (um & ma) && (um & mb);
+        const uint64_t bal = __ballot(hit);
+        __syncthreads();
+        if (lane == 0) wcnt[wave] = __popcll(bal);
+        __syncthreads();
+        int base = 0, nl = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int w = 0; w < kFacBlock / 64; ++w) { base += w < wave ? wcnt[w] : 0; nl += wcnt[w]; }
+        if (hit) list[base + __popcll(bal & ((uint64_t(1) << lane) - 1))] = u0 + tid;
+        __syncthreads();
+        for (int t = 0; t < nl; ++t) {
+            const auto &ud = G(S.lu_upd)[list[t]];
+            const auto &qd = G(S.lu_sup)[ud.d];
+            // rows of R_d holding the tile's nodes (-1: none); the panel rows
+            // of R_d's rows ascend, so each is met once
+            if (tid < kSchurNodes) { src[0][tid] = -1; src[1][tid] = -1; }
+            __syncthreads();
+            const int i0 = ud.i0, rd = qd.r;
+            for (int i = i0 + tid; i < rd; i += kFacBlock) {
+                const int v = G(S.lu_relmap)[ud.map + i - i0];
+                const int va = v - kSchurNodes * ta, vb = v - kSchurNodes * tb;
+                if (va >= 0 && va < kSchurNodes) src[0][va] = i;
+                if (vb >= 0 && vb < kSchurNodes) src[1][vb] = i;
+            }
+            __syncthreads();
+            const int Nd = 3 * qd.n, ldnd = qd.ldn, ldrd = qd.ldr;
+            const auto Bd = F + qd.off + (int64_t)Nd * ldnd;        // Bt_d: Nd x Rd (row stride ldrd)
+            const auto Vd = Bd + (int64_t)Nd * ldrd;                // Vt_d: Rd x Nd (row stride ldnd)
+            int sa[2], sb[2];                                       // rows of R_d of this lane's operands
+            bool ca[2], cb[2][4];                                   // and whether its outputs have a row / column
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int aa = at + 4 * tx + i, bb = bt + 4 * ty + j;
-                    if (aa >= Rd || bb >= Rd || (aa >= a1 && bb >= a1)) continue;
-                    const int ra = rel[aa / 3 - ud.i0], rb = rel[bb / 3 - ud.i0];
-                    const int ca = aa % 3, cb = bb % 3;
-                    if (bb < a1) {                          // column in s
-                        if (ra < n) D[(int64_t)(3 * rb + cb) * ldn + 3 * ra + ca] -= acc[i][j];
-                        else Bp[(int64_t)(3 * rb + cb) * ldr + 3 * (ra - n) + ca] -= acc[i][j];
-                    } else {                                // row in s, column in R_s
-                        C[(int64_t)(3 * (rb - n) + cb) * ldn + 3 * ra + ca] -= acc[i][j];
+            for (int o = 0; o < 2; ++o) {
+                const int a = a_w + 16 * o + l16, b = b_w + 16 * o + l16;
+                const int ia = a < 3 * kSchurNodes ? src[0][a / 3] : -1, ib = b < 3 * kSchurNodes ? src[1][b / 3] : -1;
+                sa[o] = ia >= 0 ? 3 * ia + a % 3 : -1;
+                sb[o] = ib >= 0 ? 3 * ib + b % 3 : -1;
+                ca[o] = ia >= 0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int bo = b_w + 16 * o + 4 * r + kq;
+                    cb[o][r] = bo < 3 * kSchurNodes && src[1][bo / 3] >= 0;
+                }
+            }
+            __syncthreads();                                        // src is rewritten for the next updater
+            if (!__any(sa[0] >= 0 || sa[1] >= 0) || !__any(sb[0] >= 0 || sb[1] >= 0)) continue;
+            touched = true;
+            v4d acc[2][2];
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int ai = 0; ai < 2; ++ai) acc[bi][ai] = v4d{0.0, 0.0, 0.0, 0.0};
+            const int oa[2] = {max(sa[0], 0), max(sa[1], 0)}, ob[2] = {max(sb[0], 0) * ldnd, max(sb[1], 0) * ldnd};
+            for (int k0 = 0; k0 < Nd; k0 += 16) {
+                double av[4][2], bv[4][2];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int k = k0 + 4 * s + kq, kk = min(k, Nd - 1);
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        const double x = Bd[(int64_t)kk * ldrd + oa[o]], y = Vd[(int64_t)ob[o] + kk];
+                        bv[s][o] = k < Nd && sa[o] >= 0 ? x : 0.0;
+                        av[s][o] = k < Nd && sb[o] >= 0 ? y : 0.0;
                     }
                 }
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                        for (int ai = 0; ai < 2; ++ai)
+                            acc[bi][ai] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][bi], bv[s][ai], acc[bi][ai], 0, 0, 0);
+            }
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                for (int ai = 0; ai < 2; ++ai)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (ca[ai] && cb[bi][r]) T[bi][ai][r] -= acc[bi][ai][r];
         }
+    }
+    if (!touched) return;
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int ai = 0; ai < 2; ++ai)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const auto e = entry(a_w + 16 * ai + l16, b_w + 16 * bi + 4 * r + kq);
+                if (e) *e = T[bi][ai][r];
+            }
+}
+
+// The inverse of each chunk's diagonal block, one workgroup per (handle, slot, chunk).
+template <int E>
+__global__ __launch_bounds__(kFacBlock) void k_adj_invert(const SimDev *__restrict__ sims,
+                                                          const int32_t *__restrict__ work) {
+    const int hidx = work[3 * blockIdx.x], slot = work[3 * blockIdx.x + 1], sn = work[3 * blockIdx.x + 2];
+    const SimDev &S = sims[hidx];
+    __shared__ GjShared sh;
+    __shared__ double red[kFacBlock / 64];
+    const auto &q = G(S.lu_sup)[sn];
+    const int pert = gj_inverse_regs<E>(G(S.af) + (int64_t)slot * S.af_size + q.off, 3 * q.n, q.ldn, &sh, red);
+    if (threadIdx.x == 0) ((GLOBAL int32_t *)(slot_ws(S, slot) + ws_anorm(S) + 1))[sn] = pert;
 }
 
 // V_t = D_t^{-1} A(t, R_t), transposed: Vt = Ct (D^{-1})^T with Ct (R x N) and
-// the stored inverse (D^{-1})^T (N x N), in place over Ct: 64-row bands of Ct,
-// k in chunks of 16 staged in LDS (tile: 64 x 16 + 16 x 128 doubles), a 4 x 4
-// block of outputs per thread and column tile (N <= 128: two column tiles).
-__device__ __forceinline__ void v_product(GLOBAL double *C, GLOBAL const double *Dinv, int R, int N, int ld,
-                                          double *tile) {
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    double *ta = tile, *tb = tile + 64 * 16;                // ta[k][j], tb[k][i]
-    for (int jb = 0; jb < R; jb += 64) {
-        double acc[2][4][4];
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[c][i][j] = 0.0;
-        for (int k0 = 0; k0 < N; k0 += 16) {
-            for (int e = tid; e < 64 * 16; e += kFacBlock) {
-                const int jj = e >> 4, kk = e & 15;
-                ta[kk * 64 + jj] = (jb + jj < R && k0 + kk < N) ? C[(int64_t)(jb + jj) * ld + k0 + kk] : 0.0;
-            }
-            for (int e = tid; e < 16 * 128; e += kFacBlock) {
-                const int kk = e >> 7, ii = e & 127;
-                tb[e] = (k0 + kk < N && ii < N) ? Dinv[(int64_t)(k0 + kk) * ld + ii] : 0.0;
-            }
-            __syncthreads();
-#pragma unroll 4
-            for (int kk = 0; kk < 16; ++kk) {
-                double va[4], vb[2][4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) va[j] = ta[kk * 64 + 4 * ty + j];
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) vb[c][i] = tb[kk * 128 + 64 * c + 4 * tx + i];
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[c][j][i] += va[j] * vb[c][i];
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = jb + 4 * ty + j, col = 64 * c + 4 * tx + i;
-                    if (row < R && col < N) C[(int64_t)row * ld + col] = acc[c][j][i];
-                }
-        __syncthreads();
-    }
-}
-
-// One workgroup per (handle, slot, chunk) of one level of the factor's tree:
-// the Schur updates of the descendants reaching the chunk (finished by earlier
-// launches), the Gauss-Jordan inverse of its diagonal block (E x E register
-// tile per thread, N <= 16 E), then V.  Blocks are stored transposed: Dt = D^T,
-// Bt = B^T (N x R), Ct = A(t, R_t)^T (R x N), row-major.
-constexpr int kFacTile = 64 * 16 + 16 * 128;                 // doubles of LDS for the product tiles
-template <int E>
-__global__ __launch_bounds__(kFacBlock) void k_adj_factor_level(const SimDev *__restrict__ sims,
-                                                                const int32_t *__restrict__ work) {
+// the stored inverse (D^{-1})^T (N x N), in place over Ct: one workgroup per band
+// of kBandRows rows of Ct, a quarter of the columns per wavefront (N <= 128),
+// every row read before any is written.
+__global__ __launch_bounds__(kFacBlock) void k_adj_panel(const SimDev *__restrict__ sims,
+                                                         const int32_t *__restrict__ work) {
     const int hidx = work[3 * blockIdx.x], slot = work[3 * blockIdx.x + 1], sn = work[3 * blockIdx.x + 2];
     const SimDev &S = sims[hidx];
-    const auto F = G(S.af) + (int64_t)slot * S.af_size;
-    const auto ws = slot_ws(S, slot);
-    __shared__ double tile[kFacTile];
-    __shared__ GjShared small;
-    __shared__ double red[kFacBlock / 64];
     const auto &q = G(S.lu_sup)[sn];
-    const int N = 3 * q.n, R = 3 * q.r;
-    const auto D = F + q.off;
+    const int N = 3 * q.n, R = 3 * q.r, ld = q.ldn, jb = kBandRows * (int)blockIdx.y;
+    if (jb >= R) return;
+    const auto D = G(S.af) + (int64_t)slot * S.af_size + q.off;
     const auto C = D + (int64_t)N * q.ldn + (int64_t)N * q.ldr;
-    for (int u = G(S.lu_upd_ptr)[sn]; u < G(S.lu_upd_ptr)[sn + 1]; ++u) {
-        schur_update(S, F, q, G(S.lu_upd)[u], tile);
-        __syncthreads();
+    const int lane = threadIdx.x & 63, c_w = 32 * (threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
+    v4d acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    if (c_w < N) {
+        int64_t oa[2];
+        int ob[2];
+        bool va[2], vb[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int row = jb + 16 * o + l16, col = c_w + 16 * o + l16;
+            va[o] = row < R;
+            vb[o] = col < N;
+            oa[o] = (int64_t)min(row, R - 1) * ld;
+            ob[o] = min(col, N - 1);
+        }
+        for (int k0 = 0; k0 < N; k0 += 16) {
+            double av[4][2], bv[4][2];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = k0 + 4 * s + kq, kk = min(k, N - 1);
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    const double x = C[oa[o] + kk], y = D[(int64_t)kk * ld + ob[o]];
+                    av[s][o] = k < N && va[o] ? x : 0.0;
+                    bv[s][o] = k < N && vb[o] ? y : 0.0;
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s][i], bv[s][j], acc[i][j], 0, 0, 0);
+        }
     }
-    const int pert = gj_inverse_regs<E>(D, N, q.ldn, &small, red);
-    if (R > 0) v_product(C, D, R, N, q.ldn, tile);
-    if (threadIdx.x == 0) ((GLOBAL int32_t *)(ws + ws_anorm(S) + 1))[sn] = pert;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = jb + 16 * i + 4 * r + kq, col = c_w + 16 * j + l16;
+                if (row < R && col < N) C[(int64_t)row * ld + col] = acc[i][j][r];
+            }
 }
 
 // lane j's value of x, for every lane (j wave-uniform)
@@ -2808,18 +2953,30 @@ hipError_t kernel_static_lds(size_t *fwd, size_t *bwd) {
     return hipSuccess;
 }
 
-hipError_t launch_adj_assemble(const SimDev *d_sims, const int32_t *work, int nblocks, hipStream_t st) {
-    if (nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_adj_assemble, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+// nnz, m: largest pattern of K_s and node count among the launch's handles
+hipError_t launch_adj_assemble(const SimDev *d_sims, const int32_t *work, int nslots, int nnz, int m, hipStream_t st) {
+    if (nslots <= 0) return hipSuccess;
+    // enough workgroups to fill the chip, each clearing at least 32 KB of a 40 x 40 slot
+    const int parts = std::max(8, std::min(256, 2048 / nslots));
+    hipLaunchKernelGGL(k_adj_prepare, dim3(nslots, parts), dim3(kFacBlock), 0, st, d_sims, work);
+    hipLaunchKernelGGL(k_adj_blocks, dim3(nslots, (nnz + kFacBlock - 1) / kFacBlock), dim3(kFacBlock), 0, st, d_sims, work);
+    hipLaunchKernelGGL(k_adj_norm, dim3(nslots, (m + kFacBlock - 1) / kFacBlock), dim3(kFacBlock), 0, st, d_sims, work);
     return hipGetLastError();
 }
 
-// nmax: largest diagonal block of the launch's chunks (degrees of freedom, <= kGjMax)
-hipError_t launch_adj_factor_level(const SimDev *d_sims, const int32_t *work, int nblocks, int nmax, hipStream_t st) {
+// One level: nmax: largest diagonal block of its chunks (degrees of freedom,
+// <= kGjMax); tiles: most Schur tiles of a chunk (0: nothing to update); bands:
+// most row bands of a chunk's panel
+hipError_t launch_adj_factor_level(const SimDev *d_sims, const int32_t *work, int nblocks, int nmax, int tiles, int bands,
+                                   hipStream_t st) {
     if (nblocks <= 0) return hipSuccess;
     if (nmax > kGjMax) return hipErrorInvalidValue;
-    if (nmax <= 96) hipLaunchKernelGGL(k_adj_factor_level<6>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
-    else hipLaunchKernelGGL(k_adj_factor_level<8>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+    if (tiles > 0) hipLaunchKernelGGL(k_adj_schur, dim3(nblocks, tiles), dim3(kFacBlock), 0, st, d_sims, work);
+    if (nmax <= 32) hipLaunchKernelGGL(k_adj_invert<2>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+    else if (nmax <= 64) hipLaunchKernelGGL(k_adj_invert<4>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+    else if (nmax <= 96) hipLaunchKernelGGL(k_adj_invert<6>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+    else hipLaunchKernelGGL(k_adj_invert<8>, dim3(nblocks), dim3(kFacBlock), 0, st, d_sims, work);
+    if (bands > 0) hipLaunchKernelGGL(k_adj_panel, dim3(nblocks, bands), dim3(kFacBlock), 0, st, d_sims, work);
     return hipGetLastError();
 }
 

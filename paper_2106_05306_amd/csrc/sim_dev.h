@@ -93,7 +93,10 @@ constexpr int kMaxDevices = 64;
 struct LuUpd {              // supernode s is updated by descendant d: rows [i0, i1) of R_d lie in s
     int32_t d, i0, i1;
     int32_t map;            // offset in lu_relmap of the panel rows (in s) of R_d[i0..r_d)
+    uint64_t mask;          // bit t: R_d[i0..r_d) has a node in panel tile t (bit 63: in a tile >= 63)
 };
+constexpr int kSchurNodes = 21;     // nodes per panel tile of the Schur updates (63 degrees of freedom)
+constexpr int kBandRows = 32;       // rows per workgroup of the panel product
 struct LuSup {              // supernode (chunk) data of the direct adjoint factor
     int32_t c0, n, r;       // first node, nodes, rows of R_s
     int32_t rptr;           // offset of R_s in sup_rows
@@ -242,8 +245,10 @@ struct SimDev {
     const int32_t *lu_relmap;         // panel row in s of each row of R_d from i0 on (< n_s: in s)
     const int64_t *ks_dst;            // [nnz K_s] offset of block (i, j) in a step factor
     const int32_t *ks_ld;             // [nnz K_s] row stride there
-    const int32_t *dp_ptr;            // [n_inc+1] per incidence entry (node i, constraint c):
-    const int32_t *dp_ks;             //   K_s entry of (i, l) for each stencil node l of c
+    const int32_t *ks_row;            // [nnz K_s] row of each entry
+    const int32_t *dp_ptr;            // [nnz K_s + 1] per entry (i, l): the active constraints holding both
+    const int32_t *dp_con;            //   nodes (in node i's incidence order),
+    const double *dp_coef;            //   and their coefficients of i and l (2 per constraint)
     const int32_t *lu_lvl;            // [2*(levels+1)]: per level start of its row gathers, x_R gathers
     const GatherItem *lu_gat;         // backward: x_{R_t} copied into the update slots of chunk t
     const AdjItem *adj_items;         // items of the phases (level l: 3l = D^{-1}, 3l+1 = B, 3l+2 = V)
