@@ -32,9 +32,11 @@ hipError_t launch_adj_assemble(const SimDev *d_sims, const int32_t *work, int ns
 hipError_t launch_adj_factor_level(const SimDev *d_sims, const int32_t *work, int nblocks, int nmax, int tiles, int bands,
                                    hipStream_t st);
 hipError_t noalloc_scratch(void **out);
-hipError_t launch_forward_mw(const SimDev *d, int W, bool mixed, bool mesh, bool lw, size_t lds, int threads,
+hipError_t launch_forward_mw(const SimDev *d, const int32_t *map, int blocks, bool mixed, bool mesh, size_t lds, int threads,
                              hipStream_t st);
+hipError_t mw_static_lds(size_t *bytes);
 hipError_t configure_mw_lds(size_t bytes);
+hipError_t launch_poison(const int64_t *flag, double *x, double *v, int64_t n, hipStream_t st);
 }  // namespace dc
 
 using namespace dc;
@@ -48,9 +50,18 @@ struct sim {
     std::vector<std::pair<void *, int64_t>> owned;   // every device allocation of the handle and its size
     int64_t bytes = 0;                  // their total (what sim_stats reports)
     SimDev *batch_desc = nullptr;       // descriptors of the batched launches this handle leads
-    bool mw_used = false;               // a multi-workgroup forward ran since the last mw_check
-    size_t mw_lds = 0;                  // dynamic LDS of its workgroups
-    bool mw_lw = false;                 // each of them solves its subtree in LDS (else vectors in HBM)
+    // multi-workgroup forward: the solve's items (host copy), for the LDS a
+    // launch on some number of workgroups needs (mw_plan)
+    std::vector<FwdItem> fitems;
+    std::vector<BwdItem> bitems;
+    std::vector<int32_t> lvl_items, lvl_bwd, lvl_root;
+    size_t mw_max_lds = 0;              // dynamic LDS it may use (0: not available for this handle)
+    int mw_cap = 0;                     // workgroups the forward may be split over (below 2: none)
+    int mw_wgs = 0;                     //   and those of this handle's own launches (below 2: k_forward)
+    size_t mw_lds = 0;                  //   and their dynamic LDS
+    bool mw_used = false;               // such a forward ran since the last mw_check
+    int32_t *batch_map = nullptr;       // handle and workgroup of each block of a batched one
+    std::vector<int32_t> h_batch_map;   //   (host copy)
     SimDev hd_noalloc{};                // descriptor of the allocation-free forward (copied to the
                                         //   device scratch on every call; lives as long as the handle)
     int step_info_cap = 0;              // steps the per-step record (hd.step_info) can hold
@@ -114,14 +125,13 @@ namespace {
 int hip_err(hipError_t e) { return e == hipSuccess ? SIM_OK : SIM_EHIP; }
 
 // Nested-dissection leaf size (nodes per leaf supernode) of a mesh of m
-// nodes: 128 where the multi-workgroup forward runs by default (its solves
-// pay per level: at 40 x 40, leaves of 32 / 64 / 128 nodes give 5 / 4 / 3
-// levels and 641 / 684 / 744 cloth steps/s), else 32.  DIFFCLOTH_LEAF
+// nodes: 128 for large ones (the multi-workgroup forward pays per level: at
+// 40 x 40, leaves of 32 / 64 / 128 nodes give 5 / 4 / 3 levels), else 32.  DIFFCLOTH_LEAF
 // overrides it for experiments.
 int leaf_size_default(int m) {
     const char *e = std::getenv("DIFFCLOTH_LEAF");
     const int v = e ? std::atoi(e) : 0;
-    return v >= 4 && v <= 256 ? v : (m >= kMwMinNodes ? 128 : 32);
+    return v >= 4 && v <= 256 ? v : (m >= kTeamNodes ? 128 : 32);
 }
 
 // Largest merged top supernode of P (nodes); DIFFCLOTH_MERGE overrides it for
@@ -147,30 +157,28 @@ int fwd_helpers(sim *const *sims, int n) {
     return h > 0 && (int64_t)n * (1 + h) <= sims[0]->cus ? h : 0;
 }
 
-// Workgroups of a single handle's forward launch (the multi-workgroup kernel
-// when the elimination tree allows it): DIFFCLOTH_FWD_WGS, 0 or 1 = one;
-// unset: as many as the root has subtrees (at most 16) from kMwMinNodes on --
-// below that its barriers cost more than the split saves (24 x 24 nodes: 39
-// against 27 us per PD iteration; 40 x 40: 61 against 73; 64 x 64: 136
-// against 340, measured on MI355X).
-int mw_workgroups_default(int m) {
+// Workgroups a handle's forward is split over: DIFFCLOTH_FWD_WGS, 0 or 1 = one;
+// unset: one per 64 KB of the factor (both copies), which then stays in the
+// workgroups' LDS.
+int mw_workgroups_default(int64_t factor_bytes) {
     const char *e = std::getenv("DIFFCLOTH_FWD_WGS");
     const int v = e ? std::atoi(e) : -1;
     if (v >= 0) return std::min(v, kMwMax);
-    return m >= kMwMinNodes ? kMwMax : 0;
+    return (int)std::min<int64_t>(std::max<int64_t>(2 * factor_bytes / (64 << 10), 8), 128);
 }
 
-// Whether a multi-workgroup forward solves each workgroup's subtree in LDS
-// (DIFFCLOTH_MW_LDS=0: vectors in HBM).
+// Nodes from which a handle's own launches (and batches with such a handle) take
+// the multi-workgroup forward unless DIFFCLOTH_FWD_WGS says otherwise.  Below,
+// one workgroup needs less time than the barriers; us per PD iteration on one
+// workgroup / split: 16 x 16 17.8 / 24.0, 28 x 28 36.9 / 41.1, 34 x 34 59.0 /
+// 61.5, 36 x 36 (where the leaves are larger and the levels fewer) 69.8 / 42.2,
+// 48 x 48 205 / 68.
+constexpr int kMwMinNodes = kTeamNodes;
+
+// Whether the workgroups of a multi-workgroup forward may copy their shares of
+// the factor into LDS (DIFFCLOTH_MW_LDS=0: read from L2).
 bool mw_lds_default() {
     const char *e = std::getenv("DIFFCLOTH_MW_LDS");
-    return !(e && *e == '0');
-}
-
-// Whether each workgroup of a multi-workgroup forward keeps its run of the
-// root's stored inverse in LDS (DIFFCLOTH_MW_ROOT_LDS=0: read from L2).
-bool mw_root_lds_default() {
-    const char *e = std::getenv("DIFFCLOTH_MW_ROOT_LDS");
     return !(e && *e == '0');
 }
 
@@ -178,17 +186,15 @@ bool mw_root_lds_default() {
 int64_t mw_spin_default() {
     const char *e = std::getenv("DIFFCLOTH_MW_SPIN");
     const long long v = e ? std::atoll(e) : -1;
-    return v >= 0 ? (int64_t)v : (int64_t)100000000;       // 1 s
+    return v >= 0 ? (int64_t)v : (int64_t)1000000000;      // 10 s
 }
 
-// Threads per workgroup of the multi-workgroup forward (a multiple of 64 up
-// to 1024; DIFFCLOTH_MW_THREADS).  The work of a subtree is split into items
-// and nodes that any thread count covers in the same arithmetic, so the count
-// changes timing only.
+// Threads per workgroup of the multi-workgroup forward (DIFFCLOTH_MW_THREADS, a
+// multiple of 64; at most kMwThreads run): timing only.
 int mw_threads_default() {
     const char *e = std::getenv("DIFFCLOTH_MW_THREADS");
     const int v = e ? std::atoi(e) : 0;
-    return v >= 64 && v <= 1024 && v % 64 == 0 ? v : 1024;
+    return v >= 64 && v <= 1024 && v % 64 == 0 ? std::min(v, kMwThreads) : kMwThreads;
 }
 
 // prefetch workgroups of a single-handle direct adjoint launch (0: none)
@@ -492,6 +498,50 @@ void spring_incidence(const HostModel &hm, const std::vector<int32_t> &corder, i
     }
 }
 
+// Multi-workgroup forward of handle s on W workgroups: the LDS layout (into d)
+// and the dynamic LDS it takes (bytes); false: not available.  The factor goes
+// into LDS when every workgroup's share fits beside its vectors.
+bool mw_plan(const sim *s, int W, SimDev &d, size_t &bytes) {
+    if (s->mw_max_lds == 0 || W < 1 || W > kMwMax) return false;
+    int64_t pairs = 0, vec = 3, res = 3, own = 1;
+    auto share = [&](int a, int b, int w) { return a + (int)((int64_t)(b - a) * w / W); };
+    for (int w = 0; w < W; ++w) {
+        int64_t p = 0, o = 0;
+        for (size_t l = 0; l < s->lvl_root.size(); ++l) {
+            const int fa = share(s->lvl_items[l], s->lvl_items[l + 1], w), fb = share(s->lvl_items[l], s->lvl_items[l + 1], w + 1);
+            if (fb > fa) {
+                const FwdItem &i0 = s->fitems[fa], &i1 = s->fitems[fb - 1];
+                p += i1.pair + i1.kmax - i0.pair;
+                vec = std::max<int64_t>(vec, 3 * (i1.row + i1.kmax - i0.row));
+                const int64_t nr = 2 * (int64_t)std::max(0, fb - std::max(fa, s->lvl_root[l]));   // rows of root items
+                res = std::max(res, 3 * nr);
+                o += nr;
+            }
+            const int ba = share(s->lvl_bwd[l], s->lvl_bwd[l + 1], w), bb = share(s->lvl_bwd[l], s->lvl_bwd[l + 1], w + 1);
+            if (bb > ba) {
+                const BwdItem &i0 = s->bitems[ba], &i1 = s->bitems[bb - 1];
+                p += i1.pair + i1.n1 + i1.n2 - i0.pair;
+                vec = std::max<int64_t>(vec, 3 * (i1.row + i1.n1 - i0.row + i1.gat + i1.n2 - i0.gat));
+                const int64_t nr = i1.row + 2 - i0.row;
+                res = std::max(res, 3 * nr);
+                o += nr;
+            }
+        }
+        pairs = std::max(pairs, p);
+        own = std::max(own, o);
+    }
+    const int64_t rest = vec + res + kMwNodeDoubles * own;
+    const int64_t fac = mw_lds_default() && (2 * pairs + rest) * 8 <= (int64_t)s->mw_max_lds ? 2 * pairs : 0;
+    if ((fac + rest) * 8 > (int64_t)s->mw_max_lds) return false;
+    d.mw = W;
+    d.mw_lds = fac > 0 ? 1 : 0;
+    d.mw_off_t = (int)fac;
+    d.mw_off_x = (int)(fac + vec);
+    d.mw_off_own = (int)(fac + vec + res);
+    bytes = (size_t)(fac + rest) * 8;
+    return true;
+}
+
 // Build every device table from the host model and upload it.
 void build_device(sim *s) {
     HostModel &hm = s->hm;
@@ -657,6 +707,8 @@ void build_device(sim *s) {
         if (snr[sn] == 0)
             for (int c = sc0[sn]; c < sc0[sn] + sns[sn]; ++c) is_root_row[c] = 1;
     std::vector<FwdItem> fitems;
+    std::vector<int32_t> lvl_root(hm.n_levels, 0);                   // first forward item of a root, per level
+    int32_t fpairs = 0, bpairs = 0;
     std::vector<int> lfmax(hm.n_levels, 1), lbmax(hm.n_levels, 1);   // longest item per level
     auto pick_team = [](int items, int maxlen) {
         int best = 1;
@@ -676,10 +728,8 @@ void build_device(sim *s) {
                     std::vector<GatherItem> &gi, int &fmx, int &bmx) {
         const int c0 = sc0[sn], nsz = sns[sn], ld = nsz + snr[sn];
         if (ld >= 32768) throw std::runtime_error("supernode too large");
-        const int ldp = ld + (ld & 1), nszp = nsz + (nsz & 1);
         const bool root = snr[sn] == 0;
-        (void)ldp;
-        (void)nszp;
+        const int row0 = (int)ri.size(), gat0 = (int)gi.size();
         for (int k = 0; k < nsz; ++k) ri.push_back(RowItem{3 * (c0 + k), up[c0 + k], up[c0 + k + 1], 0});
         int64_t bo = gofft[sn];                       // items' pairs stored one after another (stacked_factor)
         for (int k = 0; k < nsz && !root; k += 2) {  // columns k, k + 1
@@ -689,8 +739,11 @@ void build_device(sim *s) {
             b.n2 = (int16_t)snr[sn];
             b.ybase = 3 * (c0 + k);
             b.ubase = uoff[sn];
-            b.st = 2;                                 // consecutive rows: consecutive 16-byte pairs
             b.two = k + 1 < nsz;
+            b.row = row0 + k;
+            b.gat = gat0;
+            b.pair = bpairs;
+            bpairs += ld - k;
             bi.push_back(b);
             bo += 2 * (int64_t)(ld - k);
             bmx = std::max(bmx, ld - k);
@@ -704,8 +757,10 @@ void build_device(sim *s) {
         for (int r = 0; r < ld; r += 2) {           // rows r, r + 1
             FwdItem f{};
             f.g = (int32_t)fo;
-            f.ld = 2;                                 // consecutive columns: consecutive 16-byte pairs
-            f.kmax = (int16_t)fwd_pair_cols(nsz, r, root);
+            f.kmax = fwd_pair_cols(nsz, r, root);
+            f.row = row0;
+            f.pair = fpairs;
+            fpairs += f.kmax;
             fo += 2 * (int64_t)f.kmax;
             f.tbase = 3 * c0;
             f.out0 = out_of(r);
@@ -716,11 +771,14 @@ void build_device(sim *s) {
     };
     for (int l = 0; l < hm.n_levels; ++l) {
         int fmax = 1, bmax = 1;
-        for (int sn = 0; sn < ns; ++sn) {
-            if (hm.sup_level[sn] != l) continue;
-            if (snr[sn] == 0)
-                for (int k = 0; k < sns[sn]; ++k) root_rows.push_back(3 * (sc0[sn] + k));
-            emit(sn, ritems, fitems, bitems, bgat, fmax, bmax);
+        for (bool roots : {false, true}) {          // a level's root supernodes last
+            if (roots) lvl_root[l] = (int32_t)fitems.size();
+            for (int sn = 0; sn < ns; ++sn) {
+                if (hm.sup_level[sn] != l || (snr[sn] == 0) != roots) continue;
+                if (roots)
+                    for (int k = 0; k < sns[sn]; ++k) root_rows.push_back(3 * (sc0[sn] + k));
+                emit(sn, ritems, fitems, bitems, bgat, fmax, bmax);
+            }
         }
         lrp[l + 1] = (int32_t)ritems.size();
         lip[l + 1] = (int32_t)fitems.size();
@@ -730,176 +788,29 @@ void build_device(sim *s) {
         lbmax[l] = bmax;
         team_adj[2 * l] = team[2 * l] = pick_team(lip[l + 1] - lip[l], fmax);
         team_adj[2 * l + 1] = team[2 * l + 1] = pick_team(lbp[l + 1] - lbp[l], bmax);
-        // a large root (the stored inverse) of a mesh the multi-workgroup
-        // forward serves: 16 lanes per row pair, so that each workgroup's run of
-        // a few row pairs is short (the one-workgroup kernel, which must sum in
-        // the same order, pays about 15 % more on this product)
-        if (l == hm.n_levels - 1 && m >= kMwMinNodes && fmax >= 128) team[2 * l] = std::max(team[2 * l], 16);
+        // a large root (the stored inverse) of a large mesh: 16 lanes per row
+        // pair, so that each workgroup's few row pairs are short (the
+        // one-workgroup kernel, which must sum in the same order, pays about
+        // 15 % more on this product)
+        if (l == hm.n_levels - 1 && m >= kTeamNodes && fmax >= 128) team[2 * l] = std::max(team[2 * l], 16);
     }
-    // Multi-workgroup forward: with one root supernode (the merged top
-    // separators) whose children head subtrees of their own columns, W
-    // workgroups each solve whole subtrees alone and share the root.  Subtrees
-    // go to the least loaded workgroup (factor entries, largest first); every
-    // workgroup also owns a slice of the root's columns.
-    D.mw = 0;
+    // large meshes with one root supernode (the merged top separators): lanes per
+    // item of the levels below it sized for one of the root's subtrees' share of
+    // a level's items (every forward kernel takes the same teams, so all sum in
+    // the same order)
     {
-        const int L = hm.n_levels;
         std::vector<int> parent(ns, -1);
         for (int sn = 0; sn < ns; ++sn)
             if (snr[sn] > 0) parent[sn] = hm.sup_of[rows[rptr[sn]]];
-        int nroot = 0, root = -1;
+        int nroot = 0, root = -1, kids = 0;
         for (int sn = 0; sn < ns; ++sn)
             if (parent[sn] < 0) { ++nroot; root = sn; }
-        std::vector<int> kids;
-        for (int sn = 0; sn < ns; ++sn)
-            if (parent[sn] >= 0 && parent[sn] == root) kids.push_back(sn);
-        // a mesh the multi-workgroup forward serves by default: lanes per item
-        // of the levels below the root sized for one workgroup's share of a
-        // level's items (whether or not that kernel runs: the one-workgroup
-        // kernel takes the same teams, so both sum in the same order)
-        if (m >= kMwMinNodes && nroot == 1 && kids.size() >= 2) {
-            const int Wt = std::min<int>((int)kids.size(), kMwMax);
-            for (int l = 0; l + 1 < L; ++l) {
+        for (int sn = 0; sn < ns; ++sn) kids += parent[sn] >= 0 && parent[sn] == root;
+        if (m >= kTeamNodes && nroot == 1 && kids >= 2) {
+            const int Wt = std::min(kids, kTeamShare);
+            for (int l = 0; l + 1 < hm.n_levels; ++l) {
                 team[2 * l] = pick_team((lip[l + 1] - lip[l] + Wt - 1) / Wt, lfmax[l]);
                 team[2 * l + 1] = pick_team((lbp[l + 1] - lbp[l] + Wt - 1) / Wt, lbmax[l]);
-            }
-        }
-        const int want = mw_workgroups_default(m);
-        int W = std::min<int>({want, (int)kids.size(), kMwMax});
-        bool ok = nroot == 1 && L >= 2 && W >= 2 && sns[root] <= kMwRootMax && hm.sup_level[root] == L - 1;
-        for (int sn = 0; sn < ns && ok; ++sn)
-            if (sn != root && hm.sup_level[sn] == L - 1) ok = false;   // the root alone on the top level
-        if (ok) {
-            std::vector<int> head(ns, -1);          // root child heading each supernode's subtree
-            std::vector<int> kid_of(ns, -1);
-            for (size_t k = 0; k < kids.size(); ++k) kid_of[kids[k]] = (int)k;
-            for (int sn = 0; sn < ns; ++sn) {
-                int t = sn;
-                while (t >= 0 && parent[t] >= 0 && parent[t] != root) t = parent[t];
-                head[sn] = (t >= 0 && parent[t] == root) ? kid_of[t] : -1;
-            }
-            std::vector<double> wt(kids.size(), 0.0);
-            std::vector<int> lo(kids.size(), INT32_MAX), hi(kids.size(), -1), cnt(kids.size(), 0);
-            for (int sn = 0; sn < ns; ++sn) {
-                const int k = head[sn];
-                if (k < 0) continue;
-                wt[k] += (double)sns[sn] * (sns[sn] + snr[sn]);
-                lo[k] = std::min(lo[k], sc0[sn]);
-                hi[k] = std::max(hi[k], sc0[sn] + sns[sn]);
-                cnt[k] += sns[sn];
-            }
-            for (size_t k = 0; k < kids.size(); ++k)
-                if (hi[k] - lo[k] != cnt[k]) ok = false;     // a subtree's columns are contiguous
-            std::vector<int> order(kids.size()), owner(kids.size(), 0);
-            for (size_t k = 0; k < kids.size(); ++k) order[k] = (int)k;
-            std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return wt[a] > wt[b]; });
-            std::vector<double> load(W, 0.0);
-            std::vector<int> nsub(W, 0);
-            for (int k : order) {
-                const int wbest = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-                owner[k] = wbest;
-                load[wbest] += wt[k];
-                ++nsub[wbest];
-            }
-            for (int w = 0; w < W; ++w)
-                if (nsub[w] + 1 > kMwRanges) ok = false;
-            if (ok) {
-                std::vector<int32_t> nodes((size_t)W * kMwRanges * 2, 0);
-                std::vector<int> used(W, 0);
-                for (size_t k = 0; k < kids.size(); ++k) {
-                    const int w = owner[k], r = used[w]++;
-                    nodes[2 * ((size_t)w * kMwRanges + r)] = lo[k];
-                    nodes[2 * ((size_t)w * kMwRanges + r) + 1] = hi[k];
-                }
-                const int rc0 = sc0[root], rn = sns[root];
-                for (int w = 0; w < W; ++w) {           // the root's columns, in W slices
-                    const int r = used[w]++;
-                    nodes[2 * ((size_t)w * kMwRanges + r)] = rc0 + (int)((int64_t)rn * w / W);
-                    nodes[2 * ((size_t)w * kMwRanges + r) + 1] = rc0 + (int)((int64_t)rn * (w + 1) / W);
-                }
-                std::vector<RowItem> mri;
-                std::vector<FwdItem> mfi;
-                std::vector<BwdItem> mbi;
-                std::vector<GatherItem> mgi;
-                const int Q = W * (L - 1);
-                std::vector<int32_t> ptr(4 * ((size_t)Q + 1), 0);     // rows, fwd, bwd, gather
-                for (int w = 0; w < W; ++w)
-                    for (int l = 0; l < L - 1; ++l) {
-                        int fmx = 1, bmx = 1;
-                        for (int sn = 0; sn < ns; ++sn)
-                            if (hm.sup_level[sn] == l && head[sn] >= 0 && owner[head[sn]] == w)
-                                emit(sn, mri, mfi, mbi, mgi, fmx, bmx);
-                        const int q = w * (L - 1) + l + 1;
-                        ptr[q] = (int32_t)mri.size();
-                        ptr[(Q + 1) + q] = (int32_t)mfi.size();
-                        ptr[2 * (Q + 1) + q] = (int32_t)mbi.size();
-                        ptr[3 * (Q + 1) + q] = (int32_t)mgi.size();
-                    }
-                // one subtree per workgroup: its columns and update slots, solved in LDS
-                bool one = (int)kids.size() == W;
-                std::vector<int32_t> win(4 * (size_t)W, 0);
-                size_t need = 0;
-                for (size_t k = 0; k < kids.size() && one; ++k) {
-                    int ulo = INT32_MAX, uhi = -1, nu = 0;
-                    for (int sn = 0; sn < ns; ++sn)
-                        if (head[sn] == (int)k) {
-                            ulo = std::min(ulo, uoff[sn]);
-                            uhi = std::max(uhi, uoff[sn + 1]);
-                            nu += uoff[sn + 1] - uoff[sn];
-                        }
-                    if (uhi - ulo != nu) { one = false; break; }
-                    const int w = owner[k];
-                    win[4 * w] = lo[k];
-                    win[4 * w + 1] = hi[k];
-                    win[4 * w + 2] = ulo;
-                    win[4 * w + 3] = uhi;
-                    need = std::max(need, (size_t)(6 * (hi[k] - lo[k]) + (uhi - ulo)) * sizeof(double));
-                }
-                // the root's forward items (row pairs of its stored inverse) in W
-                // contiguous runs, and where each run's factor entries lie in gval
-                std::vector<int32_t> rootw(4 * (size_t)W, 0);
-                size_t rootc = 0;
-                {
-                    const int i0 = lip[L - 1], nit = lip[L] - lip[L - 1];
-                    for (int w = 0; w < W; ++w) {
-                        const int a = i0 + (int)((int64_t)nit * w / W), b = i0 + (int)((int64_t)nit * (w + 1) / W);
-                        rootw[4 * w] = a;
-                        rootw[4 * w + 1] = b;
-                        if (b > a) {        // an item's pairs follow the previous item's (emit)
-                            const int64_t g0 = fitems[a].g;
-                            const int64_t g1 = (int64_t)fitems[b - 1].g + 2 * (int64_t)fitems[b - 1].kmax;
-                            rootw[4 * w + 2] = (int32_t)g0;
-                            rootw[4 * w + 3] = (int32_t)(g1 - g0);
-                            rootc = std::max(rootc, (size_t)(g1 - g0) * sizeof(double));
-                        }
-                    }
-                }
-                const size_t mw_static = (3 * kMwRootMax + kBlock / 64 + 8) * sizeof(double);
-                int dev = 0, maxlds = 0;
-                const bool attr = hipGetDevice(&dev) == hipSuccess &&
-                                  hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess;
-                // (with node-node contacts a pair's leader updates its follower's row,
-                // which another workgroup's LDS window would hold: vectors in HBM)
-                bool lw = one && attr && mw_lds_default() && !D.self_on && need + mw_static <= (size_t)maxlds;
-                const size_t wbytes = lw ? (need + 15) / 16 * 16 : 0;
-                bool rl = attr && mw_root_lds_default() && rootc > 0 && wbytes + rootc + mw_static <= (size_t)maxlds;
-                if ((lw || rl) && configure_mw_lds((size_t)maxlds - mw_static) != hipSuccess)   // the largest any handle may need
-                    lw = rl = false;
-                if (lw) D.mw_win = upload(s, win);
-                s->mw_lw = lw;
-                s->mw_lds = lw || rl ? std::max<size_t>(wbytes + (rl ? rootc : 0), 8) : 0;
-                D.mw_rootw = upload(s, rootw);
-                D.mw_root_lds = rl ? 1 : 0;
-                D.mw_root_off = (int)(wbytes / sizeof(double));
-                D.mw = W;
-                D.mw_root_c0 = rc0;
-                D.mw_ptr = upload(s, ptr);
-                D.mw_rows = upload(s, mri);
-                D.mw_fitems = upload(s, mfi);
-                D.mw_bitems = upload(s, mbi);
-                D.mw_bgat = upload(s, mgi);
-                D.mw_nodes = upload(s, nodes);
-                D.mw_sync = (uint32_t *)zeros<double>(s, kMwSyncDoubles);
             }
         }
     }
@@ -940,6 +851,12 @@ void build_device(sim *s) {
     D.rows = upload(s, ritems);
     D.fitems = upload(s, fitems);
     D.bitems = upload(s, bitems);
+    D.lvl_root = upload(s, lvl_root);
+    s->fitems = std::move(fitems);
+    s->bitems = std::move(bitems);
+    s->lvl_items = lip;
+    s->lvl_bwd = lbp;
+    s->lvl_root = lvl_root;
     D.sup_rows = upload(s, rows);
     D.gval = upload(s, gval);
     D.gvalt = upload(s, gvalt);
@@ -1199,6 +1116,8 @@ void build_device(sim *s) {
     D.b0 = zeros<double>(s, v3);
     D.rhs = zeros<double>(s, v3);
     D.ysol = zeros<double>(s, v3);
+    D.bsep = zeros<double>(s, v3);
+    D.mw_sync = zeros<uint64_t>(s, kMwSyncWords);
     D.f = zeros<double>(s, v3);
     D.wp = zeros<double>(s, 3 * (size_t)std::max(nca, 1));
     D.mode = zeros<uint8_t>(s, m);
@@ -1273,6 +1192,18 @@ void build_device(sim *s) {
     if (configure_lds(s->max_lds - s->static_fwd, s->max_lds - s->static_bwd) != hipSuccess) s->max_lds = 0;
     plan_lds(s, s->flags_fwd, s->lds_fwd, true);
     plan_lds(s, s->flags_bwd, s->lds_bwd, false);
+    // the multi-workgroup forward: a tree of at least two levels without a root
+    // at the leaves' level (a root node's contact update would overtake the
+    // local step of other workgroups there)
+    size_t mw_static = 0;
+    if (hm.n_levels >= 2 && hm.n_levels <= kMwLevels && s->lvl_root[0] == s->lvl_items[1] &&
+        mw_static_lds(&mw_static) == hipSuccess && mw_static < (size_t)maxlds &&
+        configure_mw_lds((size_t)maxlds - mw_static) == hipSuccess)
+        s->mw_max_lds = (size_t)maxlds - mw_static;
+    const int want = mw_workgroups_default(s->factor_bytes);
+    if (want >= 2 && mw_plan(s, want, D, s->mw_lds)) s->mw_cap = want;
+    s->mw_wgs = m >= kMwMinNodes || std::getenv("DIFFCLOTH_FWD_WGS") ? s->mw_cap : 0;
+    D.mw = s->mw_wgs;
 }
 
 // A batched launch shares one placement: the same greedy choice as for one
@@ -1303,6 +1234,70 @@ size_t batch_lds(sim *const *sims, int n, bool fwd, int &flags) {
         }
     }
     return bytes;
+}
+
+int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, bool mesh, size_t lds, hipStream_t st);
+int mw_limit(const sim *s);
+
+// Workgroups of each handle of a batched forward launch (empty: one each,
+// k_forward).  A PD iteration of a handle takes about 2.5 us per level and
+// direction of its solves (a barrier and the loads after it) and 0.7 ns per pair
+// of factor entries on one workgroup; the workgroups the device can hold go to
+// whichever handle would finish last.
+std::vector<int> batch_workgroups(sim *const *sims, int n) {
+    const int limit = mw_limit(sims[0]);
+    bool want = false;
+    for (int i = 0; i < n; ++i) {
+        if (sims[i]->mw_max_lds == 0) return {};
+        want = want || sims[i]->mw_wgs >= 2;
+    }
+    if (!want || 2 * n > limit) return {};
+    std::vector<int> W(n, 1);
+    std::vector<double> work(n), chain(n);
+    for (int i = 0; i < n; ++i) {
+        work[i] = 0.7e-3 * (double)sims[i]->factor_bytes * 2 / 16;
+        chain[i] = 2.5 * (2 * sims[i]->hm.n_levels - 1);
+    }
+    for (int used = n; used < limit; ++used) {
+        int worst = -1;
+        double tw = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const double t = chain[i] + work[i] / W[i];
+            if (t > tw) { tw = t; worst = i; }
+        }
+        if (worst < 0 || W[worst] >= std::max(sims[worst]->mw_cap, 1)) break;
+        ++W[worst];
+    }
+    return W;
+}
+
+// Batched forward launch: descs (host; completed here for the multi-workgroup
+// kernel) go to d on the stream st, then the launch.
+int launch_batch_forward(sim *const *sims, int n, std::vector<SimDev> &descs, SimDev *d, hipStream_t st) {
+    const std::vector<int> W = batch_workgroups(sims, n);
+    std::vector<int32_t> &map = sims[0]->h_batch_map;
+    map.clear();
+    size_t lds = 0;
+    bool mw = !W.empty();
+    for (int i = 0; i < n && mw; ++i) {
+        size_t b = 0;
+        mw = mw_plan(sims[i], W[i], descs[i], b);
+        lds = std::max(lds, b);
+        for (int w = 0; w < W[i]; ++w) { map.push_back(i); map.push_back(w); }
+    }
+    if (mw && !sims[0]->batch_map) sims[0]->batch_map = (int32_t *)dev_alloc(sims[0], 2 * sizeof(int32_t) * 4 * kMwMax);
+    mw = mw && map.size() <= 2 * 4 * (size_t)kMwMax;
+    int rc = hip_err(hipMemcpyAsync(d, descs.data(), n * sizeof(SimDev), hipMemcpyHostToDevice, st));
+    if (rc) return rc;
+    if (mw) {
+        rc = hip_err(hipMemcpyAsync(sims[0]->batch_map, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+        for (int i = 0; i < n; ++i) sims[i]->mw_used = true;
+        if (!rc) rc = mw_launch(sims[0], d, sims[0]->batch_map, (int)map.size() / 2, has_mesh(sims, n), lds, st);
+        return rc;
+    }
+    int fl = 0;
+    const size_t lb = batch_lds(sims, n, true, fl);
+    return hip_err(launch_forward(d, n, sims[0]->hd.mixed != 0, lb, fl, fwd_helpers(sims, n), has_mesh(sims, n), st));
 }
 
 int push_desc(sim *s) {
@@ -1377,43 +1372,101 @@ std::vector<int> overlap_chunks(const sim *s, int n_steps) {
     return ends;
 }
 
-// Forward over [a, b) from the handle's current state into the record buffer.
-// Forward launch of one handle (descriptor already pushed): the
-// multi-workgroup kernel when the handle's tree allows it, its barrier block
-// cleared first (a fill kernel), else one workgroup (plus prefetchers).
+// Workgroups of multi-workgroup launches wait for each other, so all of them
+// have to be resident: on one device at most the compute units, less
+// kMwNoalloc for an allocation-free forward (which may be captured and is not
+// counted here), may belong to launches that can run at the same time.  A
+// launch of W workgroups on st first waits (on the device) for the oldest ones
+// still in flight that would exceed this; their events are kept in launch order.
+struct MwAdmission {
+    std::mutex mu;
+    struct Entry { hipEvent_t ev; int W; };
+    std::vector<Entry> flight;
+    std::vector<hipEvent_t> spare;                     // at most kSpare
+    static constexpr size_t kSpare = 16;
+
+    void drop_finished() {
+        size_t k = 0;
+        for (size_t i = 0; i < flight.size(); ++i) {
+            if (hipEventQuery(flight[i].ev) == hipErrorNotReady) flight[k++] = flight[i];
+            else if (spare.size() < kSpare) spare.push_back(flight[i].ev);
+            else (void)hipEventDestroy(flight[i].ev);
+        }
+        flight.resize(k);
+    }
+    int before(int W, int limit, hipStream_t st) {
+        drop_finished();
+        int sum = W;
+        size_t i = flight.size();
+        while (i > 0 && sum + flight[i - 1].W <= limit) sum += flight[--i].W;
+        for (size_t j = 0; j < i; ++j)
+            if (hipStreamWaitEvent(st, flight[j].ev, 0) != hipSuccess) return SIM_EHIP;
+        return SIM_OK;
+    }
+    int after(int W, hipStream_t st) {
+        hipEvent_t ev = nullptr;
+        if (!spare.empty()) { ev = spare.back(); spare.pop_back(); }
+        else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return SIM_EHIP;
+        const hipError_t e = hipEventRecord(ev, st);
+        flight.push_back({ev, W});
+        return hip_err(e);
+    }
+};
+MwAdmission &mw_admission() {
+    static MwAdmission per_device[kMaxDevices];
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    return per_device[dev >= 0 && dev < kMaxDevices ? dev : 0];
+}
+int mw_limit(const sim *s) { return std::max(s->cus - kMwNoalloc, 2); }
+
+// A multi-workgroup launch of `blocks` workgroups (see MwAdmission).
+int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, bool mesh, size_t lds, hipStream_t st) {
+    MwAdmission &adm = mw_admission();
+    std::lock_guard<std::mutex> lock(adm.mu);
+    int rc = adm.before(blocks, mw_limit(s), st);
+    if (!rc) rc = hip_err(launch_forward_mw(d, map, blocks, s->hd.mixed != 0, mesh, lds, mw_threads_default(), st));
+    if (!rc) rc = adm.after(blocks, st);
+    return rc;
+}
+
+// Tags the next forward launch of the handle (before its descriptor is copied).
+void arm_forward(sim *s) {
+    ++s->hd.fwd_epoch;
+    s->hd.mw_epoch += uint64_t(1) << 40;
+}
+
+// Forward launch of one handle (descriptor already pushed).
 int launch_single_forward(sim *s) {
     if (s->hd.mw >= 2) {
-        int rc = hip_err(launch_fill((double *)s->hd.mw_sync, 0.0, kMwSyncDoubles, s->stream));
-        if (!rc)
-            rc = hip_err(launch_forward_mw(s->dd, s->hd.mw, s->hd.mixed != 0, has_mesh(&s, 1), s->mw_lw, s->mw_lds,
-                                           mw_threads_default(), s->stream));
         s->mw_used = true;
-        return rc;
+        return mw_launch(s, s->dd, nullptr, s->hd.mw, has_mesh(&s, 1), s->mw_lds, s->stream);
     }
     return hip_err(launch_forward(s->dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, fwd_helpers(&s, 1),
                                   has_mesh(&s, 1), s->stream));
 }
 
+// Forward over [a, b) from the handle's current state into the record buffer.
 int run_forward_range(sim *s, int a, int b) {
     s->hd.step_begin = a;
     s->hd.step_end = b;
     s->hd.rec_step0 = a;
-    ++s->hd.fwd_epoch;
+    arm_forward(s);
     int rc = push_desc(s);
     if (rc) return rc;
     return launch_single_forward(s);
 }
 
 // A multi-workgroup forward launch since the last check gave up at a barrier
-// (a workgroup waited longer than mw_spin): SIM_ESYNC; clears the flag.
+// (a workgroup waited longer than mw_spin): SIM_ESYNC.
 int mw_check(sim *s) {
     if (!s->mw_used) return SIM_OK;
-    uint32_t flag[4] = {0, 0, 0, 0};
-    int rc = hip_err(hipMemcpyAsync(flag, s->hd.mw_sync, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
+    int64_t flag = 0;
+    int rc = hip_err(hipMemcpyAsync(&flag, s->hd.counters + 7, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
     if (!rc) rc = hip_err(hipStreamSynchronize(s->stream));
     if (rc) return rc;
     s->mw_used = false;
-    return flag[2] ? SIM_ESYNC : SIM_OK;
+    return flag ? SIM_ESYNC : SIM_OK;
 }
 
 // Timing event k of the handle's stream (0/1 forward start/end, 2/3 backward).
@@ -1757,7 +1810,7 @@ int forward_overlapped(sim *s, int n_steps, const std::vector<int> &ends) {
         s->hd.step_begin = a;
         s->hd.step_end = b;
         s->hd.rec_step0 = 0;
-        ++s->hd.fwd_epoch;
+        arm_forward(s);
         rc = push_desc(s);
         if (!rc) rc = launch_single_forward(s);
         if (!rc && pa >= 0) {                // the previous chunk, queued behind this one's launch
@@ -1811,11 +1864,13 @@ int forward_all(sim *s, int n_steps, double *x_traj_dev) {
 
 int finish_forward(sim *s, int n_steps, double *xT_dev, double *vT_dev) {
     const int m = s->hd.m;
-    int rc = mw_check(s);
-    if (rc) s->T = -1;                        // nothing usable was recorded
-    if (!rc && xT_dev) rc = hip_err(launch_permute3(s->hd.x, xT_dev, s->d_perm, m, true, s->stream));
+    int rc = SIM_OK;
+    if (xT_dev) rc = hip_err(launch_permute3(s->hd.x, xT_dev, s->d_perm, m, true, s->stream));
     if (!rc && vT_dev) rc = hip_err(launch_permute3(s->hd.v, vT_dev, s->d_perm, m, true, s->stream));
     if (!rc) rc = read_counters(s);
+    if (!rc && s->mw_used && s->counters_host[7]) rc = SIM_ESYNC;
+    s->mw_used = false;
+    if (rc) s->T = -1;                        // nothing usable was recorded
     if (!rc) {
         s->T = n_steps;
         s->phase = 2;
@@ -2057,11 +2112,22 @@ int backward_status(sim *s) {
 int sim_forward(sim_t *s, int32_t n_steps, double *x_traj_dev, double *xT_dev, double *vT_dev) {
     if (!s || n_steps < 1) return SIM_EINVAL;
     return guarded([&] {
-        int rc = prepare_forward(s, n_steps);
-        if (!rc) rc = time_mark(s, 0);
-        if (!rc) rc = forward_all(s, n_steps, x_traj_dev);
-        if (!rc) rc = time_mark(s, 1);
-        if (!rc) rc = finish_forward(s, n_steps, xT_dev, vT_dev);
+        auto pass = [&] {
+            int rc = prepare_forward(s, n_steps);
+            if (!rc) rc = time_mark(s, 0);
+            if (!rc) rc = forward_all(s, n_steps, x_traj_dev);
+            if (!rc) rc = time_mark(s, 1);
+            if (!rc) rc = finish_forward(s, n_steps, xT_dev, vT_dev);
+            return rc;
+        };
+        int rc = pass();
+        if (rc == SIM_ESYNC && !s->hd.mw_absent) {
+            // its workgroups were not all resident in time (the device shared
+            // with other long launches): the same pass on one workgroup
+            s->hd.mw = 0;
+            rc = pass();
+            s->hd.mw = s->mw_wgs;
+        }
         s->tev_fwd = rc == SIM_OK;
         return rc;
     });
@@ -2220,7 +2286,7 @@ int sim_stats(const sim_t *cs, sim_stats_t *out) {
     out->adj_pivot_perturbed = s->counters_host[5];
     out->fwd_launches = s->fwd_launches;
     out->lds_flags_fwd = s->flags_fwd;
-    out->fwd_workgroups = s->hd.mw >= 2 ? s->hd.mw : 1;
+    out->fwd_workgroups = std::max(s->mw_wgs, 1);
     out->lds_flags_bwd = s->flags_bwd;
     if (s->tev_fwd) {
         float ms = 0.0f;
@@ -2363,6 +2429,9 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
     d.step_end = n_steps;
     d.rec_step0 = 0;
     d.fwd_epoch = 0;
+    size_t mw_lds = 0;
+    const bool mw = s->mw_wgs >= 2 && mw_plan(s, std::min(s->mw_wgs, kMwNoalloc), d, mw_lds);
+    d.mw_epoch = uint64_t(1) << 40;              // (its barrier block is cleared below)
     SimDev *dd = (SimDev *)(b + L.desc);
     // everything below is enqueued on the handle's stream; nothing allocates,
     // synchronises or clears memory with a memset (the call may be captured)
@@ -2372,8 +2441,16 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
     if (!rc) rc = hip_err(launch_fill(d.f, 0.0, 3 * (int64_t)m, s->stream));        // warm start of step 0
     if (!rc) rc = copy_d2d(s, d.x, s->start_x, v3b);
     if (!rc) rc = copy_d2d(s, d.v, s->start_v, v3b);
-    if (!rc) rc = hip_err(launch_forward(dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, 0, has_mesh(&s, 1),
-                                         s->stream));
+    if (!rc && mw) {
+        rc = hip_err(launch_fill((double *)d.mw_sync, 0.0, kMwSyncWords, s->stream));
+        if (!rc)
+            rc = hip_err(launch_forward_mw(dd, nullptr, d.mw, s->hd.mixed != 0, has_mesh(&s, 1), mw_lds, mw_threads_default(),
+                                           s->stream));
+        // a launch that gave up at a barrier must not pass for a result
+        if (!rc) rc = hip_err(launch_poison(d.counters + 7, d.x, d.v, 3 * (int64_t)m, s->stream));
+    } else if (!rc) {
+        rc = hip_err(launch_forward(dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, 0, has_mesh(&s, 1), s->stream));
+    }
     if (!rc) rc = hip_err(launch_permute3(d.x, xT_dev, s->d_perm, m, true, s->stream));
     if (!rc) rc = hip_err(launch_permute3(d.v, vT_dev, s->d_perm, m, true, s->stream));
     return rc;
@@ -2400,17 +2477,12 @@ int sim_batch_forward(sim_t *const *sims, int32_t n, const int32_t *n_steps, dou
             sims[i]->hd.step_begin = 0;
             sims[i]->hd.step_end = n_steps[i];
             sims[i]->hd.rec_step0 = 0;
-            ++sims[i]->hd.fwd_epoch;
+            arm_forward(sims[i]);
             descs[i] = sims[i]->hd;
             if (!rc) rc = push_desc(sims[i]);
         }
         if (rc) return rc;
-        SimDev *d = batch_descs(s0, n);
-        rc = hip_err(hipMemcpyAsync(d, descs.data(), n * sizeof(SimDev), hipMemcpyHostToDevice, s0->stream));
-        int fl = 0;
-        const size_t lb = batch_lds(sims, n, true, fl);
-        if (!rc) rc = hip_err(launch_forward(d, n, s0->hd.mixed != 0, lb, fl, fwd_helpers(sims, n), has_mesh(sims, n),
-                                             s0->stream));
+        rc = launch_batch_forward(sims, n, descs, batch_descs(s0, n), s0->stream);
         for (int i = 0; i < n && !rc; ++i)
             rc = finish_forward(sims[i], n_steps[i], xT_dev ? xT_dev[i] : nullptr, vT_dev ? vT_dev[i] : nullptr);
         (void)hipStreamSynchronize(s0->stream);
@@ -2478,7 +2550,7 @@ int sim_trim(sim_t *s) {
     for (void **p : {(void **)&s->hd.rec_x, (void **)&s->hd.rec_v, (void **)&s->hd.rec_ubar, (void **)&s->hd.rec_mode,
                      (void **)&s->hd.rec_obst, (void **)&s->ckpt, (void **)&s->gsteps, (void **)&s->hd.af,
                      (void **)&s->hd.af_ws, (void **)&s->d_work, (void **)&s->batch_desc,
-                     (void **)&s->hd.step_info}) {
+                     (void **)&s->batch_map, (void **)&s->hd.step_info}) {
         dev_release(s, *p);
         *p = nullptr;
     }
@@ -2542,7 +2614,7 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
                 h->hd.step_begin = h->cursor;
                 h->hd.step_end = std::min(h->target, h->cursor + steps[i]);
                 h->hd.rec_step0 = 0;
-                ++h->hd.fwd_epoch;
+                arm_forward(h);
                 fw.push_back(h);
                 df.push_back(h->hd);
             } else {
@@ -2565,16 +2637,9 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
         SimDev *room = batch_descs(sims[0], fw.size() + bw.size());
         SimDev *dfd = fw.empty() ? nullptr : room;
         SimDev *dbd = bw.empty() ? nullptr : room + fw.size();
-        if (dfd) rc = hip_err(hipMemcpyAsync(dfd, df.data(), df.size() * sizeof(SimDev), hipMemcpyHostToDevice, sf));
-        if (!rc && dbd) rc = hip_err(hipMemcpyAsync(dbd, db.data(), db.size() * sizeof(SimDev), hipMemcpyHostToDevice, sf));
+        if (dbd) rc = hip_err(hipMemcpyAsync(dbd, db.data(), db.size() * sizeof(SimDev), hipMemcpyHostToDevice, sf));
         if (!rc) rc = hip_err(hipStreamSynchronize(sf));          // descriptors in place before either stream uses them
-        if (!rc && dfd) {
-            int fl = 0;
-            const size_t lb = batch_lds(fw.data(), (int)fw.size(), true, fl);
-            rc = hip_err(launch_forward(dfd, (int)fw.size(), fw[0]->hd.mixed != 0, lb, fl, fwd_helpers(fw.data(), (int)fw.size()),
-                                        has_mesh(fw.data(), (int)fw.size()),
-                                        sf));
-        }
+        if (!rc && dfd) rc = launch_batch_forward(fw.data(), (int)fw.size(), df, dfd, sf);
         if (!rc && dbd) {
             if (!pairs.empty()) rc = factor_pairs(bw[0], dbd, bw, pairs, sb);
             int fl = 0;
@@ -2585,6 +2650,8 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
         const int r1 = hip_err(hipStreamSynchronize(sf));
         const int r2 = hip_err(hipStreamSynchronize(sb));
         if (!rc) rc = r1 ? r1 : r2;
+        for (sim *h : fw)
+            if (!rc) rc = mw_check(h);
         if (rc) return rc;
         for (sim *h : fw) {
             h->cursor = h->hd.step_end;

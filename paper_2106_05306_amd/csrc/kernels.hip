@@ -40,8 +40,26 @@ constexpr uint8_t FREE = 0, TAKEOFF = 1, STICK = 2, SLIP = 3;
 
 // ------------------------------------------------------------------ reductions
 
-__device__ inline double team_sum(double v, int tl) {
-    for (int o = tl >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, tl);
+// a double moved between the lanes of a row of 16 (data-parallel primitive CTRL)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, 0xf, 0xf, false);
+    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2));
+}
+
+// Sum over a team of tl lanes, in lane 0 of the team: halves are added pairwise
+// (lane i + lane i + tl/2, ...).  Within 16 lanes the moves are row shifts of
+// the vector unit instead of LDS permutes (only lane 0's tree is needed).
+__device__ __forceinline__ double team_sum(double v, int tl) {
+    if (tl > 32) v += __shfl_xor(v, 32, 64);
+    if (tl > 16) v += __shfl_xor(v, 16, 64);
+    if (tl > 8) v += dpp_move<0x108>(v);              // row_shl: lane i takes lane i + n
+    if (tl > 4) v += dpp_move<0x104>(v);
+    if (tl > 2) v += dpp_move<0x102>(v);
+    if (tl > 1) v += dpp_move<0x101>(v);
     return v;
 }
 
@@ -129,131 +147,138 @@ __device__ __forceinline__ void announce(int64_t *where, int64_t epoch, int64_t 
     if (threadIdx.x == 0) __hip_atomic_store(where, (epoch << 40) | pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Forward-solve products of items t0, t0 + stride, ... < t1 (rows r, r + 1 of a
-// stacked block G_s times the gathered right-hand side), one team of tl lanes
-// per item; cur / cur2 hold the first item's descriptor (fetched early by the
-// caller), the next one is in flight while the current one is computed.
-// Whole batches of a lane's columns run without bounds checks, the last,
+// Forward product of one item: rows r, r + 1 of a stacked block G_s times the
+// gathered right-hand side, this lane's columns lane, lane + tl, ... (Gb: the
+// item's pairs).  Whole batches of columns run without bounds checks, the last,
 // partial one with them; the columns are taken in the same order either way.
-__device__ __forceinline__ void fwd_products(GLOBAL const v4i *fit, auto gv2, int t0, int t1, int stride,
+__device__ __forceinline__ void fwd_item(auto Gb, auto Tb, int kmax, int tl, int lane, double (&a)[3], double (&b)[3]) {
+    double a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
+    auto acc = [&](v2d g, int k) {
+        const double t0v = Tb[3 * k], t1v = Tb[3 * k + 1], t2v = Tb[3 * k + 2];
+        a0 = fma(g.x, t0v, a0); a1 = fma(g.x, t1v, a1); a2 = fma(g.x, t2v, a2);
+        b0 = fma(g.y, t0v, b0); b1 = fma(g.y, t1v, b1); b2 = fma(g.y, t2v, b2);
+    };
+    const int step = kSolveBatch * tl;
+    int k0 = lane;
+    for (; k0 + (kSolveBatch - 1) * tl < kmax; k0 += step) {
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[k0 + j * tl];   // loads in flight together
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) acc(g[j], k0 + j * tl);
+    }
+    if (k0 < kmax) {
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) {
+            const int k = k0 + j * tl;
+            g[j] = k < kmax ? Gb[k] : v2d{0.0, 0.0};
+        }
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j)
+            if (k0 + j * tl < kmax) acc(g[j], k0 + j * tl);
+    }
+    a[0] = team_sum(a0, tl); a[1] = team_sum(a1, tl); a[2] = team_sum(a2, tl);
+    b[0] = team_sum(b0, tl); b[1] = team_sum(b1, tl); b[2] = team_sum(b2, tl);
+}
+
+// Forward-solve products of items t0, t0 + stride, ... < t1, one team of tl
+// lanes per item; cur / cur2 hold the first item's descriptor (fetched early by
+// the caller), the next one is in flight while the current one is computed.
+__device__ __forceinline__ void fwd_products(GLOBAL const v4i *fit, GLOBAL const v2d *gv2, int t0, int t1, int stride,
                                              int tl, int lane, v4i cur, v4i cur2, auto T, auto Y, auto U) {
     for (int t = t0; t < t1; t += stride) {
         v4i nxt = {0, 0, 0, 0}, nxt2 = {0, 0, 0, 0};  // next descriptor, in flight meanwhile
         if (t + stride < t1) { nxt = fit[2 * (t + stride)]; nxt2 = fit[2 * (t + stride) + 1]; }
-        const auto Gb = gv2 + (cur.x >> 1);
-        const auto Tb = T + cur.z;
-        const int ld2 = (cur.y & 0xffff) >> 1, kmax = cur.y >> 16;
-        double a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
-        auto acc = [&](v2d g, int k) {
-            const double t0v = Tb[3 * k], t1v = Tb[3 * k + 1], t2v = Tb[3 * k + 2];
-            a0 += g.x * t0v; a1 += g.x * t1v; a2 += g.x * t2v;
-            b0 += g.y * t0v; b1 += g.y * t1v; b2 += g.y * t2v;
-        };
-        const int step = kSolveBatch * tl;
-        int k0 = lane;
-        for (; k0 + (kSolveBatch - 1) * tl < kmax; k0 += step) {
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[(k0 + j * tl) * ld2];   // loads in flight together
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) acc(g[j], k0 + j * tl);
-        }
-        if (k0 < kmax) {
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) {
-                const int k = k0 + j * tl;
-                g[j] = k < kmax ? Gb[k * ld2] : v2d{0.0, 0.0};
-            }
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j)
-                if (k0 + j * tl < kmax) acc(g[j], k0 + j * tl);
-        }
-        a0 = team_sum(a0, tl); a1 = team_sum(a1, tl); a2 = team_sum(a2, tl);
-        b0 = team_sum(b0, tl); b1 = team_sum(b1, tl); b2 = team_sum(b2, tl);
+        double a[3], b[3];
+        fwd_item(gv2 + (cur.x >> 1), T + cur.z, cur.y, tl, lane, a, b);
         if (lane == 0) {
-            put_row(cur.w, a0, a1, a2, Y, U);
-            put_row(cur2.x, b0, b1, b2, Y, U);
+            put_row(cur.w, a[0], a[1], a[2], Y, U);
+            put_row(cur2.x, b[0], b[1], b[2], Y, U);
         }
         cur = nxt;
         cur2 = nxt2;
     }
 }
 
-// Backward-solve products of items t0, t0 + stride, ... < t1 (column pairs of
-// a stacked block: x_s = L_ss^{-T} y_s - (B_s L_ss^{-1})^T x_{R_s}, x_{R_s}
-// gathered into the supernode's update slots first).  A lane's rows of the
-// diagonal block come first, then those of B_s; whole batches on either side
-// run without bounds checks, in the same order as the checked batches.
+// Backward product of one item (a column pair of a stacked block:
+// x_s = L_ss^{-T} y_s - (B_s L_ss^{-1})^T x_{R_s}): n rows, the first n1 times
+// y_s (Yb), the others times x_{R_s} (Ub[3 (k - n1)] is row k).  A lane's rows
+// of the diagonal block come first, then those of B_s; whole batches on either
+// side run without bounds checks, in the same order as the checked batches.
+__device__ __forceinline__ void bwd_item(auto Gb, auto Yb, auto Ub, int n1, int n, int tl, int lane, double (&a)[3],
+                                         double (&b)[3]) {
+    double a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
+    auto acc_y = [&](v2d g, int k) {                 // row k < n1: times y_s
+        const double w0 = Yb[3 * k], w1 = Yb[3 * k + 1], w2 = Yb[3 * k + 2];
+        a0 = fma(g.x, w0, a0); a1 = fma(g.x, w1, a1); a2 = fma(g.x, w2, a2);
+        b0 = fma(g.y, w0, b0); b1 = fma(g.y, w1, b1); b2 = fma(g.y, w2, b2);
+    };
+    auto acc_u = [&](v2d g, int k) {                 // row k >= n1: minus times x_{R_s}
+        const int o = 3 * (k - n1);
+        const double w0 = Ub[o], w1 = Ub[o + 1], w2 = Ub[o + 2];
+        a0 = fma(-g.x, w0, a0); a1 = fma(-g.x, w1, a1); a2 = fma(-g.x, w2, a2);
+        b0 = fma(-g.y, w0, b0); b1 = fma(-g.y, w1, b1); b2 = fma(-g.y, w2, b2);
+    };
+    const int step = kSolveBatch * tl;
+    int k0 = lane;
+    for (; k0 + (kSolveBatch - 1) * tl < n1; k0 += step) {   // whole batches of y_s rows
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[k0 + j * tl];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) acc_y(g[j], k0 + j * tl);
+    }
+    if (k0 < n) {                                            // the batch reaching past n1 (checked)
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) {
+            const int k = k0 + j * tl;
+            g[j] = k < n ? Gb[k] : v2d{0.0, 0.0};
+        }
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) {
+            const int k = k0 + j * tl;
+            if (k < n1) acc_y(g[j], k);
+            else if (k < n) acc_u(g[j], k);
+        }
+        k0 += step;
+    }
+    for (; k0 + (kSolveBatch - 1) * tl < n; k0 += step) {    // whole batches of x_{R_s} rows
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[k0 + j * tl];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) acc_u(g[j], k0 + j * tl);
+    }
+    if (k0 < n) {                                            // the last, partial batch
+        v2d g[kSolveBatch];
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j) {
+            const int k = k0 + j * tl;
+            g[j] = k < n ? Gb[k] : v2d{0.0, 0.0};
+        }
+#pragma unroll
+        for (int j = 0; j < kSolveBatch; ++j)
+            if (k0 + j * tl < n) acc_u(g[j], k0 + j * tl);
+    }
+    a[0] = team_sum(a0, tl); a[1] = team_sum(a1, tl); a[2] = team_sum(a2, tl);
+    b[0] = team_sum(b0, tl); b[1] = team_sum(b1, tl); b[2] = team_sum(b2, tl);
+}
+
+// Backward-solve products of items t0, t0 + stride, ... < t1, x_{R_s} gathered
+// into the supernode's update slots first.
 __device__ __forceinline__ void bwd_products(GLOBAL const v4i *bit, GLOBAL const v2d *gt2, int t0, int t1, int stride,
                                              int tl, int lane, v4i cur, v4i cur2, auto Y, auto x, auto U) {
     for (int t = t0; t < t1; t += stride) {
         v4i nxt = {0, 0, 0, 0}, nxt2 = {0, 0, 0, 0};
         if (t + stride < t1) { nxt = bit[2 * (t + stride)]; nxt2 = bit[2 * (t + stride) + 1]; }
-        const auto Gb = gt2 + (cur.x >> 1);
-        const int st2 = cur2.x >> 1;
         const int n1 = cur.y & 0xffff, n = n1 + (cur.y >> 16), yb = cur.z;
-        const auto Yb = Y + yb;
-        const int ub = cur.w - 3 * n1;               // U[ub + 3k] is row k >= n1
-        double a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
-        auto acc_y = [&](v2d g, int k) {                 // row k < n1: times y_s
-            const double w0 = Yb[3 * k], w1 = Yb[3 * k + 1], w2 = Yb[3 * k + 2];
-            a0 += g.x * w0; a1 += g.x * w1; a2 += g.x * w2;
-            b0 += g.y * w0; b1 += g.y * w1; b2 += g.y * w2;
-        };
-        auto acc_u = [&](v2d g, int k) {                 // row k >= n1: minus times x_{R_s}
-            const int o = ub + 3 * k;
-            const double w0 = U[o], w1 = U[o + 1], w2 = U[o + 2];
-            a0 -= g.x * w0; a1 -= g.x * w1; a2 -= g.x * w2;
-            b0 -= g.y * w0; b1 -= g.y * w1; b2 -= g.y * w2;
-        };
-        const int step = kSolveBatch * tl;
-        int k0 = lane;
-        for (; k0 + (kSolveBatch - 1) * tl < n1; k0 += step) {   // whole batches of y_s rows
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[(k0 + j * tl) * st2];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) acc_y(g[j], k0 + j * tl);
-        }
-        if (k0 < n) {                                            // the batch reaching past n1 (checked)
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) {
-                const int k = k0 + j * tl;
-                g[j] = k < n ? Gb[k * st2] : v2d{0.0, 0.0};
-            }
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) {
-                const int k = k0 + j * tl;
-                if (k < n1) acc_y(g[j], k);
-                else if (k < n) acc_u(g[j], k);
-            }
-            k0 += step;
-        }
-        for (; k0 + (kSolveBatch - 1) * tl < n; k0 += step) {    // whole batches of x_{R_s} rows
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) g[j] = Gb[(k0 + j * tl) * st2];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) acc_u(g[j], k0 + j * tl);
-        }
-        if (k0 < n) {                                            // the last, partial batch
-            v2d g[kSolveBatch];
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j) {
-                const int k = k0 + j * tl;
-                g[j] = k < n ? Gb[k * st2] : v2d{0.0, 0.0};
-            }
-#pragma unroll
-            for (int j = 0; j < kSolveBatch; ++j)
-                if (k0 + j * tl < n) acc_u(g[j], k0 + j * tl);
-        }
-        a0 = team_sum(a0, tl); a1 = team_sum(a1, tl); a2 = team_sum(a2, tl);
-        b0 = team_sum(b0, tl); b1 = team_sum(b1, tl); b2 = team_sum(b2, tl);
+        double a[3], b[3];
+        bwd_item(gt2 + (cur.x >> 1), Y + yb, U + cur.w, n1, n, tl, lane, a, b);
         if (lane == 0) {
-            x[yb] = a0; x[yb + 1] = a1; x[yb + 2] = a2;
-            if (cur2.y) { x[yb + 3] = b0; x[yb + 4] = b1; x[yb + 5] = b2; }
+            x[yb] = a[0]; x[yb + 1] = a[1]; x[yb + 2] = a[2];
+            if (cur2.y) { x[yb + 3] = b[0]; x[yb + 4] = b[1]; x[yb + 5] = b[2]; }
         }
         cur = nxt;
         cur2 = nxt2;
@@ -322,6 +347,14 @@ __device__ __forceinline__ void solve_P(const SimDev &S, GLOBAL const int32_t *t
 }
 
 // ------------------------------------------------------------------ geometry
+
+// a.b in one fixed form.  Which products of a sum a compiler fuses may change
+// with the code around it; the forward kernels have to agree bit for bit, so
+// what they share spells its fused multiply-adds out.
+template <class F>
+__device__ __forceinline__ F dot3(F a0, F b0, F a1, F b1, F a2, F b2) {
+    return __builtin_elementwise_fma(a2, b2, __builtin_elementwise_fma(a0, b0, a1 * b1));
+}
 
 // Closest point of triangle T (a, b, c, unit face normal, bounding-ball
 // centre and radius: 16 doubles) to x by Voronoi regions, following the
@@ -468,10 +501,10 @@ __device__ __forceinline__ void contact_frame(const SimDev &S, int o, auto xi, d
     }
     if (ob.type == 0) {
         n[0] = ob.n[0]; n[1] = ob.n[1]; n[2] = ob.n[2];
-        phi = (xi[0] - ob.p[0]) * n[0] + (xi[1] - ob.p[1]) * n[1] + (xi[2] - ob.p[2]) * n[2];
+        phi = dot3(xi[0] - ob.p[0], n[0], xi[1] - ob.p[1], n[1], xi[2] - ob.p[2], n[2]);
     } else {
         const double d0 = xi[0] - ob.p[0], d1 = xi[1] - ob.p[1], d2 = xi[2] - ob.p[2];
-        const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        const double r = sqrt(dot3(d0, d0, d1, d1, d2, d2));
         n[0] = d0 / r; n[1] = d1 / r; n[2] = d2 / r;
         phi = r - ob.radius;
     }
@@ -485,7 +518,7 @@ __device__ __forceinline__ double signed_distance(const ObstacleDev &ob, const d
                 // outside a ball around a closed surface: outside the surface, and
                 // phi > 0 is all the contact test needs (not its value)
                 const double b0 = y[0] - ob.ball[0], b1 = y[1] - ob.ball[1], b2 = y[2] - ob.ball[2];
-                const double db = sqrt(b0 * b0 + b1 * b1 + b2 * b2);
+                const double db = sqrt(dot3(b0, b0, b1, b1, b2, b2));
                 if (db > ob.ball[3]) return db - ob.ball[3];
             }
             double n[3], phi, e[3];
@@ -495,9 +528,9 @@ __device__ __forceinline__ double signed_distance(const ObstacleDev &ob, const d
         }
     }
     if (ob.type == 0)
-        return (y[0] - ob.p[0]) * ob.n[0] + (y[1] - ob.p[1]) * ob.n[1] + (y[2] - ob.p[2]) * ob.n[2];
+        return dot3(y[0] - ob.p[0], ob.n[0], y[1] - ob.p[1], ob.n[1], y[2] - ob.p[2], ob.n[2]);
     const double d0 = y[0] - ob.p[0], d1 = y[1] - ob.p[1], d2 = y[2] - ob.p[2];
-    return sqrt(d0 * d0 + d1 * d1 + d2 * d2) - ob.radius;
+    return sqrt(dot3(d0, d0, d1, d1, d2, d2)) - ob.radius;
 }
 
 // attachment target of rest point X at time t: c + R(axis, omega t)(X - c)
@@ -516,15 +549,15 @@ __device__ __forceinline__ void attach_target(const SimDev &S, auto X, double t,
 // v = ub + f/m; gap-corrected normal velocity.  Decisions in float64.
 __device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const double *n, double phi, double mu,
                                             double h, double mass, double *v, double *f) {
-    const double un = n[0] * ub[0] + n[1] * ub[1] + n[2] * ub[2];
+    const double un = dot3(n[0], ub[0], n[1], ub[1], n[2], ub[2]);
     const double a = un + phi / h;
     if (a > 0.0) {
         v[0] = ub[0]; v[1] = ub[1]; v[2] = ub[2];
         f[0] = f[1] = f[2] = 0.0;
         return TAKEOFF;
     }
-    const double ut0 = ub[0] - un * n[0], ut1 = ub[1] - un * n[1], ut2 = ub[2] - un * n[2];
-    const double tau = sqrt(ut0 * ut0 + ut1 * ut1 + ut2 * ut2);
+    const double ut0 = fma(-un, n[0], ub[0]), ut1 = fma(-un, n[1], ub[1]), ut2 = fma(-un, n[2], ub[2]);
+    const double tau = sqrt(dot3(ut0, ut0, ut1, ut1, ut2, ut2));
     const double vn = -phi / h;
     uint8_t md;
     if (tau <= mu * (-a)) {
@@ -532,9 +565,9 @@ __device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const dou
         md = STICK;
     } else {
         const double k = mu * a / tau;
-        v[0] = vn * n[0] + ut0 + k * ut0;
-        v[1] = vn * n[1] + ut1 + k * ut1;
-        v[2] = vn * n[2] + ut2 + k * ut2;
+        v[0] = fma(k, ut0, fma(vn, n[0], ut0));
+        v[1] = fma(k, ut1, fma(vn, n[1], ut1));
+        v[2] = fma(k, ut2, fma(vn, n[2], ut2));
         md = SLIP;
     }
     f[0] = mass * (v[0] - ub[0]);
@@ -548,21 +581,21 @@ __device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const dou
 // w_c p_c for active constraints [c0, c1) at x^k = x_n + h v^k (local step,
 // constraint-centred; used for curved bending stencils).
 template <bool MIXED>
-__device__ __forceinline__ void local_projection(const SimDev &S, auto XN, auto vk, int c0, int c1) {
+__device__ __forceinline__ void local_projection(const SimDev &S, auto XN, auto vk, auto wp, int c0, int c1) {
     const double h = S.h;
     for (int c = c0 + threadIdx.x; c < c1; c += (int)blockDim.x) {
         double q0 = 0, q1 = 0, q2 = 0;
         for (int p = G(S.c_ptr)[c]; p < G(S.c_ptr)[c + 1]; ++p) {
             const int j = G(S.c_node)[p];
             const double a = G(S.c_coef)[p];
-            q0 += a * (XN[3 * j] + h * vk[3 * j]);
-            q1 += a * (XN[3 * j + 1] + h * vk[3 * j + 1]);
-            q2 += a * (XN[3 * j + 2] + h * vk[3 * j + 2]);
+            q0 = fma(a, fma(h, vk[3 * j], XN[3 * j]), q0);
+            q1 = fma(a, fma(h, vk[3 * j + 1], XN[3 * j + 1]), q1);
+            q2 = fma(a, fma(h, vk[3 * j + 2], XN[3 * j + 2]), q2);
         }
         double p0, p1, p2;
         if (MIXED) {
             const float f0 = (float)q0, f1 = (float)q1, f2 = (float)q2;
-            const float nq = sqrtf(f0 * f0 + f1 * f1 + f2 * f2);
+            const float nq = sqrtf(dot3(f1, f1, f0, f0, f2, f2));
             const float rho = G(S.c_rhof)[c], w = G(S.c_wf)[c];
             float r0, r1, r2;
             if (nq < 1e-12f * rho) {
@@ -574,7 +607,7 @@ __device__ __forceinline__ void local_projection(const SimDev &S, auto XN, auto 
             }
             p0 = (double)(w * r0); p1 = (double)(w * r1); p2 = (double)(w * r2);
         } else {
-            const double nq = sqrt(q0 * q0 + q1 * q1 + q2 * q2);
+            const double nq = sqrt(dot3(q1, q1, q0, q0, q2, q2));
             const double rho = G(S.c_rho)[c], w = G(S.c_w)[c];
             if (nq < 1e-12 * rho) {
                 p0 = w * rho * G(S.c_restdir)[3 * c]; p1 = w * rho * G(S.c_restdir)[3 * c + 1];
@@ -584,7 +617,39 @@ __device__ __forceinline__ void local_projection(const SimDev &S, auto XN, auto 
                 p0 = sc * q0; p1 = sc * q1; p2 = sc * q2;
             }
         }
-        G(S.wp)[3 * c] = p0; G(S.wp)[3 * c + 1] = p1; G(S.wp)[3 * c + 2] = p2;
+        wp[3 * c] = p0; wp[3 * c + 1] = p1; wp[3 * c + 2] = p2;
+    }
+}
+
+// Weighted projection of a spring with record sp (SpringInc), rest length rho
+// and vector q from its other node: w rho q / |q|.
+template <bool MIXED>
+__device__ __forceinline__ void spring_projection(const SimDev &S, v4i sp, double rho, double q0, double q1, double q2,
+                                                  double &p0v, double &p1v, double &p2v) {
+    const int cs = sp.y;
+    const double wr = __longlong_as_double(((long long)sp.w << 32) | (uint32_t)sp.z);
+    if (MIXED) {
+        const float f0 = (float)q0, f1 = (float)q1, f2 = (float)q2;
+        const float nq = sqrtf(dot3(f0, f0, f1, f1, f2, f2));
+        const float wrf = (float)wr;
+        if (nq < 1e-12f * (float)rho) {
+            const auto rd = G(S.c_restdir) + 3 * (cs >= 0 ? cs : ~cs);
+            const float sg = cs >= 0 ? wrf : -wrf;
+            p0v = (double)(sg * (float)rd[0]); p1v = (double)(sg * (float)rd[1]); p2v = (double)(sg * (float)rd[2]);
+        } else {
+            const float sc = wrf / nq;
+            p0v = (double)(sc * f0); p1v = (double)(sc * f1); p2v = (double)(sc * f2);
+        }
+    } else {
+        const double nq = sqrt(dot3(q0, q0, q1, q1, q2, q2));
+        if (nq < 1e-12 * rho) {
+            const auto rd = G(S.c_restdir) + 3 * (cs >= 0 ? cs : ~cs);
+            const double sg = cs >= 0 ? wr : -wr;
+            p0v = sg * rd[0]; p1v = sg * rd[1]; p2v = sg * rd[2];
+        } else {
+            const double sc = wr / nq;
+            p0v = sc * q0; p1v = sc * q1; p2v = sc * q2;
+        }
     }
 }
 
@@ -602,8 +667,8 @@ __device__ __forceinline__ void spring_rhs(const SimDev &S, auto XN, auto V, aut
         const int p0 = G(S.sinc_ptr)[i], p1 = G(S.sinc_ptr)[i + 1];
         // q = (x_i + h v_i) - (x_j + h v_j) = sign (x_a - x_b) exactly, so the
         // two nodes of a spring add exact negatives
-        const double y0 = XN[3 * i] + h * V[3 * i], y1 = XN[3 * i + 1] + h * V[3 * i + 1],
-                     y2 = XN[3 * i + 2] + h * V[3 * i + 2];
+        const double y0 = fma(h, V[3 * i], XN[3 * i]), y1 = fma(h, V[3 * i + 1], XN[3 * i + 1]),
+                     y2 = fma(h, V[3 * i + 2], XN[3 * i + 2]);
         const auto rec = (GLOBAL const v4i *)S.sinc;       // SpringInc as 16 bytes
         for (int pb = p0; pb < p1; pb += 8) {
             v4i spv[8];
@@ -614,35 +679,12 @@ __device__ __forceinline__ void spring_rhs(const SimDev &S, auto XN, auto V, aut
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 if (pb + j >= p1) break;
-                const int nj = spv[j].x, cs = spv[j].y;
-                const double wr = __longlong_as_double(((long long)spv[j].w << 32) | (uint32_t)spv[j].z);
-                const double q0 = y0 - (XN[3 * nj] + h * V[3 * nj]);
-                const double q1 = y1 - (XN[3 * nj + 1] + h * V[3 * nj + 1]);
-                const double q2 = y2 - (XN[3 * nj + 2] + h * V[3 * nj + 2]);
+                const int nj = spv[j].x;
+                const double q0 = y0 - fma(h, V[3 * nj], XN[3 * nj]);
+                const double q1 = y1 - fma(h, V[3 * nj + 1], XN[3 * nj + 1]);
+                const double q2 = y2 - fma(h, V[3 * nj + 2], XN[3 * nj + 2]);
                 double p0v, p1v, p2v;
-                if (MIXED) {
-                    const float f0 = (float)q0, f1 = (float)q1, f2 = (float)q2;
-                    const float nq = sqrtf(f0 * f0 + f1 * f1 + f2 * f2);
-                    const float wrf = (float)wr;
-                    if (nq < 1e-12f * (float)rhov[j]) {
-                        const auto rd = G(S.c_restdir) + 3 * (cs >= 0 ? cs : ~cs);
-                        const float sg = cs >= 0 ? wrf : -wrf;
-                        p0v = (double)(sg * (float)rd[0]); p1v = (double)(sg * (float)rd[1]); p2v = (double)(sg * (float)rd[2]);
-                    } else {
-                        const float sc = wrf / nq;
-                        p0v = (double)(sc * f0); p1v = (double)(sc * f1); p2v = (double)(sc * f2);
-                    }
-                } else {
-                    const double nq = sqrt(q0 * q0 + q1 * q1 + q2 * q2);
-                    if (nq < 1e-12 * rhov[j]) {
-                        const auto rd = G(S.c_restdir) + 3 * (cs >= 0 ? cs : ~cs);
-                        const double sg = cs >= 0 ? wr : -wr;
-                        p0v = sg * rd[0]; p1v = sg * rd[1]; p2v = sg * rd[2];
-                    } else {
-                        const double sc = wr / nq;
-                        p0v = sc * q0; p1v = sc * q1; p2v = sc * q2;
-                    }
-                }
+                spring_projection<MIXED>(S, spv[j], rhov[j], q0, q1, q2, p0v, p1v, p2v);
                 r0 += p0v; r1 += p1v; r2 += p2v;
             }
         }
@@ -650,12 +692,12 @@ __device__ __forceinline__ void spring_rhs(const SimDev &S, auto XN, auto V, aut
             for (int p = G(S.binc_ptr)[i]; p < G(S.binc_ptr)[i + 1]; ++p) {
                 const int c = G(S.binc_con)[p];
                 const double a = G(S.binc_coef)[p];
-                r0 += a * G(S.wp)[3 * c]; r1 += a * G(S.wp)[3 * c + 1]; r2 += a * G(S.wp)[3 * c + 2];
+                r0 = fma(a, G(S.wp)[3 * c], r0); r1 = fma(a, G(S.wp)[3 * c + 1], r1); r2 = fma(a, G(S.wp)[3 * c + 2], r2);
             }
         }
-        out[3 * i] = G(S.b0)[3 * i] + h * r0 + G(S.f)[3 * i];
-        out[3 * i + 1] = G(S.b0)[3 * i + 1] + h * r1 + G(S.f)[3 * i + 1];
-        out[3 * i + 2] = G(S.b0)[3 * i + 2] + h * r2 + G(S.f)[3 * i + 2];
+        out[3 * i] = fma(h, r0, G(S.b0)[3 * i]) + G(S.f)[3 * i];
+        out[3 * i + 1] = fma(h, r1, G(S.b0)[3 * i + 1]) + G(S.f)[3 * i + 1];
+        out[3 * i + 2] = fma(h, r2, G(S.b0)[3 * i + 2]) + G(S.f)[3 * i + 2];
     }
 }
 
@@ -749,18 +791,18 @@ __device__ __forceinline__ void fwd_prologue_node(const SimDev &S, int i, double
     for (int p = G(S.ks_ptr)[i]; p < G(S.ks_ptr)[i + 1]; ++p) {
         const int j = G(S.ks_col)[p];
         const double kv = G(S.ks_val)[p];
-        kx0 += kv * G(S.x)[3 * j];
-        kx1 += kv * G(S.x)[3 * j + 1];
-        kx2 += kv * G(S.x)[3 * j + 2];
+        kx0 = fma(kv, G(S.x)[3 * j], kx0);
+        kx1 = fma(kv, G(S.x)[3 * j + 1], kx1);
+        kx2 = fma(kv, G(S.x)[3 * j + 2], kx2);
     }
-    double b[3] = {mi * vi[0] + h * (mi * S.g[0] + fe[0]) - h * kx0,
-                   mi * vi[1] + h * (mi * S.g[1] + fe[1]) - h * kx1,
-                   mi * vi[2] + h * (mi * S.g[2] + fe[2]) - h * kx2};
+    double b[3] = {fma(-h, kx0, fma(mi, vi[0], h * fma(mi, S.g[0], fe[0]))),
+                   fma(-h, kx1, fma(mi, vi[1], h * fma(mi, S.g[1], fe[1]))),
+                   fma(-h, kx2, fma(mi, vi[2], h * fma(mi, S.g[2], fe[2])))};
     const int as = G(S.att_of)[i];
     if (as >= 0) {
         double tg[3];
         attach_target(S, G(S.att_rest) + 3 * as, t1, tg);
-        for (int d = 0; d < 3; ++d) b[d] += h * S.w_att * tg[d];
+        for (int d = 0; d < 3; ++d) b[d] = fma(h * S.w_att, tg[d], b[d]);
     }
     if (S.self_on)
         for (int d = 0; d < 3; ++d) G(S.ybuf)[3 * i + d] = y[d];
@@ -771,7 +813,7 @@ __device__ __forceinline__ void fwd_prologue_node(const SimDev &S, int i, double
     for (int d = 0; d < 3; ++d) {
         G(S.b0)[3 * i + d] = b[d];
         if (!keep) G(S.f)[3 * i + d] = 0.0;
-        A[3 * i + d] = vi[d] + h * ae[d];
+        A[3 * i + d] = fma(h, ae[d], vi[d]);
     }
     if constexpr (KX)
         for (int d = 0; d < 3; ++d) XN[3 * i + d] = xi[d];
@@ -870,7 +912,7 @@ __device__ __forceinline__ void self_pair_setup(const SimDev &S, int i) {
 __device__ __forceinline__ void self_frame(const SimDev &S, int L, int F, auto XN, double *n, double &phi,
                                            double &r) {
     const double e0 = XN[3 * L] - XN[3 * F], e1 = XN[3 * L + 1] - XN[3 * F + 1], e2 = XN[3 * L + 2] - XN[3 * F + 2];
-    r = sqrt(e0 * e0 + e1 * e1 + e2 * e2);
+    r = sqrt(dot3(e0, e0, e1, e1, e2, e2));
     n[0] = e0 / r; n[1] = e1 / r; n[2] = e2 / r;
     phi = r - S.self_d;
 }
@@ -879,14 +921,14 @@ __device__ __forceinline__ void self_frame(const SimDev &S, int L, int F, auto X
 // velocities ub_L = v_L - f/m_L, ub_F = v_F + f/m_F, the closed-form law on
 // their difference with the reduced mass, then v_L = ub_L + f'/m_L,
 // v_F = ub_F - f'/m_F; both nodes' share of the iteration's change.
-__device__ __forceinline__ void self_pair_update(const SimDev &S, int L, int F, auto B, auto XN, auto Vprev,
+__device__ __forceinline__ void self_pair_update(const SimDev &S, int L, int F, auto X, auto B, auto f, auto XN, auto Vprev,
                                                  bool converge, double &dmax) {
     const double mL = G(S.mass)[L], mF = G(S.mass)[F];
     double ubL[3], ubF[3], ur[3], fp[3];
     for (int d = 0; d < 3; ++d) {
-        fp[d] = G(S.f)[3 * L + d];
-        ubL[d] = B[3 * L + d] - fp[d] / mL;
-        ubF[d] = B[3 * F + d] + fp[d] / mF;
+        fp[d] = f[3 * L + d];
+        ubL[d] = X[3 * L + d] - fp[d] / mL;
+        ubF[d] = X[3 * F + d] + fp[d] / mF;
         ur[d] = ubL[d] - ubF[d];
     }
     double nrm[3], phi, r, u[3], fn[3];
@@ -903,32 +945,35 @@ __device__ __forceinline__ void self_pair_update(const SimDev &S, int L, int F, 
         }
         B[3 * L + d] = vL;
         B[3 * F + d] = vF;
-        G(S.f)[3 * L + d] = fn[d];
-        G(S.f)[3 * F + d] = -fn[d];
+        f[3 * L + d] = fn[d];
+        f[3 * F + d] = -fn[d];
         G(S.ubar)[3 * L + d] = ubL[d];
         G(S.ubar)[3 * F + d] = ubF[d];
     }
 }
 
-// Contact update of node i after a global solve (its new velocity in B), and
-// the node's share of the iteration's change max(|dv|, |df| / m).  A pair
-// node: its leader updates both nodes (the follower does nothing here).
-template <bool km>
-__device__ __forceinline__ void fwd_contact_node(const SimDev &S, int i, auto B, auto XN, auto Vprev, bool converge,
-                                                 double &dmax) {
+// Contact update of node i after a global solve (its solution in X; its new
+// velocity goes to B, which may be X itself: COPY false), impulses f, and the
+// node's share of the iteration's change max(|dv|, |df| / m).  A pair node: its
+// leader updates both nodes (the follower does nothing here).
+template <bool km, bool COPY>
+__device__ __forceinline__ void fwd_contact_node(const SimDev &S, int i, auto X, auto B, auto f, auto XN, auto Vprev,
+                                                 bool converge, double &dmax) {
     const double h = S.h;
     if (S.self_on) {
         const int p = G(S.partner)[i];
         if (p >= 0) {
-            if (G(S.caller_id)[i] < G(S.caller_id)[p]) self_pair_update(S, i, p, B, XN, Vprev, converge, dmax);
+            if (G(S.caller_id)[i] < G(S.caller_id)[p]) self_pair_update(S, i, p, X, B, f, XN, Vprev, converge, dmax);
             return;
         }
     }
-    if (G(S.mode)[i] != FREE) {
+    double vv[3] = {X[3 * i], X[3 * i + 1], X[3 * i + 2]};
+    const bool contact = G(S.mode)[i] != FREE;
+    if (contact) {
         const double mi = G(S.mass)[i];
-        const double ub[3] = {B[3 * i] - G(S.f)[3 * i] / mi, B[3 * i + 1] - G(S.f)[3 * i + 1] / mi,
-                              B[3 * i + 2] - G(S.f)[3 * i + 2] / mi};
-        double nrm[3], phi, vv[3], ff[3];
+        const double fo[3] = {f[3 * i], f[3 * i + 1], f[3 * i + 2]};
+        const double ub[3] = {vv[0] - fo[0] / mi, vv[1] - fo[1] / mi, vv[2] - fo[2] / mi};
+        double nrm[3], phi, ff[3];
         bool cached = false;                            // mesh: the frame of the step's start
         if constexpr (km) cached = S.obst[G(S.cobst)[i]].type == 2;
         if (cached) {
@@ -941,14 +986,15 @@ __device__ __forceinline__ void fwd_contact_node(const SimDev &S, int i, auto B,
         for (int d = 0; d < 3; ++d) {
             // the iterate is (v, f): a node held by the contact update
             // keeps its velocity while its impulse may still change
-            if (converge) dmax = fmax(dmax, fabs(ff[d] - G(S.f)[3 * i + d]) / mi);
-            B[3 * i + d] = vv[d];
-            G(S.f)[3 * i + d] = ff[d];
+            if (converge) dmax = fmax(dmax, fabs(ff[d] - fo[d]) / mi);
+            f[3 * i + d] = ff[d];
             G(S.ubar)[3 * i + d] = ub[d];
         }
     }
+    if (COPY || contact)
+        for (int d = 0; d < 3; ++d) B[3 * i + d] = vv[d];
     if (converge)
-        for (int d = 0; d < 3; ++d) dmax = fmax(dmax, fabs(B[3 * i + d] - Vprev[3 * i + d]));
+        for (int d = 0; d < 3; ++d) dmax = fmax(dmax, fabs(vv[d] - Vprev[3 * i + d]));
 }
 
 // Advance and record node i (the converged iterate is in A); counts its mode.
@@ -958,7 +1004,7 @@ __device__ __forceinline__ void fwd_record_node(const SimDev &S, int i, int slot
     const double h = S.h;
     for (int d = 0; d < 3; ++d) {
         const double vv = A[3 * i + d];
-        const double xx = XN[3 * i + d] + h * vv;
+        const double xx = fma(h, vv, XN[3 * i + d]);
         G(S.x)[3 * i + d] = xx;
         G(S.v)[3 * i + d] = vv;
         xn[3 * i + d] = xx;
@@ -1041,7 +1087,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const SimDev *__restrict__ s
         int k = 0;
         while (true) {
             if (S.nca_bend > 0) {
-                local_projection<MIXED>(S, XN, A, S.nca - S.nca_bend, S.nca);
+                local_projection<MIXED>(S, XN, A, G(S.wp), S.nca - S.nca_bend, S.nca);
                 __syncthreads();
             }
             spring_rhs<MIXED>(S, XN, A, B, 0, m);
@@ -1051,7 +1097,7 @@ __global__ __launch_bounds__(kBlock) void k_forward(const SimDev *__restrict__ s
             solve_P(S, G(S.lvl_team), B, B, A, B, U, it_run * 2 * S.n_levels);
             ++it_run;
             double dmax = 0.0;
-            for (int i = threadIdx.x; i < m; i += (int)blockDim.x) fwd_contact_node<km>(S, i, B, XN, Vprev, converge, dmax);
+            for (int i = threadIdx.x; i < m; i += (int)blockDim.x) fwd_contact_node<km, false>(S, i, B, B, G(S.f), XN, Vprev, converge, dmax);
             ++k;
             auto tmp = A; A = B; B = tmp;
             if (converge) {
@@ -1085,154 +1131,365 @@ __global__ __launch_bounds__(kBlock) void k_forward(const SimDev *__restrict__ s
 
 // ------------------------------------------------------------------ multi-workgroup forward
 
-// A right-hand-side vector held from column c0 on (the root's gathered rows in
-// LDS), indexed with the global offsets the work items carry.
-struct Shifted {
-    double *p;
-    int off;
-    __device__ double &operator[](int i) const { return p[i - off]; }
-    __device__ Shifted operator+(int k) const { return Shifted{p, off - k}; }
+// A vector shared by the workgroups of a launch: every access is a relaxed
+// agent-scope atomic, i.e. it passes the caches that are private to a compute
+// unit or an XCD, so the launch's barriers need no cache write-back or
+// invalidation (measured per barrier with 64 doubles exchanged, 128 workgroups:
+// 2.1 us, against 4.8 us with agent fences around plain accesses; 256: 2.2 / 7.7).
+struct SharedRef {
+    GLOBAL double *p;
+    __device__ __forceinline__ operator double() const {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ void operator=(double v) const {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+struct Shared {
+    GLOBAL double *p;
+    __device__ __forceinline__ SharedRef operator[](int i) const { return SharedRef{p + i}; }
 };
 
-// Pairs of factor entries copied into LDS, indexed like the pairs in gval
-// (pair index minus the copy's first pair), for fwd_products.
+// Pairs of factor entries copied into LDS.
 struct LdsPairs {
     const double *p;
-    int off;
-    __device__ LdsPairs operator+(int k) const { return LdsPairs{p, off - k}; }
-    __device__ v2d operator[](int i) const {
-        const int j = 2 * (i - off);
-        return v2d{p[j], p[j + 1]};
+    __device__ __forceinline__ v2d operator[](int i) const { return v2d{p[2 * i], p[2 * i + 1]}; }
+};
+
+// One workgroup's share of a level: forward items [fa, fb), the rows [fr, fr +
+// fn) their products read, backward items [ba, bb), their rows [br, br + bn) and
+// gathers [bq, bq + bqn), the nodes it owns as rows [oa, ob) (columns of its
+// backward items) and [pa, pb) (rows of its root items), the place of those
+// nodes in its list (the backward items' first), the first pair of its forward
+// and backward items in its LDS copy of the factor (minus the items' own pair
+// counts), lanes per item (log2), the level's first root item, whether the level
+// has backward items at all.
+struct MwLevel {
+    int fa, fb, fr, fn, ba, bb, br, bn, bq, bqn, oa, ob, pa, pb, own, fp, bp, ft, bt, root, back;
+};
+
+// The barrier of a handle's workgroups: workgroup w's count of arrivals at
+// words[kMwPad w], the failure flag after the last one.
+struct MwSync {
+    GLOBAL uint64_t *words;
+    uint64_t base, count;                                  // the launch's base; arrivals so far, from there
+    int W, w;
+    uint64_t spin;
+    int *ok;                                               // LDS
+    GLOBAL int64_t *failed;                                // the host's failure flag (counters[7])
+
+    __device__ __forceinline__ GLOBAL uint64_t *fail() const { return words + kMwPad * kMwMax; }
+
+    // This workgroup's stores to shared vectors are done (FENCE: its plain
+    // stores too, by an agent release), and it says so.
+    template <bool FENCE = false>
+    __device__ __forceinline__ void arrive() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        ++count;
+        if (threadIdx.x == 0) {
+            if constexpr (FENCE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __hip_atomic_store(words + kMwPad * w, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // Every workgroup of the handle has arrived (FENCE: an agent acquire after
+    // it).  A wait ends after spin ticks of the 100 MHz wall clock, or when
+    // another workgroup has given up; then the failure flag is raised and every
+    // thread gets false (the kernel returns, the host reports).
+    template <bool FENCE = false>
+    __device__ __forceinline__ bool await() {
+        for (int q = threadIdx.x; q < W; q += (int)blockDim.x) {
+            if (__hip_atomic_load(words + kMwPad * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= count) continue;
+            const uint64_t t0 = wall_clock64();
+            while (__hip_atomic_load(words + kMwPad * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < count) {
+                const uint64_t dt = wall_clock64() - t0;
+                const bool out = dt > spin;
+                if (out) __hip_atomic_store(fail(), count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (out || (dt > 1000 && __hip_atomic_load(fail(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > base)) {
+                    *ok = 0;
+                    *failed = 1;
+                    break;
+                }
+            }
+        }
+        if constexpr (FENCE) {
+            if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        asm volatile("" ::: "memory");
+        __syncthreads();
+        return *ok != 0;
+    }
+    template <bool FENCE = false>
+    __device__ __forceinline__ bool wait() {
+        arrive<FENCE>();
+        return await<FENCE>();
     }
 };
 
-// Copies n doubles (n even, src 16-byte aligned) from global memory into LDS,
-// the whole workgroup, four 16-byte loads per thread in flight.
-__device__ __forceinline__ void lds_copy(double *dst, GLOBAL const double *src, int n) {
-    const auto s2 = (GLOBAL const v2d *)src;
-    const int np = n >> 1, bd = (int)blockDim.x;
-    for (int j = (int)threadIdx.x; j < np; j += 4 * bd) {
-        v2d v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = j + u * bd < np ? s2[j + u * bd] : v2d{0.0, 0.0};
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j + u * bd < np) {
-                dst[2 * (j + u * bd)] = v[u].x;
-                dst[2 * (j + u * bd) + 1] = v[u].y;
-            }
-    }
-}
+// Right-hand side of a row (see spring_rhs) by a group of 4 lanes, two of eight
+// springs per lane, summed in the springs' order.  What does not change during a
+// step (the row, its springs, positions) is loaded ahead, the rest in rhs().
+template <bool MIXED>
+struct RhsTask {
+    int i = 0, p0 = 0, p1 = 0;
+    v4i sp[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    double rho[2] = {0, 0}, xi[3], xj[2][3], b[3];
 
-// Barrier of the S.mw workgroups of a multi-workgroup forward launch (placed
-// on one XCD).  An agent-scope release before arriving and an acquire after
-// leaving make every workgroup's global writes visible to the others.  Thread
-// 0 waits at most S.mw_spin ticks of the 100 MHz wall clock; then, or when
-// another workgroup has already given up, it raises the failure flag, and
-// every thread of the workgroup gets false (the kernel then returns and the
-// host reports the failure).  gen: thread 0's count of barriers passed.
-__device__ __forceinline__ bool mw_barrier(const SimDev &S, uint32_t &gen, int &ok_lds) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t *cnt = S.mw_sync, *gn = S.mw_sync + 1, *fail = S.mw_sync + 2;
-        int ok = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = 0;
-        } else {
-            const uint32_t g = gen;
-            const uint32_t arrived = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-            if (arrived == (uint32_t)S.mw) {
-                __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(gn, g + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                const uint64_t t0 = wall_clock64();
-                while (__hip_atomic_load(gn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g) {
-                    if (__hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-                        wall_clock64() - t0 > (uint64_t)S.mw_spin) {
-                        ok = 0;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
+    __device__ __forceinline__ void row(const SimDev &S, int r, int slot) {
+        i = r;
+        p0 = G(S.sinc_ptr)[i];
+        p1 = G(S.sinc_ptr)[i + 1];
+        springs(S, p0, slot);
+    }
+    __device__ __forceinline__ void springs(const SimDev &S, int p, int slot) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int q = p + slot + 4 * e;
+            sp[e].x = i;
+            if (q < p1) {
+                sp[e] = ((GLOBAL const v4i *)S.sinc)[q];
+                rho[e] = G(S.sinc_rho)[q];
+            }
+        }
+    }
+    __device__ __forceinline__ void positions(auto XN) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            for (int d = 0; d < 3; ++d) xj[e][d] = XN[3 * sp[e].x + d];
+    }
+    __device__ __forceinline__ void constants(const SimDev &S, auto XN) {
+        positions(XN);
+        for (int d = 0; d < 3; ++d) { xi[d] = XN[3 * i + d]; b[d] = G(S.b0)[3 * i + d]; }
+    }
+    __device__ __forceinline__ void rhs(const SimDev &S, auto XN, auto V, auto f, auto wp, int slot, double (&out)[3]) {
+        const double h = S.h;
+        double vj[2][3];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            for (int d = 0; d < 3; ++d) vj[e][d] = V[3 * sp[e].x + d];
+        const double vi[3] = {V[3 * i], V[3 * i + 1], V[3 * i + 2]};
+        const double fi[3] = {f[3 * i], f[3 * i + 1], f[3 * i + 2]};
+        const double y0 = fma(h, vi[0], xi[0]), y1 = fma(h, vi[1], xi[1]), y2 = fma(h, vi[2], xi[2]);
+        double r0 = 0, r1 = 0, r2 = 0;
+        for (int pb = p0; pb < p1; pb += 8) {
+            if (pb > p0) {                                 // more than eight springs
+                springs(S, pb, slot);
+                positions(XN);
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    for (int d = 0; d < 3; ++d) vj[e][d] = V[3 * sp[e].x + d];
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const double q0 = y0 - fma(h, vj[e][0], xj[e][0]);
+                const double q1 = y1 - fma(h, vj[e][1], xj[e][1]);
+                const double q2 = y2 - fma(h, vj[e][2], xj[e][2]);
+                double p0v = 0, p1v = 0, p2v = 0;
+                if (pb + slot + 4 * e < p1) spring_projection<MIXED>(S, sp[e], rho[e], q0, q1, q2, p0v, p1v, p2v);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double s0 = __shfl(p0v, j, 4), s1 = __shfl(p1v, j, 4), s2 = __shfl(p2v, j, 4);
+                    if (pb + 4 * e + j < p1) { r0 += s0; r1 += s1; r2 += s2; }
                 }
             }
-            gen = g + 1u;
         }
-        if (!ok) __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        ok_lds = ok;
+        if (p1 - p0 > 8) springs(S, p0, slot);             // ready for the next iteration
+        if (S.nca_bend > 0)
+            for (int p = G(S.binc_ptr)[i]; p < G(S.binc_ptr)[i + 1]; ++p) {
+                const int c = G(S.binc_con)[p];
+                const double a = G(S.binc_coef)[p];
+                r0 = fma(a, wp[3 * c], r0); r1 = fma(a, wp[3 * c + 1], r1); r2 = fma(a, wp[3 * c + 2], r2);
+            }
+        out[0] = fma(h, r0, b[0]) + fi[0];
+        out[1] = fma(h, r1, b[1]) + fi[1];
+        out[2] = fma(h, r2, b[2]) + fi[2];
     }
-    __syncthreads();
-    return ok_lds != 0;
+};
+
+// Contact state of the owned nodes during a step, in LDS: impulse, frame at x_n
+// and gap, mass, friction, free velocity, mode.
+struct MwNodes {
+    double *f, *nrm, *phi, *mass, *mu, *ub;
+    int *node, *mode;
+    __device__ MwNodes(double *p, int n)
+        : f(p), nrm(p + 3 * n), phi(p + 6 * n), mass(p + 7 * n), mu(p + 8 * n), ub(p + 9 * n), node((int *)(p + 12 * n)),
+          mode((int *)(p + 12 * n) + n) {}
+};
+
+// Contact update of owned node t (fwd_contact_node for a node outside any pair,
+// its state in LDS): solution xs, new velocity to B.
+__device__ __forceinline__ void mw_contact(const MwNodes &N, int t, const double *xs, auto B, auto f, auto Vprev, double h,
+                                           bool converge, double &dmax) {
+    const int i = N.node[t];
+    double vv[3] = {xs[0], xs[1], xs[2]};
+    if (N.mode[t] != FREE) {
+        const double mi = N.mass[t];
+        const double fo[3] = {N.f[3 * t], N.f[3 * t + 1], N.f[3 * t + 2]};
+        const double ub[3] = {vv[0] - fo[0] / mi, vv[1] - fo[1] / mi, vv[2] - fo[2] / mi};
+        const double nrm[3] = {N.nrm[3 * t], N.nrm[3 * t + 1], N.nrm[3 * t + 2]};
+        double ff[3];
+        N.mode[t] = signorini_coulomb(ub, nrm, N.phi[t], N.mu[t], h, mi, vv, ff);
+        for (int d = 0; d < 3; ++d) {
+            if (converge) dmax = fmax(dmax, fabs(ff[d] - fo[d]) / mi);
+            N.f[3 * t + d] = ff[d];
+            f[3 * i + d] = ff[d];
+            N.ub[3 * t + d] = ub[d];
+        }
+    }
+    for (int d = 0; d < 3; ++d) B[3 * i + d] = vv[d];
+    if (converge)
+        for (int d = 0; d < 3; ++d) dmax = fmax(dmax, fabs(vv[d] - Vprev[3 * i + d]));
 }
 
-// Forward steps [step_begin, step_end) of one handle on S.mw workgroups of one
-// XCD (workgroups 8 w; the others of the grid return at once).  Workgroup w
-// owns whole subtrees of the elimination tree below the root supernode and a
-// slice of the root's columns (node ranges S.mw_nodes): it does their step
-// prologue, right-hand side, both triangular solves and contact updates; the
-// root's forward product (its stored inverse) is split over all workgroups in
-// contiguous runs of row pairs, each of which first gathers the root's whole
-// right-hand side into LDS; its run of the stored inverse is copied into LDS
-// once per launch when it fits (S.mw_root_lds).
-// Barriers per PD iteration: after the subtrees' forward solves, after the
-// root product, after the contact updates (and after the bending projections
-// when there are curved bending constraints).  Every node, row and item is
-// computed with the arithmetic of k_forward (same items, team sizes and
-// summation orders), so results are bitwise those of the single-workgroup
-// kernel.  Vectors live in HBM and are shared through the XCD's L2.
-template <bool MIXED, bool km, bool LW>
-__global__ __launch_bounds__(kBlock) void k_forward_mw(const SimDev *__restrict__ sims) {
-    if ((int)blockIdx.x % kXcds != 0) return;
-    const SimDev &S = sims[0];
-    const int W = S.mw, w = (int)blockIdx.x / kXcds;
+// Forward steps [step_begin, step_end) of the launch's handles, each on S.mw
+// workgroups.  Every level of the two triangular solves splits its items evenly
+// over the workgroups, whatever their number; a barrier separates the levels
+// (2 L - 1 per PD iteration: the local step runs with the leaves' forward
+// products, a workgroup computing the rows its items read by itself, and a
+// node's contact update follows its solution in the workgroup that formed it).
+// The kernel is bound by this chain of exchanges (a barrier and the loads after
+// it), not by arithmetic or memory: more workgroups shorten only the work
+// between barriers.  So a workgroup copies its share of the factor into LDS once
+// per launch when it fits, keeps its nodes' contact state there, exchanges
+// vectors past the caches (Shared), and loads what does not depend on the other
+// workgroups (descriptors, offsets, positions, earlier results) between its
+// arrival at a barrier and the wait.  Per PD iteration, against one XCD's 16
+// workgroups with a subtree each (40 x 40, 72 x 72) or one workgroup (100 x 100
+// without allocations): 43 -> 31 us, 174 -> 79 us, 1.2 ms -> 150 us.
+// Every node, row and item is computed with the arithmetic of k_forward (same
+// items, teams and summation orders), so results are bitwise those of the
+// one-workgroup kernel for any number of workgroups.
+template <bool MIXED, bool km>
+__global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restrict__ sims, const int32_t *__restrict__ map) {
+    const SimDev &S = sims[map ? map[2 * blockIdx.x] : 0];
+    const int W = S.mw, w = map ? map[2 * blockIdx.x + 1] : (int)blockIdx.x;
     if (w >= W || (S.mw_absent && w == W - 1)) return;
     extern __shared__ double dyn[];
-    __shared__ double red[kBlock / 64];
-    __shared__ double troot[3 * kMwRootMax];
-    __shared__ int ok_lds;
-    uint32_t gen = 0;
-    const int m = S.m, L = S.n_levels, Q = W * (L - 1);
+    __shared__ double red[kMwThreads / 64];
+    __shared__ MwLevel lv[kMwLevels];
+    __shared__ int ok_lds, n_own_lds[2];
+    const int tid = threadIdx.x, bd = blockDim.x;
+    const int m = S.m, L = S.n_levels;
     const double h = S.h;
-    const bool converge = S.fwd_tol > 0;
-    auto A = G(S.vk);
-    auto B = G(S.rhs);
-    auto U = G(S.ubuf);
-    auto XN = G(S.x);
-    auto Y = G(S.ysol);
-    auto Vprev = G(S.vk1);
+    const bool converge = S.fwd_tol > 0, pairs = S.self_on != 0, bend = S.nca_bend > 0;
+    Shared A{G(S.vk)}, B{G(S.vk1)};                         // velocities before and after the iteration
+    const Shared X{G(S.rhs)}, Y{G(S.ysol)}, U{G(S.ubuf)}, F{G(S.f)}, WP{G(S.wp)}, BS{G(S.bsep)};
+    const auto XN = G(S.x);
+    const auto rows = G(S.rows);
+    const auto upd = G(S.upd_off);
+    const auto bgat = G(S.bgat);
+    const auto fit = (GLOBAL const v4i *)S.fitems;
+    const auto bit = (GLOBAL const v4i *)S.bitems;
     const auto gv2 = (GLOBAL const v2d *)S.gval;
     const auto gt2 = (GLOBAL const v2d *)S.gvalt;
-    auto part = (GLOBAL double *)(S.mw_sync + 4);         // partials: W maxima, then 2 W packed counts
-    if (threadIdx.x == 0) gen = __hip_atomic_load(S.mw_sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int ra[kMwRanges], rb[kMwRanges];
-    for (int r = 0; r < kMwRanges; ++r) {
-        ra[r] = G(S.mw_nodes)[2 * (w * kMwRanges + r)];
-        rb[r] = G(S.mw_nodes)[2 * (w * kMwRanges + r) + 1];
+    const bool in_lds = S.mw_lds != 0;
+    double *const T = dyn + S.mw_off_t, *const xl = dyn + S.mw_off_x;
+    MwSync sync{G(S.mw_sync), S.mw_epoch, S.mw_epoch, W, w, (uint64_t)S.mw_spin, &ok_lds, G(S.counters) + 7};
+    const Shared part{(GLOBAL double *)(S.mw_sync + kMwPad * (kMwMax + 1))};   // W maxima, then 2 W counts
+
+    // ---- this workgroup's shares
+    if (tid == 0) ok_lds = 1;
+    for (int l = tid; l < L; l += bd) {
+        MwLevel q{};
+        const int f0 = G(S.lvl_items_ptr)[l], f1 = G(S.lvl_items_ptr)[l + 1];
+        q.root = G(S.lvl_root)[l];
+        q.ft = __builtin_ctz(G(S.lvl_team)[2 * l]);
+        q.bt = __builtin_ctz(G(S.lvl_team)[2 * l + 1]);
+        q.fa = f0 + (int)((int64_t)(f1 - f0) * w / W);
+        q.fb = f0 + (int)((int64_t)(f1 - f0) * (w + 1) / W);
+        if (q.fb > q.fa) {
+            const auto &i0 = G(S.fitems)[q.fa];
+            const auto &i1 = G(S.fitems)[q.fb - 1];
+            q.fr = i0.row;
+            q.fn = i1.row + i1.kmax - i0.row;
+            const int ra = max(q.fa, q.root);
+            if (ra < q.fb) {                                // root items: their rows' nodes
+                const auto &j0 = G(S.fitems)[ra];
+                q.pa = j0.row + (j0.out0 - j0.tbase) / 3;
+                q.pb = i1.row + (i1.out0 - i1.tbase) / 3 + (i1.out1 >= 0 ? 2 : 1);
+            }
+        }
+        const int c0 = G(S.lvl_bwd_ptr)[l], c1 = G(S.lvl_bwd_ptr)[l + 1];
+        q.back = c1 > c0;
+        q.ba = c0 + (int)((int64_t)(c1 - c0) * w / W);
+        q.bb = c0 + (int)((int64_t)(c1 - c0) * (w + 1) / W);
+        if (q.bb > q.ba) {
+            const auto &i0 = G(S.bitems)[q.ba];
+            const auto &i1 = G(S.bitems)[q.bb - 1];
+            q.br = i0.row;
+            q.bn = i1.row + i1.n1 - i0.row;
+            q.bq = i0.gat;
+            q.bqn = i1.gat + i1.n2 - i0.gat;
+            q.oa = i0.row;
+            q.ob = i1.row + (i1.two ? 2 : 1);
+        }
+        lv[l] = q;
     }
-    auto own = [&](auto &&f) {
-        for (int r = 0; r < kMwRanges; ++r)
-            for (int i = ra[r] + (int)threadIdx.x; i < rb[r]; i += (int)blockDim.x) f(i);
-    };
-    const int rs0 = S.mw_root_c0, rn = S.n_root_rows;
-    const int ys0 = rs0 + (int)((int64_t)rn * w / W), ys1 = rs0 + (int)((int64_t)rn * (w + 1) / W);
-    // LW: the workgroup's one subtree (columns [lo, hi), update slots [ulo, uhi))
-    // is solved in LDS: right-hand side / solution, forward result and update
-    // buffer; what other workgroups read goes out to HBM (the root rows' update
-    // entries after the forward solve, the new iterate after the contact update)
-    const int lo = LW ? G(S.mw_win)[4 * w] : 0, hi = LW ? G(S.mw_win)[4 * w + 1] : 0;
-    const int ulo = LW ? G(S.mw_win)[4 * w + 2] : 0, uhi = LW ? G(S.mw_win)[4 * w + 3] : 0;
-    const int nl = hi - lo;
-    const Shifted sB{dyn, 3 * lo}, sY{dyn + 3 * nl, 3 * lo}, sU{dyn + 6 * nl, ulo};
-    auto TY = pick<LW>(sY, Y);                             // own rows of the solve's vectors
-    auto TU = pick<LW>(sU, U);
-    const int ria = G(S.mw_rootw)[4 * w], rib = G(S.mw_rootw)[4 * w + 1];
-    const int rgb = G(S.mw_rootw)[4 * w + 2], rgc = G(S.mw_rootw)[4 * w + 3];
-    double *rootG = dyn + S.mw_root_off;
-    if (S.mw_root_lds) {                                   // this workgroup's run of the root's inverse
-        lds_copy(rootG, G(S.gval) + rgb, rgc);
-        __syncthreads();
+    __syncthreads();
+    if (tid == 0) {                                         // LDS pairs and owned nodes, level by level
+        int p = 0;
+        for (int l = 0; l < L; ++l) {
+            MwLevel &q = lv[l];
+            if (q.fb > q.fa) {
+                const auto &i0 = G(S.fitems)[q.fa];
+                const auto &i1 = G(S.fitems)[q.fb - 1];
+                q.fp = p - i0.pair;
+                p += i1.pair + i1.kmax - i0.pair;
+            }
+            if (q.bb > q.ba) {
+                const auto &i0 = G(S.bitems)[q.ba];
+                const auto &i1 = G(S.bitems)[q.bb - 1];
+                q.bp = p - i0.pair;
+                p += i1.pair + i1.n1 + i1.n2 - i0.pair;
+            }
+        }
+        int n = 0;
+        for (int l = L - 1; l >= 0; --l) {                  // nodes above the leaves first
+            if (l == 0) n_own_lds[0] = n;
+            lv[l].own = n;
+            n += lv[l].ob - lv[l].oa + lv[l].pb - lv[l].pa;
+        }
+        n_own_lds[1] = n;
     }
+    __syncthreads();
+    const int n_sep = n_own_lds[0], n_own = n_own_lds[1];
+    const MwNodes N(dyn + S.mw_off_own, n_own);
+    for (int l = 0; l < L; ++l) {
+        const MwLevel q = lv[l];
+        const int no = q.ob - q.oa, np = q.pb - q.pa;
+        for (int t = tid; t < no + np; t += bd) N.node[q.own + t] = rows[t < no ? q.oa + t : q.pa + t - no].i3 / 3;
+    }
+    if (in_lds) {                                           // a wavefront copies an item's pairs
+        const int lane = tid & 63, nw = bd >> 6;
+        for (int l = 0; l < L; ++l) {
+            const MwLevel q = lv[l];
+            for (int t = q.fa + (tid >> 6); t < q.fb; t += nw) {
+                const auto &it = G(S.fitems)[t];
+                double *const d = dyn + 2 * (q.fp + it.pair);
+                for (int k = lane; k < it.kmax; k += 64) {
+                    const v2d g = gv2[(it.g >> 1) + k];
+                    d[2 * k] = g.x; d[2 * k + 1] = g.y;
+                }
+            }
+            for (int t = q.ba + (tid >> 6); t < q.bb; t += nw) {
+                const auto &it = G(S.bitems)[t];
+                double *const d = dyn + 2 * (q.bp + it.pair);
+                for (int k = lane; k < it.n1 + it.n2; k += 64) {
+                    const v2d g = gt2[(it.g >> 1) + k];
+                    d[2 * k] = g.x; d[2 * k + 1] = g.y;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    auto each_own = [&](auto &&f) { for (int t = tid; t < n_own; t += bd) f(N.node[t], t); };
+    // the local step's rows: those the leaves' products read, then the owned
+    // rows above the leaves; this thread's first one stays in registers
+    const int fn0 = lv[0].fn, fr0 = lv[0].fr, n_rhs = (fn0 + n_sep) * 4, slt = tid & 3;
+    auto rhs_row = [&](int t) { return t < fn0 ? rows[fr0 + t].i3 / 3 : N.node[t - fn0]; };
+    RhsTask<MIXED> task;
+    if (n_rhs > 0) task.row(S, rhs_row(min(tid, n_rhs - 1) >> 2), slt);
+
     int64_t iters_total = 0;
     for (int n = S.step_begin; n < S.step_end; ++n) {
         const int slot = S.rec_ring ? 0 : n - S.rec_step0;
@@ -1240,152 +1497,243 @@ __global__ __launch_bounds__(kBlock) void k_forward_mw(const SimDev *__restrict_
         auto xrec = G(S.rec_x) + (int64_t)slot * 3 * m;
         auto vrec = G(S.rec_v) + (int64_t)slot * 3 * m;
         const double fs = S.fext == nullptr ? 0.0 : (S.fscale == nullptr ? 1.0 : G(S.fscale)[n]);
-        own([&](int i) { fwd_prologue_node<km, false>(S, i, fs, t1, n == S.step_begin, xrec, vrec, A, XN); });
-        if (!mw_barrier(S, gen, ok_lds)) return;
-        if (S.self_on) {            // node-node contacts: the grid, the search and the pairs over all workgroups
+        each_own([&](int i, int t) {
+            fwd_prologue_node<km, false>(S, i, fs, t1, n == S.step_begin, xrec, vrec, A, XN);
+            if (pairs) return;
+            const uint8_t md = G(S.mode)[i];
+            N.mode[t] = md;
+            if (md != FREE) {                               // the step's contact frame, once
+                const int o = G(S.cobst)[i];
+                double nrm[3], phi;
+                bool cached = false;
+                if constexpr (km) cached = S.obst[o].type == 2;
+                if (cached) {
+                    for (int d = 0; d < 3; ++d) nrm[d] = G(S.cfr)[8 * i + d];
+                    phi = G(S.cfr)[8 * i + 3];
+                } else {
+                    contact_frame<false>(S, o, XN + 3 * i, nrm, phi);
+                }
+                for (int d = 0; d < 3; ++d) {
+                    N.nrm[3 * t + d] = nrm[d];
+                    N.f[3 * t + d] = G(S.f)[3 * i + d];
+                }
+                N.phi[t] = phi;
+                N.mass[t] = G(S.mass)[i];
+                N.mu[t] = S.obst[o].mu;
+            }
+        });
+        if (pairs) {                // node-node contacts: the grid, the search and the pairs over all workgroups
             const int hs = S.self_hmask + 1;
-            for (int b = hs * w / W + (int)threadIdx.x; b < hs * (w + 1) / W; b += (int)blockDim.x)
+            for (int b = (int)((int64_t)hs * w / W) + tid; b < (int)((int64_t)hs * (w + 1) / W); b += bd)
                 G(S.self_head)[b] = -1;
-            if (!mw_barrier(S, gen, ok_lds)) return;
-            own([&](int i) { self_insert(S, i); });
-            if (!mw_barrier(S, gen, ok_lds)) return;
-            own([&](int i) { self_nearest(S, i, XN); });
-            if (!mw_barrier(S, gen, ok_lds)) return;
-            own([&](int i) { self_pair_setup(S, i); });
-            if (!mw_barrier(S, gen, ok_lds)) return;
+            if (!sync.wait<true>()) return;
+            each_own([&](int i, int) { self_insert(S, i); });
+            if (!sync.wait<true>()) return;
+            each_own([&](int i, int) { self_nearest(S, i, XN); });
+            if (!sync.wait<true>()) return;
+            each_own([&](int i, int) { self_pair_setup(S, i); });
         }
+        if (!sync.wait<true>()) return;
         int k = 0;
+        bool passed = true;                                // a barrier since the last velocities were written
         while (true) {
-            // the solve runs in place in B (or its LDS window), which changes
-            // with every swap of the iterates
-            auto TB = pick<LW>(sB, B);
-            if (S.nca_bend > 0) {                          // curved bending: constraints split by workgroup
-                const int c0 = S.nca - S.nca_bend, nb = S.nca_bend;
-                local_projection<MIXED>(S, XN, A, c0 + (int)((int64_t)nb * w / W), c0 + (int)((int64_t)nb * (w + 1) / W));
-                if (!mw_barrier(S, gen, ok_lds)) return;
-            }
-            if constexpr (LW) {
-                spring_rhs<MIXED>(S, XN, A, sB, lo, hi);
-                spring_rhs<MIXED>(S, XN, A, B, ys0, ys1);
-            } else {
-                for (int r = 0; r < kMwRanges; ++r)
-                    if (rb[r] > ra[r]) spring_rhs<MIXED>(S, XN, A, B, ra[r], rb[r]);
-            }
-            if (converge) own([&](int i) { for (int d = 0; d < 3; ++d) Vprev[3 * i + d] = A[3 * i + d]; });
-            __syncthreads();
-            // forward solve of this workgroup's subtrees, level by level
-            for (int l = 0; l < L - 1; ++l) {
-                const int q = w * (L - 1) + l;
-                const int tl = G(S.lvl_team)[2 * l];
-                const int team = threadIdx.x / tl, lane = threadIdx.x % tl, nteams = (int)blockDim.x / tl;
-                const int i0 = G(S.mw_ptr)[(Q + 1) + q], i1 = G(S.mw_ptr)[(Q + 1) + q + 1];
-                const auto fit = (GLOBAL const v4i *)S.mw_fitems;
-                v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
-                if (i0 + team < i1) { cur = fit[2 * (i0 + team)]; cur2 = fit[2 * (i0 + team) + 1]; }
-                gather_rows(G(S.mw_rows), G(S.upd_off), G(S.mw_ptr)[q], G(S.mw_ptr)[q + 1], TB, TB, TU);
-                __syncthreads();
-                fwd_products(fit, gv2, i0 + team, i1, nteams, tl, lane, cur, cur2, TB, TY, TU);
-                __syncthreads();
-            }
-            if constexpr (LW) {                            // the root rows' update entries, for every workgroup
-                const auto bg = (GLOBAL const v2i *)S.mw_bgat;
-                const int g0 = G(S.mw_ptr)[3 * (Q + 1) + w * (L - 1)], g1 = G(S.mw_ptr)[3 * (Q + 1) + (w + 1) * (L - 1)];
-                for (int q = g0 + (int)threadIdx.x; q < g1; q += (int)blockDim.x) {
-                    const v2i e = bg[q];
-                    if (e.y < 0) { U[e.x] = sU[e.x]; U[e.x + 1] = sU[e.x + 1]; U[e.x + 2] = sU[e.x + 2]; }
-                }
-            }
-            if (!mw_barrier(S, gen, ok_lds)) return;       // every subtree's updates of the root rows are in U
-            {   // the root: its right-hand side gathered here, this workgroup's run of its product
-                const int l = L - 1;
-                const int tl = G(S.lvl_team)[2 * l];
-                const int team = threadIdx.x / tl, lane = threadIdx.x % tl, nteams = (int)blockDim.x / tl;
-                const auto fit = (GLOBAL const v4i *)S.fitems;
-                const int t0 = ria + team;
-                v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
-                if (t0 < rib) { cur = fit[2 * t0]; cur2 = fit[2 * t0 + 1]; }
-                const Shifted T{troot, 3 * rs0};
-                gather_rows(G(S.rows), G(S.upd_off), G(S.lvl_rows_ptr)[l], G(S.lvl_rows_ptr)[l + 1], B, T, U);
-                __syncthreads();
-                if (S.mw_root_lds)
-                    fwd_products(fit, LdsPairs{rootG, rgb >> 1}, t0, rib, nteams, tl, lane, cur, cur2, T, Y, U);
-                else
-                    fwd_products(fit, gv2, t0, rib, nteams, tl, lane, cur, cur2, T, Y, U);
-            }
-            if (!mw_barrier(S, gen, ok_lds)) return;       // the root's x (in Y) is complete
-            // backward solve of this workgroup's subtrees, top level first
-            for (int l = L - 2; l >= 0; --l) {
-                const int q = w * (L - 1) + l;
-                const int tl = G(S.lvl_team)[2 * l + 1];
-                const int team = threadIdx.x / tl, lane = threadIdx.x % tl, nteams = (int)blockDim.x / tl;
-                const int c0 = G(S.mw_ptr)[2 * (Q + 1) + q], c1 = G(S.mw_ptr)[2 * (Q + 1) + q + 1];
-                const int q0 = G(S.mw_ptr)[3 * (Q + 1) + q], q1 = G(S.mw_ptr)[3 * (Q + 1) + q + 1];
-                const auto bit = (GLOBAL const v4i *)S.mw_bitems;
-                v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
-                if (c0 + team < c1) { cur = bit[2 * (c0 + team)]; cur2 = bit[2 * (c0 + team) + 1]; }
-                if (q1 > q0) {
-                    bwd_gather((GLOBAL const v2i *)S.mw_bgat, q0, q1, threadIdx.x, blockDim.x, TB, Y, TU);
-                    __syncthreads();
-                }
-                bwd_products(bit, gt2, c0 + team, c1, nteams, tl, lane, cur, cur2, TY, TB, TU);
-                __syncthreads();
-            }
-            for (int i = ys0 + (int)threadIdx.x; i < ys1; i += (int)blockDim.x)   // this slice of the root: x from Y
-                for (int d = 0; d < 3; ++d) B[3 * i + d] = Y[3 * i + d];
-            __syncthreads();
-            if (S.self_on)              // a pair's leader reads its follower's new velocity, maybe another's
-                if (!mw_barrier(S, gen, ok_lds)) return;
             double dmax = 0.0;
-            if constexpr (LW) {
-                for (int i = lo + (int)threadIdx.x; i < hi; i += (int)blockDim.x) {
-                    fwd_contact_node<km>(S, i, sB, XN, Vprev, converge, dmax);
-                    for (int d = 0; d < 3; ++d) B[3 * i + d] = sB[3 * i + d];     // the new iterate, for every workgroup
+            if (bend) {                                    // curved bending: constraints split by workgroup
+                if (!passed && !sync.wait()) return;
+                const int c0 = S.nca - S.nca_bend, nb = S.nca_bend;
+                local_projection<MIXED>(S, XN, A, WP, c0 + (int)((int64_t)nb * w / W), c0 + (int)((int64_t)nb * (w + 1) / W));
+                passed = false;
+            }
+            for (int l = 0; l < L; ++l) {                  // forward solve, with the local step at the leaves
+                const MwLevel q = lv[l];
+                const int tl = 1 << q.ft, team = tid >> q.ft, lane = tid & (tl - 1), nteams = bd >> q.ft;
+                if (l > 0 || !passed) sync.arrive();
+                v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
+                if (q.fa + team < q.fb) { cur = fit[2 * (q.fa + team)]; cur2 = fit[2 * (q.fa + team) + 1]; }
+                if (l == 0) {
+                    if (n_rhs > 0) task.constants(S, XN);
+                    if (!passed && !sync.await()) return;
+                    for (int t0 = tid; t0 < (n_rhs + 63) / 64 * 64; t0 += bd) {   // whole wavefronts take part
+                        const int t = min(t0, n_rhs - 1) >> 2;
+                        double o[3];
+                        int i;
+                        if (t0 == tid) {
+                            task.rhs(S, XN, A, F, WP, slt, o);
+                            i = task.i;
+                        } else {
+                            RhsTask<MIXED> more;
+                            more.row(S, rhs_row(t), slt);
+                            more.constants(S, XN);
+                            more.rhs(S, XN, A, F, WP, slt, o);
+                            i = more.i;
+                        }
+                        if (slt == 0 && t0 < n_rhs)
+                            for (int d = 0; d < 3; ++d) {
+                                if (t < fn0) T[3 * t + d] = o[d];
+                                else BS[3 * i + d] = o[d];
+                            }
+                    }
+                } else {
+                    // the first row of each thread: descriptor and offsets ahead of the wait
+                    constexpr int kU = 6;
+                    int i3 = 0, p0 = 0, p1 = 0, o[kU];
+                    auto row = [&](int t) {
+                        const auto &g = rows[q.fr + t];
+                        i3 = g.i3; p0 = g.p0; p1 = g.p1;
+                    };
+                    auto offsets = [&](int p) {
+#pragma unroll
+                        for (int j = 0; j < kU; ++j) o[j] = p + j < p1 ? upd[p + j] : 0;
+                    };
+                    if (tid < q.fn) { row(tid); offsets(p0); }
+                    if (!sync.await()) return;
+                    for (int t = tid; t < q.fn; t += bd) { // t_i = b_i - the update entries reaching row i, in list order
+                        if (t != tid) { row(t); offsets(p0); }
+                        double a0 = BS[i3], a1 = BS[i3 + 1], a2 = BS[i3 + 2];
+                        for (int p = p0; p < p1; p += kU) {
+                            if (p != p0) offsets(p);
+                            double u[kU][3];
+#pragma unroll
+                            for (int j = 0; j < kU; ++j)
+                                if (p + j < p1) { u[j][0] = U[o[j]]; u[j][1] = U[o[j] + 1]; u[j][2] = U[o[j] + 2]; }
+#pragma unroll
+                            for (int j = 0; j < kU; ++j)
+                                if (p + j < p1) { a0 -= u[j][0]; a1 -= u[j][1]; a2 -= u[j][2]; }
+                        }
+                        T[3 * t] = a0; T[3 * t + 1] = a1; T[3 * t + 2] = a2;
+                    }
                 }
-                for (int i = ys0 + (int)threadIdx.x; i < ys1; i += (int)blockDim.x)
-                    fwd_contact_node<km>(S, i, B, XN, Vprev, converge, dmax);
-            } else {
-                own([&](int i) { fwd_contact_node<km>(S, i, B, XN, Vprev, converge, dmax); });
+                __syncthreads();
+                for (int t = q.fa + team; t < q.fb; t += nteams) {
+                    if (t != q.fa + team) { cur = fit[2 * t]; cur2 = fit[2 * t + 1]; }
+                    double a[3], b[3];
+                    const double *const Tb = T + 3 * (cur2.y - q.fr);
+                    if (in_lds) fwd_item(LdsPairs{dyn + 2 * (q.fp + cur2.z)}, Tb, cur.y, tl, lane, a, b);
+                    else fwd_item(gv2 + (cur.x >> 1), Tb, cur.y, tl, lane, a, b);
+                    if (lane == 0) {
+                        if (t >= q.root) {                 // a root's rows: the solution itself
+                            const int r = 3 * (cur2.y - q.pa) + cur.w - cur.z;
+                            for (int d = 0; d < 3; ++d) { X[cur.w + d] = a[d]; xl[r + d] = a[d]; }
+                            if (cur2.x >= 0)
+                                for (int d = 0; d < 3; ++d) { X[cur2.x + d] = b[d]; xl[r + 3 + d] = b[d]; }
+                        } else {
+                            put_row(cur.w, a[0], a[1], a[2], Y, U);
+                            put_row(cur2.x, b[0], b[1], b[2], Y, U);
+                        }
+                    }
+                }
+                if (q.pb > q.pa && !pairs) {
+                    __syncthreads();
+                    for (int t = tid; t < q.pb - q.pa; t += bd)
+                        mw_contact(N, q.own + q.ob - q.oa + t, xl + 3 * t, B, F, A, h, converge, dmax);
+                }
+                passed = false;
+            }
+            for (int l = L - 2; l >= 0; --l) {             // backward solve
+                const MwLevel q = lv[l];
+                if (!q.back) continue;                     // root supernodes only
+                const int tl = 1 << q.bt, team = tid >> q.bt, lane = tid & (tl - 1), nteams = bd >> q.bt;
+                sync.arrive();
+                v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
+                if (q.ba + team < q.bb) { cur = bit[2 * (q.ba + team)]; cur2 = bit[2 * (q.ba + team) + 1]; }
+                int xi = tid < q.bqn ? bgat[q.bq + tid].x3 : 0;
+                if (xi < 0) xi = -xi - 1;
+                for (int t = tid; t < q.bn; t += bd) {     // y: from before an earlier barrier
+                    const int i3 = rows[q.br + t].i3;
+                    for (int d = 0; d < 3; ++d) T[3 * t + d] = Y[i3 + d];
+                }
+                if (!sync.await()) return;
+                double *const R = T + 3 * q.bn;
+                for (int t = tid; t < q.bqn; t += bd) {
+                    if (t != tid) {
+                        xi = bgat[q.bq + t].x3;
+                        if (xi < 0) xi = -xi - 1;
+                    }
+                    for (int d = 0; d < 3; ++d) R[3 * t + d] = X[xi + d];
+                }
+                __syncthreads();
+                for (int t = q.ba + team; t < q.bb; t += nteams) {
+                    if (t != q.ba + team) { cur = bit[2 * t]; cur2 = bit[2 * t + 1]; }
+                    const int n1 = cur.y & 0xffff, nn = n1 + (cur.y >> 16), yb = cur.z;
+                    double a[3], b[3];
+                    const double *const Yb = T + 3 * (cur2.z - q.br), *const Ub = R + 3 * (cur2.w - q.bq);
+                    if (in_lds) bwd_item(LdsPairs{dyn + 2 * (q.bp + cur2.x)}, Yb, Ub, n1, nn, tl, lane, a, b);
+                    else bwd_item(gt2 + (cur.x >> 1), Yb, Ub, n1, nn, tl, lane, a, b);
+                    if (lane == 0) {
+                        const int r = 3 * (cur2.z - q.oa);
+                        const bool share = l > 0 || pairs;         // the leaves' solution is read by nobody else
+                        for (int d = 0; d < 3; ++d) {
+                            if (share) X[yb + d] = a[d];
+                            xl[r + d] = a[d];
+                        }
+                        if (cur2.y)
+                            for (int d = 0; d < 3; ++d) {
+                                if (share) X[yb + 3 + d] = b[d];
+                                xl[r + 3 + d] = b[d];
+                            }
+                    }
+                }
+                if (pairs) continue;
+                __syncthreads();
+                for (int t = tid; t < q.ob - q.oa; t += bd) mw_contact(N, q.own + t, xl + 3 * t, B, F, A, h, converge, dmax);
+            }
+            if (pairs) {               // a pair's leader reads its follower's solution, maybe another workgroup's
+                if (!sync.wait()) return;
+                each_own([&](int i, int) { fwd_contact_node<km, true>(S, i, X, B, F, XN, A, converge, dmax); });
             }
             ++k;
-            auto tmp = A; A = B; B = tmp;
+            const Shared tmp = A; A = B; B = tmp;
             if (converge) {
                 dmax = block_max(dmax, red);
-                if (threadIdx.x == 0) part[w] = dmax;
-                if (!mw_barrier(S, gen, ok_lds)) return;
+                if (tid == 0) part[w] = dmax;
+                if (!sync.wait()) return;
+                passed = true;
                 double mx = 0.0;
-                for (int q = 0; q < W; ++q) mx = fmax(mx, part[q]);
+                for (int q = tid; q < W; q += bd) mx = fmax(mx, part[q]);
+                mx = block_max(mx, red);
                 if (!(mx > S.fwd_tol) || k >= S.fwd_max_iters) break;
-            } else {
-                if (!mw_barrier(S, gen, ok_lds)) return;
-                if (k >= S.K) break;
+            } else if (k >= S.K) {
+                break;
             }
         }
         iters_total += k;
+        if (pairs) {
+            if (!sync.wait<true>()) return;                // followers' modes and free velocities
+        } else {                                           // a node is recorded by another thread than the one
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   //   that updated it
+            __syncthreads();
+        }
         auto xn = xrec + 3 * m;
         auto vn = vrec + 3 * m;
         auto ubrec = G(S.rec_ubar) + (int64_t)slot * 3 * m;
         int cnt[3] = {0, 0, 0};
-        own([&](int i) { fwd_record_node(S, i, slot, A, XN, xn, vn, ubrec, cnt); });
+        each_own([&](int i, int t) {
+            if (!pairs && N.mode[t] != FREE) {
+                G(S.mode)[i] = (uint8_t)N.mode[t];
+                for (int d = 0; d < 3; ++d) G(S.ubar)[3 * i + d] = N.ub[3 * t + d];
+            }
+            fwd_record_node(S, i, slot, A, XN, xn, vn, ubrec, cnt);
+        });
         const double packed = (double)cnt[0] + 1048576.0 * (double)cnt[1];
         const double tot01 = block_sum(packed, red);
         const double tot2 = block_sum((double)cnt[2], red);
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             part[W + 2 * w] = tot01;
             part[W + 2 * w + 1] = tot2;
         }
-        if (!mw_barrier(S, gen, ok_lds)) return;           // also: x_{n+1} of every node before the next prologue
-        if (w == 0 && threadIdx.x == 0) {
+        if (!sync.wait<true>()) return;                    // also: x_{n+1} of every node before the next prologue
+        if (w == 0 && tid == 0) {
             int64_t a = 0, b = 0, c = 0;
             for (int q = 0; q < W; ++q) {
-                const int64_t t01 = (int64_t)part[W + 2 * q];
+                const int64_t t01 = (int64_t)(double)part[W + 2 * q];
                 a += t01 & 1048575;
                 b += t01 >> 20;
-                c += (int64_t)part[W + 2 * q + 1];
+                c += (int64_t)(double)part[W + 2 * q + 1];
             }
             put_step_info(S, n, k, a, b, c);
         }
     }
-    if (w == 0 && threadIdx.x == 0) G(S.counters)[0] += iters_total;
+    if (w == 0 && tid == 0) G(S.counters)[0] += iters_total;
 }
 
 // ------------------------------------------------------------------ adjoint
@@ -1854,14 +2202,6 @@ __global__ __launch_bounds__(kFacBlock) void k_adj_norm(const SimDev *__restrict
 
 // wave-wide maximum (every lane), by data-parallel moves within rows of 16
 // lanes, then across rows; NaN operands are ignored
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x) {
-    const uint64_t u = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-    const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, 0xf, 0xf, false);
-    const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((uint64_t)h2 << 32) | l2));
-}
 __device__ __forceinline__ double wave_max(double v) {
     v = fmax(v, dpp_move<0x128>(v));                  // rotate a row of 16 by 8, 4, 2, 1
     v = fmax(v, dpp_move<0x124>(v));
@@ -2842,6 +3182,12 @@ __global__ void k_fill(double *p, double v, int64_t n) {
     if (i < n) p[i] = v;
 }
 
+// NaN everywhere if flag is set (a forward launch that gave up)
+__global__ void k_poison(const int64_t *__restrict__ flag, double *__restrict__ x, double *__restrict__ v, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n && *flag != 0) x[i] = v[i] = __builtin_nan("");
+}
+
 // ------------------------------------------------------------------ launchers
 
 template <bool MIXED, int FL>
@@ -2878,27 +3224,35 @@ hipError_t launch_backward(const SimDev *d_sims, int n, bool mixed, size_t lds, 
     return hipGetLastError();
 }
 
-// multi-workgroup forward of one handle (d: its descriptor), grid 8 W, lds
-// bytes of dynamic LDS; lw: each workgroup solves its one subtree in LDS
-hipError_t launch_forward_mw(const SimDev *d, int W, bool mixed, bool mesh, bool lw, size_t lds, int threads,
+// Multi-workgroup forward: blocks workgroups of the handles of d (map: handle
+// and workgroup of each block; null: one handle), lds bytes of dynamic LDS
+hipError_t launch_forward_mw(const SimDev *d, const int32_t *map, int blocks, bool mixed, bool mesh, size_t lds, int threads,
                              hipStream_t st) {
-    if (W < 2 || W > kMwMax) return hipErrorInvalidValue;
-    if (threads < 64 || threads > kBlock || threads % 64 != 0) return hipErrorInvalidValue;
-    using F = void (*)(const SimDev *);
-    static const F tab[2][2][2] = {{{k_forward_mw<false, false, false>, k_forward_mw<false, false, true>},
-                                    {k_forward_mw<false, true, false>, k_forward_mw<false, true, true>}},
-                                   {{k_forward_mw<true, false, false>, k_forward_mw<true, false, true>},
-                                    {k_forward_mw<true, true, false>, k_forward_mw<true, true, true>}}};
-    hipLaunchKernelGGL(tab[mixed][mesh][lw], dim3(kXcds * W), dim3(threads), lds, st, d);
+    if (blocks < 1) return hipErrorInvalidValue;
+    if (threads < 64 || threads > kMwThreads || threads % 64 != 0) return hipErrorInvalidValue;
+    using F = void (*)(const SimDev *, const int32_t *);
+    static const F tab[2][2] = {{k_forward_mw<false, false>, k_forward_mw<false, true>},
+                                {k_forward_mw<true, false>, k_forward_mw<true, true>}};
+    hipLaunchKernelGGL(tab[mixed][mesh], dim3(blocks), dim3(threads), lds, st, d, map);
     return hipGetLastError();
 }
 
+// Static LDS of the multi-workgroup forward; allows lds bytes of dynamic LDS.
+hipError_t mw_static_lds(size_t *bytes) {
+    *bytes = 0;
+    for (const void *f : {(const void *)k_forward_mw<false, false>, (const void *)k_forward_mw<false, true>,
+                          (const void *)k_forward_mw<true, false>, (const void *)k_forward_mw<true, true>}) {
+        hipFuncAttributes a;
+        const hipError_t e = hipFuncGetAttributes(&a, f);
+        if (e != hipSuccess) return e;
+        *bytes = std::max(*bytes, (size_t)a.sharedSizeBytes);
+    }
+    return hipSuccess;
+}
 hipError_t configure_mw_lds(size_t bytes) {
     hipError_t e = hipSuccess, r;
-    for (const void *f : {(const void *)k_forward_mw<false, false, false>, (const void *)k_forward_mw<false, false, true>,
-                          (const void *)k_forward_mw<false, true, false>, (const void *)k_forward_mw<false, true, true>,
-                          (const void *)k_forward_mw<true, false, false>, (const void *)k_forward_mw<true, false, true>,
-                          (const void *)k_forward_mw<true, true, false>, (const void *)k_forward_mw<true, true, true>})
+    for (const void *f : {(const void *)k_forward_mw<false, false>, (const void *)k_forward_mw<false, true>,
+                          (const void *)k_forward_mw<true, false>, (const void *)k_forward_mw<true, true>})
         if ((r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes)) != hipSuccess) e = r;
     return e;
 }
@@ -3006,6 +3360,11 @@ hipError_t launch_scatter_bend(const double *dw, const int32_t *centers, int n_e
 hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_poison(const int64_t *flag, double *x, double *v, int64_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_poison, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, flag, x, v, n);
     return hipGetLastError();
 }
 

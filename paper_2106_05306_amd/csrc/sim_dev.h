@@ -26,21 +26,24 @@ constexpr int kKryM = 60;            // GMRES restart length of the adjoint fall
 // Packed solve work items (shared host/device layout).
 constexpr int32_t kNoOutput = INT32_MIN;   // FwdItem.out1 of a padding row
 struct FwdItem {            // forward: rows r, r + 1 (r even) of a stacked block G_s
-    int32_t g;              // offset of G_s[r, 0] in gval (column stride ld, even)
-    int16_t ld, kmax;       // padded column stride and number of columns used
+    int32_t g;              // offset of G_s[r, 0] in gval (the pairs {G[r][k], G[r+1][k]}, k = 0 .. kmax-1)
+    int32_t kmax;           // number of columns used
     int32_t tbase;          // 3 * c0: first right-hand-side entry of the supernode
     int32_t out0, out1;     // per row: >= 0: 3 * (c0 + r) in the forward result; < 0: -(ubuf offset) - 1;
                             //   kNoOutput: padding row
-    int32_t pad[3];
+    int32_t row;            // position in rows of the supernode's first row
+    int32_t pair;           // pairs of the items before this one (level order)
+    int32_t pad;
 };
 struct BwdItem {            // backward: columns k, k + 1 (k even) of a stacked block G_s, rows k .. ld-1
-    int32_t g;              // offset of G_s[k, k] in gvalt (row-major copy, row stride st, even)
+    int32_t g;              // offset of the pairs {G[j][k], G[j][k+1]}, j = k .. ld-1, in gvalt
     int16_t n1, n2;         // rows k .. ns-1 (times y_s) and the nR rows of B_s (times x_{R_s})
     int32_t ybase;          // 3 * (c0 + k): y_s entry of row k and output entry of column k
     int32_t ubase;          // ubuf offset of the supernode: x_{R_s} is gathered there first
-    int32_t st;             // row stride of the row-major copy
+    int32_t pair;           // pairs of the items before this one (level order)
     int32_t two;            // column k + 1 exists (else padding)
-    int32_t pad[2];
+    int32_t row;            // position in rows of row k
+    int32_t gat;            // position in bgat of the supernode's first gather
 };
 struct GatherItem {         // backward: x_{R_s} entry copied into the supernode's ubuf slot
     int32_t u;              // ubuf offset (3 doubles)
@@ -81,13 +84,17 @@ constexpr int kAdjRows = 128;       // rows per item: two per lane, read with on
 constexpr int kAdjWaves = kBlockAdj / 64;
 constexpr int kAdjHelpers = 8;      // prefetching workgroups of a single-handle direct adjoint launch
 constexpr int kXcds = 8;            // workgroup i of a launch runs on XCD i mod 8
-// multi-workgroup forward of one handle: at most kMwMax workgroups (all on one
-// XCD), a root supernode of at most kMwRootMax columns, kMwRanges node ranges
-// per workgroup; its barrier block: counter, generation, failure flag (16
-// bytes), then one partial maximum and three partial counts per workgroup
-constexpr int kMwMax = 16, kMwRootMax = 512, kMwRanges = 6;
-constexpr int kMwMinNodes = 1200;   // nodes from which a handle runs it by default
-constexpr int kMwSyncDoubles = 2 + 4 * kMwMax;
+// multi-workgroup forward: at most kMwMax workgroups per handle and kMwLevels
+// levels of its elimination tree; its barrier block (64-bit words): a flag per
+// workgroup (kMwPad words apart, a cache line), the failure flag, then one partial
+// maximum and two partial counts per workgroup
+constexpr int kMwMax = 192, kMwLevels = 24, kMwPad = 8;
+constexpr int kMwSyncWords = kMwPad * (kMwMax + 1) + 3 * kMwMax;
+constexpr int kMwThreads = 512;     // threads per workgroup, at most (1024 leave 128 registers: 88 spilled)
+constexpr int kMwNodeDoubles = 13;  // LDS of a workgroup per owned node (see MwNodes)
+constexpr int kMwNoalloc = 64;      // most workgroups of the allocation-free forward (see capi: mw_admit)
+constexpr int kTeamNodes = 1200;    // large meshes: larger leaves, lanes per item sized for a share of a level
+constexpr int kTeamShare = 16;      //   (one per subtree of the root, at most this many)
 constexpr size_t kNoallocScratchBytes = size_t(16) << 20;   // device scratch of the allocation-free forward
 constexpr int kMaxDevices = 64;
 struct LuUpd {              // supernode s is updated by descendant d: rows [i0, i1) of R_d lie in s
@@ -273,25 +280,14 @@ struct SimDev {
     const int32_t *adj_pfptr;         // [3 levels + 1] into adj_pf, by phase id
     const int64_t *adj_pf;            // [2 per range] offset and length (doubles) of a block in a step factor
 
-    // multi-workgroup forward (one handle on mw workgroups of one XCD; 0: not
-    // available): workgroup w solves whole subtrees below the root supernode
-    // alone and shares the root (its columns mw_root_c0 ..)
-    int mw;
-    int mw_root_c0;
-    const int32_t *mw_ptr;            // [4 (mw (levels - 1) + 1)]: per (workgroup, level below the
-                                      //   root) ranges into mw_rows, mw_fitems, mw_bitems, mw_bgat
-    const RowItem *mw_rows;
-    const FwdItem *mw_fitems;
-    const BwdItem *mw_bitems;
-    const GatherItem *mw_bgat;
-    const int32_t *mw_nodes;          // [mw][kMwRanges][2] node ranges [a, b) of each workgroup
-    const int32_t *mw_win;            // [mw][4]: one subtree per workgroup, solved in LDS: its columns
-                                      //   [lo, hi) and update slots [ulo, uhi) (null: vectors in HBM)
-    const int32_t *mw_rootw;          // [mw][4]: the root's forward items [a, b) of each workgroup and
-                                      //   where their factor entries start in gval and how many (doubles)
-    int mw_root_lds;                  // 1: each workgroup copies its root entries into LDS once per launch
-    int mw_root_off;                  //   (after this many doubles of dynamic LDS: the subtree window)
-    uint32_t *mw_sync;                // barrier block (kMwSyncDoubles doubles)
+    // multi-workgroup forward: every level's items are split over mw workgroups
+    int mw;                           // workgroups of the launch for this handle
+    const int32_t *lvl_root;          // [n_levels] first forward item of a root supernode (the level's last ones)
+    double *bsep;                     // [3m] right-hand side of the rows above the leaves
+    uint64_t *mw_sync;                // barrier block (kMwSyncWords words)
+    uint64_t mw_epoch;                // base of this launch's barrier counts (never decreases per block)
+    int mw_lds;                       // 1: each workgroup copies its share of the factor into LDS once per launch
+    int mw_off_t, mw_off_x, mw_off_own;   // dynamic LDS (doubles): gathered vectors, results, owned nodes' state
     int64_t mw_spin;                  // wall-clock ticks (100 MHz) a barrier waits before giving up
     int mw_absent;                    // failure-handling tests only: the last workgroup returns at
                                       //   once, so every barrier wait ends at its limit

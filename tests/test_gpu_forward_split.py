@@ -1,0 +1,119 @@
+"""The forward kernel on several workgroups at the edges of its split.
+
+Every row and column of the solve is computed by the same lanes' arithmetic
+whichever workgroup takes it, so results are compared bitwise with one
+workgroup's: as many workgroups as items and more, few large shares, several
+levels, more springs a node than one group of lanes takes at once, records in
+place and in a batch, handles on two streams at once, and meshes of which one
+component has no separator (those stay on one workgroup).
+"""
+import dataclasses
+import threading
+
+import numpy as np
+import pytest
+
+import scenes
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _fan(n, steps):
+    """n x n sheet whose centre node is tied to 40 others: long spring lists on one node."""
+    sc = scenes.tiny_scene(n, steps=steps, obstacle="sphere", height=0.01, v0_scale=0.2)
+    c = n * n // 2
+    far = np.array([[min(c, j), max(c, j)] for j in range(0, n * n, max(1, n * n // 40)) if abs(j - c) > n + 2], np.int32)
+    edges = np.unique(np.concatenate([sc.edges, far]), axis=0).astype(np.int32)
+    return dataclasses.replace(sc, edges=edges, edge_stiffness=np.full(len(edges), 60.0))
+
+
+def _apart(sc, n, x=3.0):
+    """sc with an n x n sheet of its own at x."""
+    X, tris, edges = scenes.grid_mesh(n, 0.1 * (n - 1), (x, 0.02, 0.0))
+    m = sc.n_nodes
+    return dataclasses.replace(
+        sc, X=np.concatenate([sc.X, X]), tris=np.concatenate([sc.tris, tris + m]).astype(np.int32),
+        edges=np.concatenate([sc.edges, edges + m]).astype(np.int32),
+        edge_stiffness=np.concatenate([sc.edge_stiffness, np.full(len(edges), 50.0)]),
+        node_mass=np.concatenate([sc.node_mass, np.full(len(X), sc.node_mass[0])]),
+        v0=np.concatenate([sc.v0, np.zeros_like(X)]))
+
+
+def _run(sc, monkeypatch, wgs, leaf=None, **kw):
+    from paper_2106_05306_amd.sim import Sim
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", str(wgs))
+    if leaf:
+        monkeypatch.setenv("DIFFCLOTH_LEAF", str(leaf))
+    s = Sim.from_scene(sc, device=DEV, **kw)
+    traj = s.forward(sc.steps, trajectory=True)[2].clone()
+    out = traj, [s.modes(n) for n in range(sc.steps)], s.stats()["fwd_workgroups"]
+    s.close()
+    return out
+
+
+@pytest.mark.parametrize("scene,leaf,wgs", [
+    (scenes.tiny_scene(7, steps=6, obstacle="plane", height=0.002), 8, 192),     # more workgroups than rows
+    (scenes.tiny_scene(9, steps=6, obstacle="sphere", height=0.002, v0_scale=0.3), 4, 2),
+    (scenes.tiny_scene(15, steps=6, obstacle="sphere", height=0.002), 20, 31),
+    (scenes.tiny_scene(33, steps=5, obstacle="sphere", height=0.002), 128, 128),
+    (_fan(15, 5), 16, 9),
+    (_apart(scenes.tiny_scene(13, steps=5, obstacle="sphere", height=0.002), 11), 16, 12),
+], ids=["7", "9", "15", "33", "fan", "apart"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_any_split_is_bitwise(monkeypatch, scene, leaf, wgs, precision):
+    a = _run(scene, monkeypatch, 0, leaf, precision=precision)
+    b = _run(scene, monkeypatch, wgs, leaf, precision=precision)
+    assert a[2] == 1 and b[2] == wgs
+    assert torch.equal(a[0], b[0])
+    assert all(np.array_equal(x, y) for x, y in zip(a[1], b[1]))
+    assert torch.isfinite(a[0]).all()
+
+
+def test_a_component_without_separator_stays_on_one_workgroup(monkeypatch):
+    # four 4 x 4 sheets cut one by one: the first two are tied together (a
+    # separator above their leaves), the others are leaves of their own
+    sc = scenes.tiny_scene(4, steps=5, obstacle="plane", height=0.002)
+    for x in (3.0, 9.0, 12.0):
+        sc = _apart(sc, 4, x)
+    ties = np.array([[j, 16 + j] for j in range(0, 16, 3)], np.int32)
+    sc = dataclasses.replace(sc, edges=np.concatenate([sc.edges, ties]).astype(np.int32),
+                             edge_stiffness=np.concatenate([sc.edge_stiffness, np.full(len(ties), 50.0)]))
+    a = _run(sc, monkeypatch, 0, 16, precision="mixed")
+    b = _run(sc, monkeypatch, 16, 16, precision="mixed")
+    assert b[2] == 1 and torch.equal(a[0], b[0]) and torch.isfinite(a[0]).all()
+
+
+def test_batches_and_streams_equal_one_workgroup(monkeypatch):
+    from paper_2106_05306_amd.sim import Sim, batch_forward
+    scs = [scenes.tiny_scene(n, steps=st, obstacle=o, height=0.002) for n, st, o in
+           ((17, 7, "sphere"), (4, 9, "plane"), (26, 5, "sphere"), (36, 6, "plane"))]
+    ref = [_run(sc, monkeypatch, 0, precision="mixed")[0] for sc in scs]
+    monkeypatch.delenv("DIFFCLOTH_FWD_WGS")
+    sims = [Sim.from_scene(sc, device=DEV, precision="mixed") for sc in scs]
+    outs = batch_forward(sims, [sc.steps for sc in scs])
+    for r, (x, _), s in zip(ref, outs, sims):
+        assert torch.equal(x, r[-1])
+        s.close()
+
+    got = [[] for _ in scs]
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            s = Sim.from_scene(scs[i], device=DEV, precision="mixed", stream=stream)
+            for _ in range(4):
+                s.set_state(torch.tensor(scs[i].X, device=DEV), torch.tensor(scs[i].v0, device=DEV))
+                got[i].append(s.forward(scs[i].steps)[0].clone())
+            stream.synchronize()
+            s.close()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(scs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for r, xs in zip(ref, got):
+        assert len(xs) == 4 and all(torch.equal(x, r[-1]) for x in xs)
