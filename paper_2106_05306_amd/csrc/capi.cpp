@@ -164,16 +164,15 @@ int mw_workgroups_default(int64_t factor_bytes) {
     const char *e = std::getenv("DIFFCLOTH_FWD_WGS");
     const int v = e ? std::atoi(e) : -1;
     if (v >= 0) return std::min(v, kMwMax);
-    return (int)std::min<int64_t>(std::max<int64_t>(2 * factor_bytes / (64 << 10), 8), 128);
+    return (int)std::min<int64_t>(std::max<int64_t>(2 * factor_bytes / (64 << 10), 32), 128);
 }
 
 // Nodes from which a handle's own launches (and batches with such a handle) take
 // the multi-workgroup forward unless DIFFCLOTH_FWD_WGS says otherwise.  Below,
 // one workgroup needs less time than the barriers; us per PD iteration on one
-// workgroup / split: 16 x 16 17.8 / 24.0, 28 x 28 36.9 / 41.1, 34 x 34 59.0 /
-// 61.5, 36 x 36 (where the leaves are larger and the levels fewer) 69.8 / 42.2,
-// 48 x 48 205 / 68.
-constexpr int kMwMinNodes = kTeamNodes;
+// workgroup / split: 14 x 14 17.2 / 16.9, 16 x 16 18.3 / 17.6, 18 x 18 19.4 /
+// 17.9, 24 x 24 25.7 / 19.3, 34 x 34 60.6 / 46.1, 48 x 48 200 / 53.
+constexpr int kMwMinNodes = 324;
 
 // Whether the workgroups of a multi-workgroup forward may copy their shares of
 // the factor into LDS (DIFFCLOTH_MW_LDS=0: read from L2).

@@ -63,6 +63,16 @@ __device__ __forceinline__ double team_sum(double v, int tl) {
     return v;
 }
 
+// Both of a team's sums, with one branch per half.
+__device__ __forceinline__ void team_sum(double &a, double &b, int tl) {
+    if (tl > 32) { a += __shfl_xor(a, 32, 64); b += __shfl_xor(b, 32, 64); }
+    if (tl > 16) { a += __shfl_xor(a, 16, 64); b += __shfl_xor(b, 16, 64); }
+    if (tl > 8) { a += dpp_move<0x108>(a); b += dpp_move<0x108>(b); }
+    if (tl > 4) { a += dpp_move<0x104>(a); b += dpp_move<0x104>(b); }
+    if (tl > 2) { a += dpp_move<0x102>(a); b += dpp_move<0x102>(b); }
+    if (tl > 1) { a += dpp_move<0x101>(a); b += dpp_move<0x101>(b); }
+}
+
 // Block-wide max of a non-negative value; every thread gets the result.
 __device__ inline double block_max(double v, double *red) {
 #pragma unroll
@@ -547,10 +557,11 @@ __device__ __forceinline__ void attach_target(const SimDev &S, auto X, double t,
 
 // Closed-form Signorini-Coulomb update of one node with isotropic response
 // v = ub + f/m; gap-corrected normal velocity.  Decisions in float64.
-__device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const double *n, double phi, double mu,
-                                            double h, double mass, double *v, double *f) {
+// gap: phi / h.
+__device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const double *n, double gap, double mu, double mass,
+                                                     double *v, double *f) {
     const double un = dot3(n[0], ub[0], n[1], ub[1], n[2], ub[2]);
-    const double a = un + phi / h;
+    const double a = un + gap;
     if (a > 0.0) {
         v[0] = ub[0]; v[1] = ub[1]; v[2] = ub[2];
         f[0] = f[1] = f[2] = 0.0;
@@ -558,7 +569,7 @@ __device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const dou
     }
     const double ut0 = fma(-un, n[0], ub[0]), ut1 = fma(-un, n[1], ub[1]), ut2 = fma(-un, n[2], ub[2]);
     const double tau = sqrt(dot3(ut0, ut0, ut1, ut1, ut2, ut2));
-    const double vn = -phi / h;
+    const double vn = -gap;
     uint8_t md;
     if (tau <= mu * (-a)) {
         v[0] = vn * n[0]; v[1] = vn * n[1]; v[2] = vn * n[2];
@@ -578,6 +589,37 @@ __device__ __forceinline__ uint8_t signorini_coulomb(const double *ub, const dou
 
 // ------------------------------------------------------------------ forward
 
+// w_c p_c of constraint c with vector q.
+template <bool MIXED>
+__device__ __forceinline__ void bend_projection(const SimDev &S, int c, double q0, double q1, double q2, auto wp) {
+    double p0, p1, p2;
+    if (MIXED) {
+        const float f0 = (float)q0, f1 = (float)q1, f2 = (float)q2;
+        const float nq = sqrtf(dot3(f1, f1, f0, f0, f2, f2));
+        const float rho = G(S.c_rhof)[c], w = G(S.c_wf)[c];
+        float r0, r1, r2;
+        if (nq < 1e-12f * rho) {
+            r0 = rho * (float)G(S.c_restdir)[3 * c]; r1 = rho * (float)G(S.c_restdir)[3 * c + 1];
+            r2 = rho * (float)G(S.c_restdir)[3 * c + 2];
+        } else {
+            const float sc = rho / nq;
+            r0 = sc * f0; r1 = sc * f1; r2 = sc * f2;
+        }
+        p0 = (double)(w * r0); p1 = (double)(w * r1); p2 = (double)(w * r2);
+    } else {
+        const double nq = sqrt(dot3(q1, q1, q0, q0, q2, q2));
+        const double rho = G(S.c_rho)[c], w = G(S.c_w)[c];
+        if (nq < 1e-12 * rho) {
+            p0 = w * rho * G(S.c_restdir)[3 * c]; p1 = w * rho * G(S.c_restdir)[3 * c + 1];
+            p2 = w * rho * G(S.c_restdir)[3 * c + 2];
+        } else {
+            const double sc = w * rho / nq;
+            p0 = sc * q0; p1 = sc * q1; p2 = sc * q2;
+        }
+    }
+    wp[3 * c] = p0; wp[3 * c + 1] = p1; wp[3 * c + 2] = p2;
+}
+
 // w_c p_c for active constraints [c0, c1) at x^k = x_n + h v^k (local step,
 // constraint-centred; used for curved bending stencils).
 template <bool MIXED>
@@ -592,32 +634,7 @@ __device__ __forceinline__ void local_projection(const SimDev &S, auto XN, auto 
             q1 = fma(a, fma(h, vk[3 * j + 1], XN[3 * j + 1]), q1);
             q2 = fma(a, fma(h, vk[3 * j + 2], XN[3 * j + 2]), q2);
         }
-        double p0, p1, p2;
-        if (MIXED) {
-            const float f0 = (float)q0, f1 = (float)q1, f2 = (float)q2;
-            const float nq = sqrtf(dot3(f1, f1, f0, f0, f2, f2));
-            const float rho = G(S.c_rhof)[c], w = G(S.c_wf)[c];
-            float r0, r1, r2;
-            if (nq < 1e-12f * rho) {
-                r0 = rho * (float)G(S.c_restdir)[3 * c]; r1 = rho * (float)G(S.c_restdir)[3 * c + 1];
-                r2 = rho * (float)G(S.c_restdir)[3 * c + 2];
-            } else {
-                const float sc = rho / nq;
-                r0 = sc * f0; r1 = sc * f1; r2 = sc * f2;
-            }
-            p0 = (double)(w * r0); p1 = (double)(w * r1); p2 = (double)(w * r2);
-        } else {
-            const double nq = sqrt(dot3(q1, q1, q0, q0, q2, q2));
-            const double rho = G(S.c_rho)[c], w = G(S.c_w)[c];
-            if (nq < 1e-12 * rho) {
-                p0 = w * rho * G(S.c_restdir)[3 * c]; p1 = w * rho * G(S.c_restdir)[3 * c + 1];
-                p2 = w * rho * G(S.c_restdir)[3 * c + 2];
-            } else {
-                const double sc = w * rho / nq;
-                p0 = sc * q0; p1 = sc * q1; p2 = sc * q2;
-            }
-        }
-        wp[3 * c] = p0; wp[3 * c + 1] = p1; wp[3 * c + 2] = p2;
+        bend_projection<MIXED>(S, c, q0, q1, q2, wp);
     }
 }
 
@@ -934,7 +951,7 @@ __device__ __forceinline__ void self_pair_update(const SimDev &S, int L, int F, 
     double nrm[3], phi, r, u[3], fn[3];
     self_frame(S, L, F, XN, nrm, phi, r);
     const double mred = mL * mF / (mL + mF);
-    const uint8_t md = signorini_coulomb(ur, nrm, phi, S.self_mu, S.h, mred, u, fn);
+    const uint8_t md = signorini_coulomb(ur, nrm, phi / S.h, S.self_mu, mred, u, fn);
     G(S.mode)[L] = md;
     G(S.mode)[F] = md;
     for (int d = 0; d < 3; ++d) {
@@ -982,7 +999,7 @@ __device__ __forceinline__ void fwd_contact_node(const SimDev &S, int i, auto X,
         } else {
             contact_frame<false>(S, G(S.cobst)[i], XN + 3 * i, nrm, phi);
         }
-        G(S.mode)[i] = signorini_coulomb(ub, nrm, phi, S.obst[G(S.cobst)[i]].mu, h, mi, vv, ff);
+        G(S.mode)[i] = signorini_coulomb(ub, nrm, phi / h, S.obst[G(S.cobst)[i]].mu, mi, vv, ff);
         for (int d = 0; d < 3; ++d) {
             // the iterate is (v, f): a node held by the contact update
             // keeps its velocity while its impulse may still change
@@ -1226,6 +1243,72 @@ struct MwSync {
     }
 };
 
+// A lane's part of one item's product (a pair of rows or columns of a stacked
+// block) for one component of the vectors: sums of g w over k = lane, lane + tl,
+// ... < n in that order, g = Gb[k] the pair of factor entries, w = vec[index(k)]
+// the vector entry (LDS) it multiplies.  The product is a chain of loads, not of
+// arithmetic: one lane summing all three components over batches of four waited
+// 0.25 us a batch for LDS and 0.6 us for L2.  So a lane takes one component (three
+// times the lanes work, on a third of the operations) and loads a batch while it
+// sums the one before.
+template <int B>
+struct ItemBatch {
+    v2d g[B];
+    double w[B];
+
+    __device__ __forceinline__ void pairs(auto Gb, int n, int tl, int k) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) g[j] = Gb[min(k + j * tl, n - 1)];
+    }
+    __device__ __forceinline__ void vector(const double *vec, auto &&index, int n, int tl, int k) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) w[j] = vec[index(min(k + j * tl, n - 1))];
+    }
+    __device__ __forceinline__ void add(double &a, double &b) const {
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            a = fma(g[j].x, w[j], a);
+            b = fma(g[j].y, w[j], b);
+        }
+    }
+    // the last batch: entries past n count as zero
+    __device__ __forceinline__ void add_last(int n, int tl, int k, double &a, double &b) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) w[j] = k + j * tl < n ? w[j] : 0.0;
+        add(a, b);
+    }
+};
+
+// AHEAD: first holds the lane's first batch of pairs already.
+template <bool AHEAD, int B>
+__device__ __forceinline__ void item_product(auto Gb, const double *vec, auto &&index, int n, int tl, int lane,
+                                             ItemBatch<B> &first, double &ra, double &rb) {
+    double a = 0.0, b = 0.0;
+    ItemBatch<B> second;
+    const int step = B * tl;
+    if (lane < n) {
+        if constexpr (!AHEAD) first.pairs(Gb, n, tl, lane);
+        first.vector(vec, index, n, tl, lane);
+#pragma clang loop unroll(disable)
+        for (int k = lane;; k += step) {
+            if (k + step >= n) { first.add_last(n, tl, k, a, b); break; }
+            second.pairs(Gb, n, tl, k + step);
+            second.vector(vec, index, n, tl, k + step);
+            first.add(a, b);
+            first = second;
+        }
+    }
+    team_sum(a, b, tl);
+    ra = a;
+    rb = b;
+}
+
+// Component d of a forward-solve result (see put_row).
+__device__ __forceinline__ void put_entry(int out, int d, double a, auto Y, auto U) {
+    if (out >= 0) Y[out + d] = a;
+    else if (out != kNoOutput) U[-out - 1 + d] = a;
+}
+
 // Right-hand side of a row (see spring_rhs) by a group of 4 lanes, two of eight
 // springs per lane, summed in the springs' order.  What does not change during a
 // step (the row, its springs, positions) is loaded ahead, the rest in rhs().
@@ -1234,12 +1317,26 @@ struct RhsTask {
     int i = 0, p0 = 0, p1 = 0;
     v4i sp[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     double rho[2] = {0, 0}, xi[3], xj[2][3], b[3];
+    int q0 = 0, q1 = 0, bc[2];                              // bending: constraints and coefficients, likewise
+    double ba[2];
 
     __device__ __forceinline__ void row(const SimDev &S, int r, int slot) {
         i = r;
         p0 = G(S.sinc_ptr)[i];
         p1 = G(S.sinc_ptr)[i + 1];
         springs(S, p0, slot);
+        if (S.nca_bend > 0) {
+            q0 = G(S.binc_ptr)[i];
+            q1 = G(S.binc_ptr)[i + 1];
+        }
+    }
+    __device__ __forceinline__ void bending(const SimDev &S, int p, int slot) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int q = min(p + slot + 4 * e, q1 - 1);
+            bc[e] = G(S.binc_con)[q];
+            ba[e] = G(S.binc_coef)[q];
+        }
     }
     __device__ __forceinline__ void springs(const SimDev &S, int p, int slot) {
 #pragma unroll
@@ -1257,7 +1354,8 @@ struct RhsTask {
         for (int e = 0; e < 2; ++e)
             for (int d = 0; d < 3; ++d) xj[e][d] = XN[3 * sp[e].x + d];
     }
-    __device__ __forceinline__ void constants(const SimDev &S, auto XN) {
+    __device__ __forceinline__ void constants(const SimDev &S, auto XN, int slot) {
+        if (q1 > q0) bending(S, q0, slot);
         positions(XN);
         for (int d = 0; d < 3; ++d) { xi[d] = XN[3 * i + d]; b[d] = G(S.b0)[3 * i + d]; }
     }
@@ -1269,6 +1367,12 @@ struct RhsTask {
             for (int d = 0; d < 3; ++d) vj[e][d] = V[3 * sp[e].x + d];
         const double vi[3] = {V[3 * i], V[3 * i + 1], V[3 * i + 2]};
         const double fi[3] = {f[3 * i], f[3 * i + 1], f[3 * i + 2]};
+        double wj[2][3];
+        if (q1 > q0) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                for (int d = 0; d < 3; ++d) wj[e][d] = wp[3 * bc[e] + d];
+        }
         const double y0 = fma(h, vi[0], xi[0]), y1 = fma(h, vi[1], xi[1]), y2 = fma(h, vi[2], xi[2]);
         double r0 = 0, r1 = 0, r2 = 0;
         for (int pb = p0; pb < p1; pb += 8) {
@@ -1294,49 +1398,123 @@ struct RhsTask {
             }
         }
         if (p1 - p0 > 8) springs(S, p0, slot);             // ready for the next iteration
-        if (S.nca_bend > 0)
-            for (int p = G(S.binc_ptr)[i]; p < G(S.binc_ptr)[i + 1]; ++p) {
-                const int c = G(S.binc_con)[p];
-                const double a = G(S.binc_coef)[p];
-                r0 = fma(a, wp[3 * c], r0); r1 = fma(a, wp[3 * c + 1], r1); r2 = fma(a, wp[3 * c + 2], r2);
+        for (int pb = q0; pb < q1; pb += 8) {
+            if (pb > q0) {
+                bending(S, pb, slot);
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    for (int d = 0; d < 3; ++d) wj[e][d] = wp[3 * bc[e] + d];
             }
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double a = __shfl(ba[e], j, 4);
+                    const double s0 = __shfl(wj[e][0], j, 4), s1 = __shfl(wj[e][1], j, 4), s2 = __shfl(wj[e][2], j, 4);
+                    if (pb + 4 * e + j < q1) { r0 = fma(a, s0, r0); r1 = fma(a, s1, r1); r2 = fma(a, s2, r2); }
+                }
+        }
         out[0] = fma(h, r0, b[0]) + fi[0];
         out[1] = fma(h, r1, b[1]) + fi[1];
         out[2] = fma(h, r2, b[2]) + fi[2];
     }
 };
 
-// Contact state of the owned nodes during a step, in LDS: impulse, frame at x_n
-// and gap, mass, friction, free velocity, mode.
+// Projections of the bending constraints [c0, c1) (local_projection), a
+// constraint per group of 4 lanes: two of eight stencil nodes per lane, summed in
+// the stencil's order.  What does not depend on the velocities is loaded before
+// ready() (the wait for them).
+template <bool MIXED>
+__device__ __forceinline__ bool bend_projections(const SimDev &S, auto XN, auto V, auto wp, int c0, int c1, auto &&ready) {
+    const double h = S.h;
+    const int n = (c1 - c0) * 4, slot = threadIdx.x & 3;
+    int p0 = 0, p1 = 0, node[2];
+    double a[2], x[2][3];
+    auto stencil = [&](int p) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int q = min(p + slot + 4 * e, p1 - 1);
+            node[e] = G(S.c_node)[q];
+            a[e] = G(S.c_coef)[q];
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            for (int d = 0; d < 3; ++d) x[e][d] = XN[3 * node[e] + d];
+    };
+    auto load = [&](int t) {
+        const int c = c0 + (min(t, n - 1) >> 2);
+        p0 = G(S.c_ptr)[c];
+        p1 = G(S.c_ptr)[c + 1];
+        if (p1 > p0) stencil(p0);
+        return c;
+    };
+    int c = 0;
+    if (n > 0) c = load((int)threadIdx.x);
+    if (!ready()) return false;
+    for (int t = threadIdx.x; t < (n + 63) / 64 * 64; t += (int)blockDim.x) {   // whole wavefronts take part
+        if (t != (int)threadIdx.x) c = load(t);
+        double q0 = 0, q1 = 0, q2 = 0;
+        for (int pb = p0; pb < p1; pb += 8) {
+            if (pb > p0) stencil(pb);
+            double y[2][3];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                for (int d = 0; d < 3; ++d) y[e][d] = V[3 * node[e] + d];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                for (int d = 0; d < 3; ++d) y[e][d] = fma(h, y[e][d], x[e][d]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double aj = __shfl(a[e], j, 4);
+                    const double s0 = __shfl(y[e][0], j, 4), s1 = __shfl(y[e][1], j, 4), s2 = __shfl(y[e][2], j, 4);
+                    if (pb + 4 * e + j < p1) { q0 = fma(aj, s0, q0); q1 = fma(aj, s1, q1); q2 = fma(aj, s2, q2); }
+                }
+        }
+        if (slot == 0 && t < n) bend_projection<MIXED>(S, c, q0, q1, q2, wp);
+    }
+    return true;
+}
+
+// Contact state of the owned nodes during a step, in LDS: impulse f and f / m,
+// frame at x_n and gap / h, mass, friction, free velocity, mode.  The divisions
+// that do not need the solution are done outside the chain from one barrier to
+// the next.
 struct MwNodes {
-    double *f, *nrm, *phi, *mass, *mu, *ub;
+    double *f, *nrm, *gap, *mass, *mu, *ub, *fm;
     int *node, *mode;
     __device__ MwNodes(double *p, int n)
-        : f(p), nrm(p + 3 * n), phi(p + 6 * n), mass(p + 7 * n), mu(p + 8 * n), ub(p + 9 * n), node((int *)(p + 12 * n)),
-          mode((int *)(p + 12 * n) + n) {}
+        : f(p), nrm(p + 3 * n), gap(p + 6 * n), mass(p + 7 * n), mu(p + 8 * n), ub(p + 9 * n), fm(p + 12 * n),
+          node((int *)(p + 15 * n)), mode((int *)(p + 15 * n) + n) {}
 };
 
 // Contact update of owned node t (fwd_contact_node for a node outside any pair,
 // its state in LDS): solution xs, new velocity to B.
-__device__ __forceinline__ void mw_contact(const MwNodes &N, int t, const double *xs, auto B, auto f, auto Vprev, double h,
-                                           bool converge, double &dmax) {
+__device__ __forceinline__ void mw_contact(const MwNodes &N, int t, const double *xs, auto B, auto f, auto Vprev, bool converge,
+                                           double &dmax) {
     const int i = N.node[t];
     double vv[3] = {xs[0], xs[1], xs[2]};
-    if (N.mode[t] != FREE) {
+    const bool contact = N.mode[t] != FREE;
+    if (contact) {
         const double mi = N.mass[t];
-        const double fo[3] = {N.f[3 * t], N.f[3 * t + 1], N.f[3 * t + 2]};
-        const double ub[3] = {vv[0] - fo[0] / mi, vv[1] - fo[1] / mi, vv[2] - fo[2] / mi};
+        const double ub[3] = {vv[0] - N.fm[3 * t], vv[1] - N.fm[3 * t + 1], vv[2] - N.fm[3 * t + 2]};
         const double nrm[3] = {N.nrm[3 * t], N.nrm[3 * t + 1], N.nrm[3 * t + 2]};
         double ff[3];
-        N.mode[t] = signorini_coulomb(ub, nrm, N.phi[t], N.mu[t], h, mi, vv, ff);
+        N.mode[t] = signorini_coulomb(ub, nrm, N.gap[t], N.mu[t], mi, vv, ff);
         for (int d = 0; d < 3; ++d) {
-            if (converge) dmax = fmax(dmax, fabs(ff[d] - fo[d]) / mi);
-            N.f[3 * t + d] = ff[d];
             f[3 * i + d] = ff[d];
-            N.ub[3 * t + d] = ub[d];
+            B[3 * i + d] = vv[d];
         }
+        for (int d = 0; d < 3; ++d) {
+            if (converge) dmax = fmax(dmax, fabs(ff[d] - N.f[3 * t + d]) / mi);
+            N.f[3 * t + d] = ff[d];
+            N.ub[3 * t + d] = ub[d];
+            N.fm[3 * t + d] = ff[d] / mi;
+        }
+    } else {
+        for (int d = 0; d < 3; ++d) B[3 * i + d] = vv[d];
     }
-    for (int d = 0; d < 3; ++d) B[3 * i + d] = vv[d];
     if (converge)
         for (int d = 0; d < 3; ++d) dmax = fmax(dmax, fabs(vv[d] - Vprev[3 * i + d]));
 }
@@ -1355,7 +1533,7 @@ __device__ __forceinline__ void mw_contact(const MwNodes &N, int t, const double
 // workgroups (descriptors, offsets, positions, earlier results) between its
 // arrival at a barrier and the wait.  Per PD iteration, against one XCD's 16
 // workgroups with a subtree each (40 x 40, 72 x 72) or one workgroup (100 x 100
-// without allocations): 43 -> 31 us, 174 -> 79 us, 1.2 ms -> 150 us.
+// without allocations): 43 -> 29 us, 174 -> 61 us, 1.2 ms -> 121 us.
 // Every node, row and item is computed with the arithmetic of k_forward (same
 // items, teams and summation orders), so results are bitwise those of the
 // one-workgroup kernel for any number of workgroups.
@@ -1513,12 +1691,15 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
                 } else {
                     contact_frame<false>(S, o, XN + 3 * i, nrm, phi);
                 }
+                const double mi = G(S.mass)[i];
                 for (int d = 0; d < 3; ++d) {
+                    const double fo = G(S.f)[3 * i + d];
                     N.nrm[3 * t + d] = nrm[d];
-                    N.f[3 * t + d] = G(S.f)[3 * i + d];
+                    N.f[3 * t + d] = fo;
+                    N.fm[3 * t + d] = fo / mi;
                 }
-                N.phi[t] = phi;
-                N.mass[t] = G(S.mass)[i];
+                N.gap[t] = phi / h;
+                N.mass[t] = mi;
                 N.mu[t] = S.obst[o].mu;
             }
         });
@@ -1539,19 +1720,24 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
         while (true) {
             double dmax = 0.0;
             if (bend) {                                    // curved bending: constraints split by workgroup
-                if (!passed && !sync.wait()) return;
                 const int c0 = S.nca - S.nca_bend, nb = S.nca_bend;
-                local_projection<MIXED>(S, XN, A, WP, c0 + (int)((int64_t)nb * w / W), c0 + (int)((int64_t)nb * (w + 1) / W));
+                if (!passed) sync.arrive();
+                if (!bend_projections<MIXED>(S, XN, A, WP, c0 + (int)((int64_t)nb * w / W), c0 + (int)((int64_t)nb * (w + 1) / W),
+                                             [&] { return passed || sync.await(); }))
+                    return;
                 passed = false;
             }
             for (int l = 0; l < L; ++l) {                  // forward solve, with the local step at the leaves
                 const MwLevel q = lv[l];
                 const int tl = 1 << q.ft, team = tid >> q.ft, lane = tid & (tl - 1), nteams = bd >> q.ft;
-                if (l > 0 || !passed) sync.arrive();
+                const int nt = 3 * (q.fb - q.fa);          // one task per item and component
                 v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
-                if (q.fa + team < q.fb) { cur = fit[2 * (q.fa + team)]; cur2 = fit[2 * (q.fa + team) + 1]; }
+                if (team < nt) { cur = fit[2 * (q.fa + team / 3)]; cur2 = fit[2 * (q.fa + team / 3) + 1]; }
+                if (l > 0 || !passed) sync.arrive();
+                ItemBatch<kSolveBatch> first;                 // a first batch of pairs from L2, ahead of the wait
+                if (!in_lds && team < nt && lane < cur.y) first.pairs(gv2 + (cur.x >> 1), cur.y, tl, lane);
                 if (l == 0) {
-                    if (n_rhs > 0) task.constants(S, XN);
+                    if (n_rhs > 0) task.constants(S, XN, slt);
                     if (!passed && !sync.await()) return;
                     for (int t0 = tid; t0 < (n_rhs + 63) / 64 * 64; t0 += bd) {   // whole wavefronts take part
                         const int t = min(t0, n_rhs - 1) >> 2;
@@ -1563,19 +1749,19 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
                         } else {
                             RhsTask<MIXED> more;
                             more.row(S, rhs_row(t), slt);
-                            more.constants(S, XN);
+                            more.constants(S, XN, slt);
                             more.rhs(S, XN, A, F, WP, slt, o);
                             i = more.i;
                         }
                         if (slt == 0 && t0 < n_rhs)
                             for (int d = 0; d < 3; ++d) {
-                                if (t < fn0) T[3 * t + d] = o[d];
+                                if (t < fn0) T[d * fn0 + t] = o[d];
                                 else BS[3 * i + d] = o[d];
                             }
                     }
                 } else {
                     // the first row of each thread: descriptor and offsets ahead of the wait
-                    constexpr int kU = 6;
+                    constexpr int kU = 8;
                     int i3 = 0, p0 = 0, p1 = 0, o[kU];
                     auto row = [&](int t) {
                         const auto &g = rows[q.fr + t];
@@ -1595,37 +1781,47 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
                             double u[kU][3];
 #pragma unroll
                             for (int j = 0; j < kU; ++j)
-                                if (p + j < p1) { u[j][0] = U[o[j]]; u[j][1] = U[o[j] + 1]; u[j][2] = U[o[j] + 2]; }
+                                for (int d = 0; d < 3; ++d) u[j][d] = p + j < p1 ? (double)U[o[j] + d] : 0.0;
 #pragma unroll
                             for (int j = 0; j < kU; ++j)
                                 if (p + j < p1) { a0 -= u[j][0]; a1 -= u[j][1]; a2 -= u[j][2]; }
                         }
-                        T[3 * t] = a0; T[3 * t + 1] = a1; T[3 * t + 2] = a2;
+                        T[t] = a0; T[q.fn + t] = a1; T[2 * q.fn + t] = a2;
                     }
                 }
                 __syncthreads();
-                for (int t = q.fa + team; t < q.fb; t += nteams) {
-                    if (t != q.fa + team) { cur = fit[2 * t]; cur2 = fit[2 * t + 1]; }
-                    double a[3], b[3];
-                    const double *const Tb = T + 3 * (cur2.y - q.fr);
-                    if (in_lds) fwd_item(LdsPairs{dyn + 2 * (q.fp + cur2.z)}, Tb, cur.y, tl, lane, a, b);
-                    else fwd_item(gv2 + (cur.x >> 1), Tb, cur.y, tl, lane, a, b);
+                for (int t = team; t < nt; t += nteams) {
+                    const int d = t % 3;
+                    if (t != team) {
+                        const int i = q.fa + t / 3;
+                        cur = fit[2 * i]; cur2 = fit[2 * i + 1];
+                    }
+                    double a, b;
+                    const double *const Tb = T + d * q.fn + cur2.y - q.fr;
+                    auto entry = [](int k) { return k; };
+                    if (in_lds) {
+                        ItemBatch<kSolveBatch> own;
+                        item_product<false>(LdsPairs{dyn + 2 * (q.fp + cur2.z)}, Tb, entry, cur.y, tl, lane, own, a, b);
+                    } else {
+                        if (t != team && lane < cur.y) first.pairs(gv2 + (cur.x >> 1), cur.y, tl, lane);
+                        item_product<true>(gv2 + (cur.x >> 1), Tb, entry, cur.y, tl, lane, first, a, b);
+                    }
                     if (lane == 0) {
-                        if (t >= q.root) {                 // a root's rows: the solution itself
+                        if (q.fa + t / 3 >= q.root) {      // a root's rows: the solution itself
                             const int r = 3 * (cur2.y - q.pa) + cur.w - cur.z;
-                            for (int d = 0; d < 3; ++d) { X[cur.w + d] = a[d]; xl[r + d] = a[d]; }
-                            if (cur2.x >= 0)
-                                for (int d = 0; d < 3; ++d) { X[cur2.x + d] = b[d]; xl[r + 3 + d] = b[d]; }
+                            X[cur.w + d] = a;
+                            xl[r + d] = a;
+                            if (cur2.x >= 0) { X[cur2.x + d] = b; xl[r + 3 + d] = b; }
                         } else {
-                            put_row(cur.w, a[0], a[1], a[2], Y, U);
-                            put_row(cur2.x, b[0], b[1], b[2], Y, U);
+                            put_entry(cur.w, d, a, Y, U);
+                            put_entry(cur2.x, d, b, Y, U);
                         }
                     }
                 }
                 if (q.pb > q.pa && !pairs) {
                     __syncthreads();
                     for (int t = tid; t < q.pb - q.pa; t += bd)
-                        mw_contact(N, q.own + q.ob - q.oa + t, xl + 3 * t, B, F, A, h, converge, dmax);
+                        mw_contact(N, q.own + q.ob - q.oa + t, xl + 3 * t, B, F, A, converge, dmax);
                 }
                 passed = false;
             }
@@ -1633,49 +1829,62 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
                 const MwLevel q = lv[l];
                 if (!q.back) continue;                     // root supernodes only
                 const int tl = 1 << q.bt, team = tid >> q.bt, lane = tid & (tl - 1), nteams = bd >> q.bt;
-                sync.arrive();
+                const int nt = 3 * (q.bb - q.ba);
                 v4i cur = {0, 0, 0, 0}, cur2 = {0, 0, 0, 0};
-                if (q.ba + team < q.bb) { cur = bit[2 * (q.ba + team)]; cur2 = bit[2 * (q.ba + team) + 1]; }
+                if (team < nt) { cur = bit[2 * (q.ba + team / 3)]; cur2 = bit[2 * (q.ba + team / 3) + 1]; }
+                sync.arrive();
+                ItemBatch<kSolveBatch> first;
+                {
+                    const int nn = (cur.y & 0xffff) + (cur.y >> 16);
+                    if (!in_lds && team < nt && lane < nn) first.pairs(gt2 + (cur.x >> 1), nn, tl, lane);
+                }
                 int xi = tid < q.bqn ? bgat[q.bq + tid].x3 : 0;
                 if (xi < 0) xi = -xi - 1;
+                const int nrow = q.bn + q.bqn;             // y of the rows, then minus x of the gathers
                 for (int t = tid; t < q.bn; t += bd) {     // y: from before an earlier barrier
                     const int i3 = rows[q.br + t].i3;
-                    for (int d = 0; d < 3; ++d) T[3 * t + d] = Y[i3 + d];
+                    for (int d = 0; d < 3; ++d) T[d * nrow + t] = Y[i3 + d];
                 }
                 if (!sync.await()) return;
-                double *const R = T + 3 * q.bn;
                 for (int t = tid; t < q.bqn; t += bd) {
                     if (t != tid) {
                         xi = bgat[q.bq + t].x3;
                         if (xi < 0) xi = -xi - 1;
                     }
-                    for (int d = 0; d < 3; ++d) R[3 * t + d] = X[xi + d];
+                    for (int d = 0; d < 3; ++d) T[d * nrow + q.bn + t] = -X[xi + d];
                 }
                 __syncthreads();
-                for (int t = q.ba + team; t < q.bb; t += nteams) {
-                    if (t != q.ba + team) { cur = bit[2 * t]; cur2 = bit[2 * t + 1]; }
+                for (int t = team; t < nt; t += nteams) {
+                    const int d = t % 3;
+                    if (t != team) {
+                        const int i = q.ba + t / 3;
+                        cur = bit[2 * i]; cur2 = bit[2 * i + 1];
+                    }
                     const int n1 = cur.y & 0xffff, nn = n1 + (cur.y >> 16), yb = cur.z;
-                    double a[3], b[3];
-                    const double *const Yb = T + 3 * (cur2.z - q.br), *const Ub = R + 3 * (cur2.w - q.bq);
-                    if (in_lds) bwd_item(LdsPairs{dyn + 2 * (q.bp + cur2.x)}, Yb, Ub, n1, nn, tl, lane, a, b);
-                    else bwd_item(gt2 + (cur.x >> 1), Yb, Ub, n1, nn, tl, lane, a, b);
+                    double a, b;
+                    const int oy = cur2.z - q.br, ou = q.bn + cur2.w - q.bq - n1;
+                    auto entry = [=](int k) { return k + (k < n1 ? oy : ou); };
+                    if (in_lds) {
+                        ItemBatch<kSolveBatch> own;
+                        item_product<false>(LdsPairs{dyn + 2 * (q.bp + cur2.x)}, T + d * nrow, entry, nn, tl, lane, own, a, b);
+                    } else {
+                        if (t != team && lane < nn) first.pairs(gt2 + (cur.x >> 1), nn, tl, lane);
+                        item_product<true>(gt2 + (cur.x >> 1), T + d * nrow, entry, nn, tl, lane, first, a, b);
+                    }
                     if (lane == 0) {
                         const int r = 3 * (cur2.z - q.oa);
                         const bool share = l > 0 || pairs;         // the leaves' solution is read by nobody else
-                        for (int d = 0; d < 3; ++d) {
-                            if (share) X[yb + d] = a[d];
-                            xl[r + d] = a[d];
+                        if (share) X[yb + d] = a;
+                        xl[r + d] = a;
+                        if (cur2.y) {
+                            if (share) X[yb + 3 + d] = b;
+                            xl[r + 3 + d] = b;
                         }
-                        if (cur2.y)
-                            for (int d = 0; d < 3; ++d) {
-                                if (share) X[yb + 3 + d] = b[d];
-                                xl[r + 3 + d] = b[d];
-                            }
                     }
                 }
                 if (pairs) continue;
                 __syncthreads();
-                for (int t = tid; t < q.ob - q.oa; t += bd) mw_contact(N, q.own + t, xl + 3 * t, B, F, A, h, converge, dmax);
+                for (int t = tid; t < q.ob - q.oa; t += bd) mw_contact(N, q.own + t, xl + 3 * t, B, F, A, converge, dmax);
             }
             if (pairs) {               // a pair's leader reads its follower's solution, maybe another workgroup's
                 if (!sync.wait()) return;

@@ -12,7 +12,7 @@ namespace dc {
 constexpr int kMaxObstacles = 8;
 constexpr int kBlock = 1024;         // threads per workgroup of the forward kernel (16 wavefronts)
 constexpr int kBlockAdj = 1024;      // threads per workgroup of the adjoint kernel
-constexpr int kSolveBatch = 4;      // 16-byte loads per lane in flight in the triangular solves of P
+constexpr int kSolveBatch = 4;      // 16-byte loads per lane and batch in the triangular solves of P (two batches in flight)
 // Variant bits of the persistent kernels: what the host placed in LDS and, for
 // the adjoint kernel, the adjoint solver (the bit value 4 means kLdsPositions
 // in the forward kernel and kAdjDirect in the adjoint kernel).
@@ -91,7 +91,7 @@ constexpr int kXcds = 8;            // workgroup i of a launch runs on XCD i mod
 constexpr int kMwMax = 192, kMwLevels = 24, kMwPad = 8;
 constexpr int kMwSyncWords = kMwPad * (kMwMax + 1) + 3 * kMwMax;
 constexpr int kMwThreads = 512;     // threads per workgroup, at most (1024 leave 128 registers: 88 spilled)
-constexpr int kMwNodeDoubles = 13;  // LDS of a workgroup per owned node (see MwNodes)
+constexpr int kMwNodeDoubles = 16;  // LDS of a workgroup per owned node (see MwNodes)
 constexpr int kMwNoalloc = 64;      // most workgroups of the allocation-free forward (see capi: mw_admit)
 constexpr int kTeamNodes = 1200;    // large meshes: larger leaves, lanes per item sized for a share of a level
 constexpr int kTeamShare = 16;      //   (one per subtree of the root, at most this many)

@@ -3,7 +3,8 @@
 Every row and column of the solve is computed by the same lanes' arithmetic
 whichever workgroup takes it, so results are compared bitwise with one
 workgroup's: as many workgroups as items and more, few large shares, several
-levels, more springs a node than one group of lanes takes at once, records in
+levels, more springs or bending stencils a node than one group of lanes takes at
+once, records in
 place and in a batch, handles on two streams at once, and meshes of which one
 component has no separator (those stay on one workgroup).
 """
@@ -28,6 +29,25 @@ def _fan(n, steps):
     far = np.array([[min(c, j), max(c, j)] for j in range(0, n * n, max(1, n * n // 40)) if abs(j - c) > n + 2], np.int32)
     edges = np.unique(np.concatenate([sc.edges, far]), axis=0).astype(np.int32)
     return dataclasses.replace(sc, edges=edges, edge_stiffness=np.full(len(edges), 60.0))
+
+
+def _cone(around, rings, steps):
+    """Cone with `around` triangles at its apex: curved bending with long stencils and long lists on the apex."""
+    sc = scenes.tiny_scene(3, steps=steps, obstacle="sphere", height=0.0, v0_scale=0.0)
+    ang = 2 * np.pi * np.arange(around) / around
+    X = [np.array([[0.0, 0.30, 0.0]])] + [
+        np.stack([0.06 * r * np.cos(ang), np.full(around, 0.30 - 0.03 * r), 0.06 * r * np.sin(ang)], 1) for r in range(1, rings + 1)]
+    X = np.concatenate(X) + np.random.default_rng(3).normal(0.0, 1e-3, (1 + around * rings, 3))
+    at = lambda r, j: 0 if r == 0 else 1 + (r - 1) * around + j % around
+    tris = [(0, at(1, j), at(1, j + 1)) for j in range(around)]
+    for r in range(1, rings):
+        for j in range(around):
+            tris += [(at(r, j), at(r + 1, j), at(r + 1, j + 1)), (at(r, j), at(r + 1, j + 1), at(r, j + 1))]
+    tris = np.array(tris, np.int32)
+    edges = np.unique(np.sort(np.concatenate([tris[:, [0, 1]], tris[:, [1, 2]], tris[:, [0, 2]]]), axis=1), axis=0).astype(np.int32)
+    m = len(X)
+    return dataclasses.replace(sc, X=X, tris=tris, edges=edges, edge_stiffness=np.full(len(edges), 60.0),
+                               node_mass=np.full(m, sc.node_mass[0]), v0=np.random.default_rng(4).normal(0.0, 0.2, (m, 3)))
 
 
 def _apart(sc, n, x=3.0):
@@ -61,7 +81,9 @@ def _run(sc, monkeypatch, wgs, leaf=None, **kw):
     (scenes.tiny_scene(33, steps=5, obstacle="sphere", height=0.002), 128, 128),
     (_fan(15, 5), 16, 9),
     (_apart(scenes.tiny_scene(13, steps=5, obstacle="sphere", height=0.002), 11), 16, 12),
-], ids=["7", "9", "15", "33", "fan", "apart"])
+    (_cone(14, 6, 5), 8, 6),
+    (scenes.c3_skirt(0, n_around=16, n_rings=14, steps=4), 16, 11),
+], ids=["7", "9", "15", "33", "fan", "apart", "cone", "skirt"])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_any_split_is_bitwise(monkeypatch, scene, leaf, wgs, precision):
     a = _run(scene, monkeypatch, 0, leaf, precision=precision)
