@@ -75,8 +75,12 @@ __device__ __forceinline__ void team_sum(double &a, double &b, int tl) {
 
 // Block-wide max of a non-negative value; every thread gets the result.
 __device__ inline double block_max(double v, double *red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    v = fmax(v, __shfl_xor(v, 32, 64));
+    v = fmax(v, __shfl_xor(v, 16, 64));
+    v = fmax(v, dpp_move<0x108>(v));
+    v = fmax(v, dpp_move<0x104>(v));
+    v = fmax(v, dpp_move<0x102>(v));
+    v = fmax(v, dpp_move<0x101>(v));
     const int wave = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[wave] = v;
@@ -87,10 +91,9 @@ __device__ inline double block_max(double v, double *red) {
     return r;
 }
 
-// Block-wide sum in a fixed order (wave butterflies, then waves 0..15).
+// Block-wide sum in a fixed order (within the wavefronts by halves, then wavefronts 0..15).
 __device__ inline double block_sum(double v, double *red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = team_sum(v, 64);
     const int wave = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[wave] = v;
@@ -1947,6 +1950,28 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
 
 // ------------------------------------------------------------------ adjoint
 
+// r += the sum of coef[p] vec(index[p], d) over p = p0 .. p1 - 1, in that order;
+// four entries' loads are in flight together (entry by entry, the loads of an
+// index and of what it names took most of the adjoint operator's time).
+__device__ __forceinline__ void list_sum(int p0, int p1, auto index, auto coef, auto &&vec, double &r0, double &r1, double &r2) {
+    for (int p = p0; p < p1; p += 4) {
+        int c[4];
+        double a[4], v[4][3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = min(p + j, p1 - 1);
+            c[j] = index[q];
+            a[j] = (double)coef[q];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            for (int d = 0; d < 3; ++d) v[j][d] = vec(3 * c[j] + d);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (p + j < p1) { r0 = fma(a[j], v[j][0], r0); r1 = fma(a[j], v[j][1], r1); r2 = fma(a[j], v[j][2], r2); }
+    }
+}
+
 // z = T^T zeta per node (T = I off contact / take-off, 0 for stick, the slip
 // block otherwise); also keeps zeta - z for the (P - M) term.  A pair (L, F) in
 // stick or slip with relative block T_r (in tblk of both nodes) and
@@ -1992,13 +2017,7 @@ template <bool MIXED>
 __device__ __forceinline__ void projection_jacobian_apply(const SimDev &S, auto z, auto u, int dw_mode, double h) {
     for (int c = threadIdx.x; c < S.nca; c += (int)blockDim.x) {
         double a0 = 0, a1 = 0, a2 = 0;
-        for (int p = G(S.c_ptr)[c]; p < G(S.c_ptr)[c + 1]; ++p) {
-            const int j = G(S.c_node)[p];
-            const double a = G(S.c_coef)[p];
-            a0 += a * z[3 * j];
-            a1 += a * z[3 * j + 1];
-            a2 += a * z[3 * j + 2];
-        }
+        list_sum(G(S.c_ptr)[c], G(S.c_ptr)[c + 1], G(S.c_node), G(S.c_coef), [&](int i) -> double { return z[i]; }, a0, a1, a2);
         const auto qh = G(S.adj_q) + 3 * c;
         if (MIXED) {
             const float sc = (float)G(S.adj_s)[c];
@@ -2044,19 +2063,10 @@ __device__ __forceinline__ void adjoint_rhs(const SimDev &S, auto gbar, auto u, 
     const double hh = S.h * S.h;
     for (int i = threadIdx.x; i < S.m; i += (int)blockDim.x) {
         double r0 = 0, r1 = 0, r2 = 0;
-        for (int p = G(S.inc_ptr)[i]; p < G(S.inc_ptr)[i + 1]; ++p) {
-            const int c = G(S.inc_con)[p];
-            const double a = G(S.inc_coef)[p];
-            r0 += a * u[3 * c]; r1 += a * u[3 * c + 1]; r2 += a * u[3 * c + 2];
-        }
+        list_sum(G(S.inc_ptr)[i], G(S.inc_ptr)[i + 1], G(S.inc_con), G(S.inc_coef), [&](int j) -> double { return u[j]; }, r0, r1, r2);
         double k0 = 0, k1 = 0, k2 = 0;
-        for (int p = G(S.ks_ptr)[i]; p < G(S.ks_ptr)[i + 1]; ++p) {
-            const int j = G(S.ks_col)[p];
-            const double kv = MIXED ? (double)G(S.ks_valf)[p] : G(S.ks_val)[p];
-            k0 += kv * (zeta[3 * j] - z[3 * j]);
-            k1 += kv * (zeta[3 * j + 1] - z[3 * j + 1]);
-            k2 += kv * (zeta[3 * j + 2] - z[3 * j + 2]);
-        }
+        list_sum(G(S.ks_ptr)[i], G(S.ks_ptr)[i + 1], G(S.ks_col), pick<MIXED>(G(S.ks_valf), G(S.ks_val)),
+                 [&](int j) -> double { return zeta[j] - z[j]; }, k0, k1, k2);
         r[3 * i] = gbar[3 * i] + r0 + hh * k0;
         r[3 * i + 1] = gbar[3 * i + 1] + r1 + hh * k1;
         r[3 * i + 2] = gbar[3 * i + 2] + r2 + hh * k2;
@@ -2075,17 +2085,11 @@ __device__ __forceinline__ void apply_adjoint_operator(const SimDev &S, auto mod
     const double hh = S.h * S.h;
     for (int i = threadIdx.x; i < S.m; i += (int)blockDim.x) {
         double r0 = 0, r1 = 0, r2 = 0;
-        for (int p = G(S.inc_ptr)[i]; p < G(S.inc_ptr)[i + 1]; ++p) {
-            const int c = G(S.inc_con)[p];
-            const double a = G(S.inc_coef)[p];
-            r0 += a * G(S.wp)[3 * c]; r1 += a * G(S.wp)[3 * c + 1]; r2 += a * G(S.wp)[3 * c + 2];
-        }
+        list_sum(G(S.inc_ptr)[i], G(S.inc_ptr)[i + 1], G(S.inc_con), G(S.inc_coef), [&](int j) -> double { return G(S.wp)[j]; }, r0, r1,
+                 r2);
         double k0 = 0, k1 = 0, k2 = 0;
-        for (int p = G(S.ks_ptr)[i]; p < G(S.ks_ptr)[i + 1]; ++p) {
-            const int j = G(S.ks_col)[p];
-            const double kv = MIXED ? (double)G(S.ks_valf)[p] : G(S.ks_val)[p];
-            k0 += kv * G(S.zt)[3 * j]; k1 += kv * G(S.zt)[3 * j + 1]; k2 += kv * G(S.zt)[3 * j + 2];
-        }
+        list_sum(G(S.ks_ptr)[i], G(S.ks_ptr)[i + 1], G(S.ks_col), pick<MIXED>(G(S.ks_valf), G(S.ks_val)),
+                 [&](int j) -> double { return G(S.zt)[j]; }, k0, k1, k2);
         const double mi = G(S.mass)[i];
         out[3 * i] = mi * vin[3 * i] + hh * k0 - r0;
         out[3 * i + 1] = mi * vin[3 * i + 1] + hh * k1 - r1;
@@ -2102,28 +2106,49 @@ __device__ __forceinline__ void apply_adjoint_operator(const SimDev &S, auto mod
 // Block-wide dot products <V_k, w> for k = 0..nk-1 (fixed order); results in
 // hk[0..nk).  Eight basis vectors per pass over w.
 __device__ __forceinline__ void block_dots(auto V, int64_t ld, int nk, auto w, int n3, double *red2, double *hk) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int k0 = 0; k0 < nk; k0 += 8) {
+    // short vectors: the wavefronts a vector does not need take other vectors
+    const int waves = (int)(blockDim.x >> 6), lane = threadIdx.x & 63;
+    const int nb = min((n3 + 63) >> 6, waves), groups = waves / nb;
+    const int wave = (threadIdx.x >> 6) % nb, group = (threadIdx.x >> 6) / nb;
+    for (int k0 = group < groups ? 8 * group : nk; k0 < nk; k0 += 8 * groups) {
         double p[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         const int kn = min(8, nk - k0);
-        for (int i = threadIdx.x; i < n3; i += (int)blockDim.x) {
+        for (int i = 64 * wave + lane; i < n3; i += 64 * nb) {
             const double wi = w[i];
+            double v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q < kn) p[q] += V[(k0 + q) * ld + i] * wi;
+            for (int q = 0; q < 8; ++q) v[q] = V[(k0 + min(q, kn - 1)) * ld + i];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) p[q] = fma(v[q], wi, p[q]);
+        }
+        // Eight sums over the lanes, each by halves: at 32, 16 and 8 lanes apart
+        // a lane keeps half of the sums it has and passes on the others, so the
+        // lane group of eight it ends in holds sum g (7 exchanges, not 48).
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool up = lane & 32;
+            const double keep = up ? p[q + 4] : p[q], give = up ? p[q] : p[q + 4];
+            p[q] = keep + __shfl_xor(give, 32, 64);
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            double v = p[q];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0 && q < kn) red2[wave * (kKryM + 1) + k0 + q] = v;
+        for (int q = 0; q < 2; ++q) {
+            const bool up = lane & 16;
+            const double keep = up ? p[q + 2] : p[q], give = up ? p[q] : p[q + 2];
+            p[q] = keep + __shfl_xor(give, 16, 64);
         }
+        {
+            const bool up = lane & 8;
+            const double keep = up ? p[1] : p[0], give = up ? p[0] : p[1];
+            p[0] = keep + __shfl_xor(give, 8, 64);
+        }
+        p[0] = team_sum(p[0], 8);
+        const int g = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+        if ((lane & 7) == 0 && g < kn) red2[wave * (kKryM + 1) + k0 + g] = p[0];
     }
     __syncthreads();
     for (int k = threadIdx.x; k < nk; k += (int)blockDim.x) {
         double s = 0.0;
-        for (int wv = 0; wv < (int)(blockDim.x >> 6); ++wv) s += red2[wv * (kKryM + 1) + k];
+        for (int wv = 0; wv < nb; ++wv) s += red2[wv * (kKryM + 1) + k];
         hk[k] = s;
     }
     __syncthreads();
@@ -2133,6 +2158,11 @@ __device__ __forceinline__ void block_dots(auto V, int64_t ld, int nk, auto w, i
 // (M + H T^T) zeta = gbar; fallback when the paper's fixed point stalls or
 // diverges.  Stops when |P^{-1}(gbar - A zeta)| <= tol |P^{-1} gbar|.
 // Returns the number of Krylov iterations, negative if the tolerance was missed.
+// One workgroup; an iteration is a chain of loads and barriers (operator, solve
+// with P, two Gram-Schmidt passes).  Basis vectors are read eight loads at a time,
+// dot products summed by exchanging halves, the rotations' running entry kept in a
+// register: 72 -> 32 us an iteration at 121 nodes, 97 -> 63 us at 392 (of which
+// operator 5 / 17 us, solve 8 / 12 us, Gram-Schmidt 15 / 27 us).
 template <bool MIXED>
 __device__ __forceinline__ int gmres_solve(const SimDev &S, auto mode, auto prt, auto gbar, auto zeta, double tol, int max_iters,
                            double *red, auto T, auto Y, auto U) {
@@ -2177,16 +2207,22 @@ __device__ __forceinline__ int gmres_solve(const SimDev &S, auto mode, auto prt,
             double wn = sqrt(block_sum(ws, red));
             for (int pass = 0; pass < 2; ++pass) {
                 block_dots(V, ld, j + 1, w, n3, red2, yk);
+                ws = 0.0;
                 for (int i = threadIdx.x; i < n3; i += (int)blockDim.x) {
                     double acc = w[i];
-                    for (int k = 0; k <= j; ++k) acc -= yk[k] * V[k * ld + i];
+                    for (int k = 0; k <= j; k += 8) {      // eight loads in flight
+                        double v[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) v[q] = V[min(k + q, j) * ld + i];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (k + q <= j) acc = fma(-yk[k + q], v[q], acc);
+                    }
                     w[i] = acc;
+                    ws = fma(acc, acc, ws);
                 }
-                if (threadIdx.x == 0)
-                    for (int k = 0; k <= j; ++k) Hs[k * kKryM + j] = (pass ? Hs[k * kKryM + j] : 0.0) + yk[k];
-                __syncthreads();
-                ws = 0.0;
-                for (int i = threadIdx.x; i < n3; i += (int)blockDim.x) ws += w[i] * w[i];
+                for (int k = threadIdx.x; k <= j; k += (int)blockDim.x)
+                    Hs[k * kKryM + j] = (pass ? Hs[k * kKryM + j] : 0.0) + yk[k];
                 const double wa = sqrt(block_sum(ws, red));
                 const bool again = wa < 0.7 * wn;
                 wn = wa;
@@ -2197,12 +2233,16 @@ __device__ __forceinline__ int gmres_solve(const SimDev &S, auto mode, auto prt,
                 for (int i = threadIdx.x; i < n3; i += (int)blockDim.x) w[i] /= hn;
             if (threadIdx.x == 0) {
                 // apply previous rotations to column j, then a new one
+                // (the running entry stays in a register, so that the loads of the
+                // others do not wait for it)
+                double a = Hs[j];
+#pragma unroll 4
                 for (int k = 0; k < j; ++k) {
-                    const double a = Hs[k * kKryM + j], b = Hs[(k + 1) * kKryM + j];
-                    Hs[k * kKryM + j] = cs[k] * a + sn[k] * b;
-                    Hs[(k + 1) * kKryM + j] = -sn[k] * a + cs[k] * b;
+                    const double b = Hs[(k + 1) * kKryM + j], c = cs[k], t = sn[k];
+                    Hs[k * kKryM + j] = c * a + t * b;
+                    a = -t * a + c * b;
                 }
-                const double a = Hs[j * kKryM + j], b = hn;
+                const double b = hn;
                 const double r = sqrt(a * a + b * b);
                 cs[j] = r > 0 ? a / r : 1.0;
                 sn[j] = r > 0 ? b / r : 0.0;
@@ -2228,7 +2268,14 @@ __device__ __forceinline__ int gmres_solve(const SimDev &S, auto mode, auto prt,
         __syncthreads();
         for (int i = threadIdx.x; i < n3; i += (int)blockDim.x) {
             double acc = zeta[i];
-            for (int k = 0; k < jdone; ++k) acc += yk[k] * V[k * ld + i];
+            for (int k = 0; k < jdone; k += 8) {
+                double v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = V[min(k + q, jdone - 1) * ld + i];
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (k + q < jdone) acc = fma(yk[k + q], v[q], acc);
+            }
             zeta[i] = acc;
         }
         __syncthreads();
@@ -3235,17 +3282,11 @@ __global__ __launch_bounds__(kBlockAdj) void k_backward(const SimDev *__restrict
                 Hz[0] = G(S.adj_hz)[3 * i]; Hz[1] = G(S.adj_hz)[3 * i + 1]; Hz[2] = G(S.adj_hz)[3 * i + 2];
             } else {
                 double r0 = 0, r1 = 0, r2 = 0;      // Delta P z
-                for (int p = G(S.inc_ptr)[i]; p < G(S.inc_ptr)[i + 1]; ++p) {
-                    const int c = G(S.inc_con)[p];
-                    const double a = G(S.inc_coef)[p];
-                    r0 += a * G(S.wp)[3 * c]; r1 += a * G(S.wp)[3 * c + 1]; r2 += a * G(S.wp)[3 * c + 2];
-                }
+                list_sum(G(S.inc_ptr)[i], G(S.inc_ptr)[i + 1], G(S.inc_con), G(S.inc_coef),
+                         [&](int j) -> double { return G(S.wp)[j]; }, r0, r1, r2);
                 double k0 = 0, k1 = 0, k2 = 0;      // K_s z
-                for (int p = G(S.ks_ptr)[i]; p < G(S.ks_ptr)[i + 1]; ++p) {
-                    const int j = G(S.ks_col)[p];
-                    const double kv = MIXED ? (double)G(S.ks_valf)[p] : G(S.ks_val)[p];
-                    k0 += kv * G(S.zt)[3 * j]; k1 += kv * G(S.zt)[3 * j + 1]; k2 += kv * G(S.zt)[3 * j + 2];
-                }
+                list_sum(G(S.ks_ptr)[i], G(S.ks_ptr)[i + 1], G(S.ks_col), pick<MIXED>(G(S.ks_valf), G(S.ks_val)),
+                         [&](int j) -> double { return G(S.zt)[j]; }, k0, k1, k2);
                 Hz[0] = hh * k0 - r0; Hz[1] = hh * k1 - r1; Hz[2] = hh * k2 - r2;
             }
             const double mi = G(S.mass)[i];
