@@ -684,16 +684,10 @@ def bench_sphere_self(args):
     st = sim.stats()
     pairs = [sim.self_pairs(n) for n in range(T)]
     pair_steps = int(sum(np.count_nonzero(p >= 0) for p in pairs) // 2)
-    # the forward alone, self-collision off, on the same kernel variant
-    old = os.environ.get("DIFFCLOTH_MW_LDS")
-    os.environ["DIFFCLOTH_MW_LDS"] = "0"                 # the variant self-collision runs
+    # the forward alone, self-collision off, on the same kernel
     sc_off = sphere_self_scene()
     sc_off.self_thickness = 0.0
     off = Sim.from_scene(sc_off, **kw)
-    if old is None:
-        del os.environ["DIFFCLOTH_MW_LDS"]
-    else:
-        os.environ["DIFFCLOTH_MW_LDS"] = old
     off.forward(T)
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)

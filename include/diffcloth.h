@@ -249,8 +249,8 @@ typedef struct {
     double  fwd_ms, bwd_ms;         /* device time of the last sim_forward / sim_backward on the
                                        handle's stream (HIP events; 0 before the first call)    */
     int32_t fwd_workgroups;         /* workgroups of a single-handle forward launch (> 1: the
-                                       multi-workgroup kernel, subtrees of the elimination tree per
-                                       workgroup)                                               */
+                                       multi-workgroup kernel, every level of the solves split
+                                       over them)                                               */
     int32_t pad;
 } sim_stats_t;
 
@@ -375,7 +375,7 @@ int sim_stats(const sim_t *sim, sim_stats_t *out);
 int sim_step_stats(const sim_t *sim, int32_t n, int32_t *out);
 
 /* Batched forward / backward of independent handles in one persistent launch
- * (one workgroup per handle; handles may differ in size and step count).  All
+ * (one or more workgroups per handle; handles may differ in size and step count).  All
  * handles must share the first handle's stream and precision, and for the
  * backward call its adj_solver (else SIM_EINVAL).  Per-handle arguments are
  * arrays of length n (entries may be NULL where the single call allows it). */

@@ -417,7 +417,7 @@ class Sim:
 
 
 def batch_forward(sims: Sequence[Sim], n_steps: Sequence[int]):
-    """One persistent launch over independent handles (one workgroup each)."""
+    """One persistent launch over independent handles (one or more workgroups each)."""
     n = len(sims)
     hs = (ctypes.c_void_p * n)(*[s.h for s in sims])
     st = (ctypes.c_int32 * n)(*n_steps)
