@@ -2335,6 +2335,7 @@ struct NoallocLayout {
     size_t desc, ctr, red, x, v, vk, vk1, rhs, b0, f, ubar, cfr, wp, ubuf, rx, rv, rub, mode, cobst, rmode, robst;
     size_t ybuf, cand, partner, rpartner, shead, snext;   // node-node contact (self-collision on)
     size_t total;
+    size_t sync, mw_total;                                // and, after the rest, the multi-workgroup forward's barrier block
 };
 
 NoallocLayout noalloc_layout(const sim *s) {
@@ -2376,6 +2377,8 @@ NoallocLayout noalloc_layout(const sim *s) {
         L.snext = take(m * sizeof(int32_t));
     }
     L.total = o;
+    L.sync = take(kMwSyncWords * sizeof(uint64_t));
+    L.mw_total = o;
     return L;
 }
 
@@ -2428,9 +2431,14 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
     d.step_end = n_steps;
     d.rec_step0 = 0;
     d.fwd_epoch = 0;
+    // (a mesh whose rest fits the scratch but not the barrier block: one workgroup)
     size_t mw_lds = 0;
-    const bool mw = s->mw_wgs >= 2 && mw_plan(s, std::min(s->mw_wgs, kMwNoalloc), d, mw_lds);
-    d.mw_epoch = uint64_t(1) << 40;              // (its barrier block is cleared below)
+    const bool mw = s->mw_wgs >= 2 && L.mw_total <= kNoallocScratchBytes &&
+                    mw_plan(s, std::min(s->mw_wgs, kMwNoalloc), d, mw_lds);
+    // a barrier block of its own, cleared below: the handle's block holds the
+    // counts of the handle's own launches
+    if (mw) d.mw_sync = (uint64_t *)(b + L.sync);
+    d.mw_epoch = uint64_t(1) << 40;
     SimDev *dd = (SimDev *)(b + L.desc);
     // everything below is enqueued on the handle's stream; nothing allocates,
     // synchronises or clears memory with a memset (the call may be captured)

@@ -1,0 +1,62 @@
+"""The allocation-free forward beside a handle's other passes.
+
+Its barriers and work memory are the library's own array, so it may come before
+any recorded pass of the handle, and a captured one may be replayed while the
+handle runs: every pass is compared bitwise with one workgroup's.
+"""
+import numpy as np
+import pytest
+
+import scenes
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _sim(sc, **kw):
+    from paper_2106_05306_amd.sim import Sim
+    return Sim.from_scene(sc, device=DEV, precision="mixed", **kw)
+
+
+def _one_workgroup(sc, monkeypatch):
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "0")
+    s = _sim(sc)
+    assert s.stats()["fwd_workgroups"] == 1
+    xT, vT, _ = s.forward(sc.steps)
+    out = xT.clone(), vT.clone()
+    s.close()
+    monkeypatch.delenv("DIFFCLOTH_FWD_WGS")
+    return out
+
+
+def _noalloc(s, steps):
+    xT, vT = (torch.full((s.m, 3), float("nan"), dtype=torch.float64, device=DEV) for _ in range(2))
+    s.forward_noalloc(steps, xT, vT)
+    return xT, vT
+
+
+@pytest.mark.parametrize("n", [24, 48])
+@pytest.mark.parametrize("then", ["forward", "batch_forward", "batch_advance"])
+def test_first_recorded_pass_after_noalloc(monkeypatch, n, then):
+    from paper_2106_05306_amd.sim import batch_advance, batch_forward
+    sc = scenes.c2_sphere_drop(0, n=n, steps=6)
+    rx, rv = _one_workgroup(sc, monkeypatch)
+    s = _sim(sc)                                     # fresh: the allocation-free pass comes first
+    assert s.stats()["fwd_workgroups"] > 1
+    ax, av = _noalloc(s, sc.steps)
+    if then == "forward":
+        x, v, _ = s.forward(sc.steps)
+    elif then == "batch_forward":
+        (x, v), = batch_forward([s], [sc.steps])
+    else:
+        s.job_forward(sc.steps)
+        while batch_advance([s], [4])[0] > 0:
+            pass
+        x, v = s.state(sc.steps)
+    bx, bv = _noalloc(s, sc.steps)
+    torch.cuda.synchronize()
+    for a, b in ((ax, av), (x, v), (bx, bv)):
+        assert torch.equal(a, rx) and torch.equal(b, rv)
+    s.close()
