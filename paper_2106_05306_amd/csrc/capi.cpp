@@ -2435,9 +2435,15 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
     size_t mw_lds = 0;
     const bool mw = s->mw_wgs >= 2 && L.mw_total <= kNoallocScratchBytes &&
                     mw_plan(s, std::min(s->mw_wgs, kMwNoalloc), d, mw_lds);
-    // a barrier block of its own, cleared below: the handle's block holds the
-    // counts of the handle's own launches
-    if (mw) d.mw_sync = (uint64_t *)(b + L.sync);
+    if (mw) {
+        // a barrier block of its own, cleared below: the handle's block holds the
+        // counts of the handle's own launches
+        d.mw_sync = (uint64_t *)(b + L.sync);
+        // the vectors that only this kernel shares lie over slot 0 of the ring's
+        // records, which is written before the first barrier and not read
+        d.ysol = d.rec_x;
+        d.bsep = d.rec_v;
+    }
     d.mw_epoch = uint64_t(1) << 40;
     SimDev *dd = (SimDev *)(b + L.desc);
     // everything below is enqueued on the handle's stream; nothing allocates,

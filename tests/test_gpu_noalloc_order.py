@@ -60,3 +60,38 @@ def test_first_recorded_pass_after_noalloc(monkeypatch, n, then):
     for a, b in ((ax, av), (x, v), (bx, bv)):
         assert torch.equal(a, rx) and torch.equal(b, rv)
     s.close()
+
+
+def test_captured_pass_replayed_while_the_handle_runs(monkeypatch):
+    # replays on a stream of their own, several at a time beside forward and
+    # adjoint passes of the same handle, and alone between them
+    sc = scenes.c2_sphere_drop(0, n=32, steps=6)
+    rx, rv = _one_workgroup(sc, monkeypatch)
+    st, side = torch.cuda.Stream(), torch.cuda.Stream()
+    seed = torch.tensor(np.random.default_rng(2).normal(size=(sc.n_nodes, 3)), device=DEV)
+    with torch.cuda.stream(st):
+        s = _sim(sc, stream=st)
+        assert s.stats()["fwd_workgroups"] > 1
+        s.forward(sc.steps)
+        ref = s.backward(seed)["dx0"].clone()
+        xT, vT = (torch.zeros((s.m, 3), dtype=torch.float64, device=DEV) for _ in range(2))
+        st.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        s.forward_noalloc(sc.steps, xT, vT)
+    for _ in range(4):
+        with torch.cuda.stream(side):
+            xT.zero_()
+            vT.zero_()
+            for _ in range(3):
+                g.replay()
+        with torch.cuda.stream(st):
+            for _ in range(3):
+                x, v, _ = s.forward(sc.steps)
+                d = s.backward(seed)["dx0"]
+                st.synchronize()
+                assert torch.equal(x, rx) and torch.equal(v, rv) and torch.equal(d, ref)
+        side.synchronize()
+        assert torch.equal(xT, rx) and torch.equal(vT, rv)
+    torch.cuda.synchronize()
+    s.close()
