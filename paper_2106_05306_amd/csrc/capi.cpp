@@ -1322,6 +1322,12 @@ void ensure_records(sim *s, int cap) {
     s->hd.rec_ubar = (double *)dev_alloc(s, cap * v3 * sizeof(double));
     s->hd.rec_mode = (uint8_t *)dev_alloc(s, (size_t)cap * s->hd.m);
     s->hd.rec_obst = (int8_t *)dev_alloc(s, (size_t)cap * s->hd.m);
+    // a forward launch that gave up leaves records unwritten, and the overlapped
+    // factorisation queued behind it reads them: no node in contact there (an
+    // obstacle's number from unset memory would index out of the descriptor)
+    if (hipMemsetAsync(s->hd.rec_mode, 0, (size_t)cap * s->hd.m, s->stream) != hipSuccess ||
+        hipMemsetAsync(s->hd.rec_obst, 0xff, (size_t)cap * s->hd.m, s->stream) != hipSuccess)
+        throw std::runtime_error("hip");
     if (s->hd.self_on) s->hd.rec_partner = (int32_t *)dev_alloc(s, (size_t)cap * s->hd.m * sizeof(int32_t));
     s->hd.rec_cap = cap;
 }

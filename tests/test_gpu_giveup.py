@@ -1,0 +1,57 @@
+"""Forward passes whose multi-workgroup launch gives up at a barrier.
+
+The host forces it with the barrier's own limit (0 ticks: every wait that is
+not over at once ends) or by withholding a workgroup; every kernel returns
+normally, and no GPU work is broken on purpose.
+"""
+import numpy as np
+import pytest
+
+import scenes
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+KEYS = ("dx0", "dv0", "dw_edge", "dmu")
+
+
+def _sim(sc, **kw):
+    from paper_2106_05306_amd.sim import Sim
+    kw.setdefault("precision", "mixed")
+    return Sim.from_scene(sc, device=DEV, **kw)
+
+
+def _seed(sc):
+    return torch.tensor(np.random.default_rng(2).normal(size=(sc.n_nodes, 3)), device=DEV)
+
+
+def _one_workgroup(sc, monkeypatch, **kw):
+    with monkeypatch.context() as mp:
+        mp.setenv("DIFFCLOTH_FWD_WGS", "0")
+        s = _sim(sc, **kw)
+        assert s.stats()["fwd_workgroups"] == 1
+        traj = s.forward(sc.steps, trajectory=True)[2].clone()
+        g = s.backward(_seed(sc))
+        out = traj, {k: g[k].clone() for k in KEYS}
+        s.close()
+    return out
+
+
+def test_overlapped_factorisation_after_a_launch_that_gave_up(monkeypatch):
+    # the records of the first, failed attempt are new memory, and its steps
+    # are factored behind it all the same
+    sc = scenes.discretized_sphere_drop(0, n=24, steps=24, level=1)
+    kw = dict(adj_solver="direct", adj_tol=1e-10, adj_max_iters=10)
+    traj, g = _one_workgroup(sc, monkeypatch, **kw)
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "16")
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "0")
+    junk = [torch.full((64 << 20,), 0x55, dtype=torch.uint8, device=DEV) for _ in range(4)]
+    s = _sim(sc, **kw)
+    del junk                                         # what the records are allocated from
+    t = s.forward(sc.steps, trajectory=True)[2]
+    assert torch.equal(t, traj)
+    out = s.backward(_seed(sc))
+    for k in KEYS:
+        assert torch.equal(out[k], g[k]), k
+    s.close()
