@@ -1568,8 +1568,9 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
     MwSync sync{G(S.mw_sync), S.mw_epoch, S.mw_epoch, W, w, (uint64_t)S.mw_spin, &ok_lds, G(S.counters) + 7};
     const Shared part{(GLOBAL double *)(S.mw_sync + kMwPad * (kMwMax + 1))};   // W maxima, then 2 W counts
 
-    // ---- this workgroup's shares
-    if (tid == 0) ok_lds = 1;
+    // ---- this workgroup's shares (and whether an earlier launch of the pass gave
+    // up: there is no state to go on from, and nobody waits again)
+    if (tid == 0) ok_lds = *sync.failed == 0;
     for (int l = tid; l < L; l += bd) {
         MwLevel q{};
         const int f0 = G(S.lvl_items_ptr)[l], f1 = G(S.lvl_items_ptr)[l + 1];
@@ -1607,6 +1608,7 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
         lv[l] = q;
     }
     __syncthreads();
+    if (!ok_lds) return;
     if (tid == 0) {                                         // LDS pairs and owned nodes, level by level
         int p = 0;
         for (int l = 0; l < L; ++l) {

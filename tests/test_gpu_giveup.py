@@ -4,6 +4,8 @@ The host forces it with the barrier's own limit (0 ticks: every wait that is
 not over at once ends) or by withholding a workgroup; every kernel returns
 normally, and no GPU work is broken on purpose.
 """
+import time
+
 import numpy as np
 import pytest
 
@@ -54,4 +56,20 @@ def test_overlapped_factorisation_after_a_launch_that_gave_up(monkeypatch):
     out = s.backward(_seed(sc))
     for k in KEYS:
         assert torch.equal(out[k], g[k]), k
+    s.close()
+
+
+def test_launches_behind_one_that_gave_up_do_not_wait_again(monkeypatch):
+    from paper_2106_05306_amd import _binding as B
+    sc = scenes.c2_sphere_drop(0, n=24, steps=24)
+    limit = 0.25
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "8")
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", str(int(limit * 1e8)))
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "1")
+    s = _sim(sc, checkpoint_every=2)                 # twelve launches
+    t0 = time.perf_counter()
+    with pytest.raises(B.SimError) as e:
+        s.forward(sc.steps)
+    assert e.value.code == B.SIM_ESYNC
+    assert time.perf_counter() - t0 < 4 * limit
     s.close()
