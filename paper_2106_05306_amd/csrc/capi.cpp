@@ -560,7 +560,7 @@ void build_device(sim *s) {
     D.mw_spin = mw_spin_default();
     {
         const char *e = std::getenv("DIFFCLOTH_MW_TEST_ABSENT");   // failure-handling tests
-        D.mw_absent = e && std::atoi(e) > 0 ? 1 : 0;
+        D.mw_absent = e ? std::max(std::atoi(e), 0) : 0;
     }
     D.warm_start = hm.warm_start;
     D.self_on = hm.self_d > 0 ? 1 : 0;
@@ -1474,6 +1474,18 @@ int mw_check(sim *s) {
     return flag ? SIM_ESYNC : SIM_OK;
 }
 
+// After SIM_ESYNC: the handle's workgroups were not all resident in time (the
+// device shared with launches that MwAdmission does not count, another process's
+// above all).  From here on it keeps to one workgroup, so that no later pass
+// waits for the limit again; true: the pass is to be run again that way.
+bool mw_give_up(sim *s) {
+    if (s->hd.mw_absent == 1) return false;          // (tests: the failure is to be reported)
+    s->mw_cap = std::min(s->mw_cap, 1);
+    s->mw_wgs = 0;
+    s->hd.mw = 0;
+    return true;
+}
+
 // Timing event k of the handle's stream (0/1 forward start/end, 2/3 backward).
 int time_mark(sim *s, int k) {
     if (!s->tev[k]) {
@@ -2126,13 +2138,7 @@ int sim_forward(sim_t *s, int32_t n_steps, double *x_traj_dev, double *xT_dev, d
             return rc;
         };
         int rc = pass();
-        if (rc == SIM_ESYNC && !s->hd.mw_absent) {
-            // its workgroups were not all resident in time (the device shared
-            // with other long launches): the same pass on one workgroup
-            s->hd.mw = 0;
-            rc = pass();
-            s->hd.mw = s->mw_wgs;
-        }
+        if (rc == SIM_ESYNC && mw_give_up(s)) rc = pass();
         s->tev_fwd = rc == SIM_OK;
         return rc;
     });

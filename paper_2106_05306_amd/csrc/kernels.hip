@@ -1544,7 +1544,7 @@ template <bool MIXED, bool km>
 __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restrict__ sims, const int32_t *__restrict__ map) {
     const SimDev &S = sims[map ? map[2 * blockIdx.x] : 0];
     const int W = S.mw, w = map ? map[2 * blockIdx.x + 1] : (int)blockIdx.x;
-    if (w >= W || (S.mw_absent && w == W - 1)) return;
+    if (w >= W || (S.mw_absent && W > 1 && w == W - 1)) return;
     extern __shared__ double dyn[];
     __shared__ double red[kMwThreads / 64];
     __shared__ MwLevel lv[kMwLevels];

@@ -73,3 +73,23 @@ def test_launches_behind_one_that_gave_up_do_not_wait_again(monkeypatch):
     assert e.value.code == B.SIM_ESYNC
     assert time.perf_counter() - t0 < 4 * limit
     s.close()
+
+
+def test_a_handle_that_gave_up_keeps_to_one_workgroup(monkeypatch):
+    sc = scenes.c2_sphere_drop(0, n=24, steps=6)
+    limit = 0.25
+    traj, _ = _one_workgroup(sc, monkeypatch)
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "8")
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", str(int(limit * 1e8)))
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "2")
+    s = _sim(sc)
+    assert s.stats()["fwd_workgroups"] == 8
+    took = []
+    for _ in range(3):
+        t0 = time.perf_counter()
+        t = s.forward(sc.steps, trajectory=True)[2]
+        took.append(time.perf_counter() - t0)
+        assert torch.equal(t, traj)
+        assert s.stats()["fwd_workgroups"] == 1
+    assert took[0] >= limit and max(took[1:]) < limit, took
+    s.close()
