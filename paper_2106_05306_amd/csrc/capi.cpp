@@ -2493,24 +2493,38 @@ int sim_batch_forward(sim_t *const *sims, int32_t n, const int32_t *n_steps, dou
         if (seg_len(sims[i]) > 0) return SIM_EINVAL;   // batched passes keep every record
         if (sims[i]->stream != sims[0]->stream || sims[i]->hd.mixed != sims[0]->hd.mixed) return SIM_EINVAL;
     }
-    sim *s0 = sims[0];
+    hipStream_t st = sims[0]->stream;
     return guarded([&] {
-        std::vector<SimDev> descs(n);
+        std::vector<int> who(n);             // members of the launch
+        for (int i = 0; i < n; ++i) who[i] = i;
         int rc = SIM_OK;
-        for (int i = 0; i < n && !rc; ++i) {
-            rc = prepare_forward(sims[i], n_steps[i]);
-            sims[i]->hd.step_begin = 0;
-            sims[i]->hd.step_end = n_steps[i];
-            sims[i]->hd.rec_step0 = 0;
-            arm_forward(sims[i]);
-            descs[i] = sims[i]->hd;
-            if (!rc) rc = push_desc(sims[i]);
+        while (!who.empty() && !rc) {
+            const int nw = (int)who.size();
+            std::vector<SimDev> descs(nw);
+            std::vector<sim *> hs(nw);
+            for (int q = 0; q < nw && !rc; ++q) {
+                sim *h = hs[q] = sims[who[q]];
+                rc = prepare_forward(h, n_steps[who[q]]);
+                h->hd.step_begin = 0;
+                h->hd.step_end = n_steps[who[q]];
+                h->hd.rec_step0 = 0;
+                arm_forward(h);
+                descs[q] = h->hd;
+                if (!rc) rc = push_desc(h);
+            }
+            if (!rc) rc = launch_batch_forward(hs.data(), nw, descs, batch_descs(hs[0], nw), st);
+            std::vector<int> again;          // members that gave up at a barrier: once more, on one workgroup
+            for (int q = 0; q < nw && !rc; ++q) {
+                const int i = who[q];
+                rc = finish_forward(hs[q], n_steps[i], xT_dev ? xT_dev[i] : nullptr, vT_dev ? vT_dev[i] : nullptr);
+                if (rc == SIM_ESYNC && mw_give_up(hs[q])) {
+                    again.push_back(i);
+                    rc = SIM_OK;
+                }
+            }
+            who = again;
         }
-        if (rc) return rc;
-        rc = launch_batch_forward(sims, n, descs, batch_descs(s0, n), s0->stream);
-        for (int i = 0; i < n && !rc; ++i)
-            rc = finish_forward(sims[i], n_steps[i], xT_dev ? xT_dev[i] : nullptr, vT_dev ? vT_dev[i] : nullptr);
-        (void)hipStreamSynchronize(s0->stream);
+        (void)hipStreamSynchronize(st);
         return rc;
     });
 }

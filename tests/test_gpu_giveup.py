@@ -93,3 +93,30 @@ def test_a_handle_that_gave_up_keeps_to_one_workgroup(monkeypatch):
         assert s.stats()["fwd_workgroups"] == 1
     assert took[0] >= limit and max(took[1:]) < limit, took
     s.close()
+
+
+def _batch(monkeypatch):
+    """Scenes for a batch, their results on one workgroup, and handles of which the larger two will give up."""
+    scs = [scenes.c2_sphere_drop(0, n=n, steps=st) for n, st in ((28, 7), (10, 9), (40, 5))]
+    ref = [_one_workgroup(sc, monkeypatch) for sc in scs]
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    sims = []
+    for sc in scs:
+        monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "2" if sc.n_nodes > 100 else "0")
+        sims.append(_sim(sc))
+    assert [s.stats()["fwd_workgroups"] > 1 for s in sims] == [True, False, True]
+    return scs, ref, sims
+
+
+def test_batch_members_that_gave_up_run_again(monkeypatch):
+    from paper_2106_05306_amd.sim import batch_backward, batch_forward
+    scs, ref, sims = _batch(monkeypatch)
+    for _ in range(2):
+        outs = batch_forward(sims, [sc.steps for sc in scs])
+        for sc, (traj, _), s, (x, _) in zip(scs, ref, sims, outs):
+            assert torch.equal(x, traj[-1]) and s.stats()["fwd_workgroups"] == 1
+            assert all(torch.equal(s.state(n)[0], traj[n]) for n in range(sc.steps + 1))
+    for s, (_, g), out in zip(sims, ref, batch_backward(sims, [_seed(sc) for sc in scs])):
+        for k in KEYS:
+            assert torch.equal(out[k], g[k]), k
+        s.close()
