@@ -92,6 +92,7 @@ struct sim {
     int phase = 0;                      // continuous batching: 0 idle, 1 forward armed, 2 forward done,
                                         // 3 backward armed, 4 backward done
     int cursor = 0, target = 0;         // next step (forward) / steps still to go back (backward)
+    double *chunk_f = nullptr;          // warm start: impulses at the start of a job's forward chunk
     int64_t counters_host[8] = {0};
     int nca = 0;
     int af_cap = 0;                     // step factors allocated (direct adjoint)
@@ -186,6 +187,12 @@ int64_t mw_spin_default() {
     const char *e = std::getenv("DIFFCLOTH_MW_SPIN");
     const long long v = e ? std::atoll(e) : -1;
     return v >= 0 ? (int64_t)v : (int64_t)1000000000;      // 10 s
+}
+
+// Whether a launch withholds a workgroup (failure-handling tests; SimDev::mw_absent)
+int mw_absent_default() {
+    const char *e = std::getenv("DIFFCLOTH_MW_TEST_ABSENT");
+    return e ? std::max(std::atoi(e), 0) : 0;
 }
 
 // Threads per workgroup of the multi-workgroup forward (DIFFCLOTH_MW_THREADS, a
@@ -558,10 +565,6 @@ void build_device(sim *s) {
     D.h = hm.h;
     D.fwd_tol = hm.fwd_tol;
     D.mw_spin = mw_spin_default();
-    {
-        const char *e = std::getenv("DIFFCLOTH_MW_TEST_ABSENT");   // failure-handling tests
-        D.mw_absent = e ? std::max(std::atoi(e), 0) : 0;
-    }
     D.warm_start = hm.warm_start;
     D.self_on = hm.self_d > 0 ? 1 : 0;
     D.self_d = hm.self_d;
@@ -1439,6 +1442,7 @@ int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, boo
 void arm_forward(sim *s) {
     ++s->hd.fwd_epoch;
     s->hd.mw_epoch += uint64_t(1) << 40;
+    s->hd.mw_absent = mw_absent_default();
 }
 
 // Forward launch of one handle (descriptor already pushed).
@@ -2457,6 +2461,7 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
         d.bsep = d.rec_v;
     }
     d.mw_epoch = uint64_t(1) << 40;
+    d.mw_absent = mw_absent_default();
     SimDev *dd = (SimDev *)(b + L.desc);
     // everything below is enqueued on the handle's stream; nothing allocates,
     // synchronises or clears memory with a memset (the call may be captured)
@@ -2589,7 +2594,7 @@ int sim_trim(sim_t *s) {
     for (void **p : {(void **)&s->hd.rec_x, (void **)&s->hd.rec_v, (void **)&s->hd.rec_ubar, (void **)&s->hd.rec_mode,
                      (void **)&s->hd.rec_obst, (void **)&s->ckpt, (void **)&s->gsteps, (void **)&s->hd.af,
                      (void **)&s->hd.af_ws, (void **)&s->d_work, (void **)&s->batch_desc,
-                     (void **)&s->batch_map, (void **)&s->hd.step_info}) {
+                     (void **)&s->batch_map, (void **)&s->chunk_f, (void **)&s->hd.step_info}) {
         dev_release(s, *p);
         *p = nullptr;
     }
@@ -2611,6 +2616,8 @@ int sim_job_forward(sim_t *s, int32_t n_steps) {
     return guarded([&] {
         int rc = prepare_forward(s, n_steps);
         if (rc) return rc;
+        if (s->hd.warm_start && s->mw_cap >= 2 && !s->chunk_f)
+            s->chunk_f = (double *)dev_alloc(s, 3 * (size_t)s->hd.m * sizeof(double));
         s->T = -1;
         s->phase = 1;
         s->cursor = 0;
@@ -2631,6 +2638,33 @@ int sim_job_backward(sim_t *s, const double *dL_dxT_dev, const double *dL_dvT_de
         return SIM_OK;
     });
 }
+
+namespace {
+
+// After a forward chunk of a job gave up: the state that it began with (its
+// first record; the impulses, which only a warm start takes over from the step
+// before, were kept) and the count of the iterations before it.
+int restore_chunk(sim *s) {
+    const size_t v3 = 3 * (size_t)s->hd.m, b = v3 * sizeof(double);
+    const int a = s->hd.step_begin;
+    int rc = copy_d2d(s, s->hd.x, a ? s->hd.rec_x + a * v3 : s->start_x, b);
+    if (!rc) rc = copy_d2d(s, s->hd.v, a ? s->hd.rec_v + a * v3 : s->start_v, b);
+    if (!rc && a && s->chunk_f) rc = copy_d2d(s, s->hd.f, s->chunk_f, b);
+    else if (!rc) rc = hip_err(launch_fill(s->hd.f, 0.0, (int64_t)v3, s->stream));
+    std::vector<int32_t> info(4 * (size_t)a);
+    if (!rc && a)
+        rc = hip_err(hipMemcpyAsync(info.data(), s->hd.step_info, info.size() * sizeof(int32_t), hipMemcpyDeviceToHost,
+                                    s->stream));
+    if (!rc) rc = hip_err(hipStreamSynchronize(s->stream));
+    s->counters_host[0] = s->counters_host[7] = 0;
+    for (int n = 0; n < a; ++n) s->counters_host[0] += info[4 * n];
+    if (!rc)
+        rc = hip_err(hipMemcpyAsync(s->hd.counters, s->counters_host, sizeof(s->counters_host), hipMemcpyHostToDevice,
+                                    s->stream));
+    return rc;
+}
+
+}  // namespace
 
 int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void *backward_stream, int32_t *left) {
     if (!sims || n < 1 || !steps) return SIM_EINVAL;
@@ -2654,6 +2688,8 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
                 h->hd.step_end = std::min(h->target, h->cursor + steps[i]);
                 h->hd.rec_step0 = 0;
                 arm_forward(h);
+                if (h->chunk_f && h->mw_cap >= 2 && h->cursor > 0 && !rc)
+                    rc = copy_d2d(h, h->chunk_f, h->hd.f, 3 * (size_t)h->hd.m * sizeof(double));
                 fw.push_back(h);
                 df.push_back(h->hd);
             } else {
@@ -2676,7 +2712,7 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
         SimDev *room = batch_descs(sims[0], fw.size() + bw.size());
         SimDev *dfd = fw.empty() ? nullptr : room;
         SimDev *dbd = bw.empty() ? nullptr : room + fw.size();
-        if (dbd) rc = hip_err(hipMemcpyAsync(dbd, db.data(), db.size() * sizeof(SimDev), hipMemcpyHostToDevice, sf));
+        if (!rc && dbd) rc = hip_err(hipMemcpyAsync(dbd, db.data(), db.size() * sizeof(SimDev), hipMemcpyHostToDevice, sf));
         if (!rc) rc = hip_err(hipStreamSynchronize(sf));          // descriptors in place before either stream uses them
         if (!rc && dfd) rc = launch_batch_forward(fw.data(), (int)fw.size(), df, dfd, sf);
         if (!rc && dbd) {
@@ -2689,10 +2725,44 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
         const int r1 = hip_err(hipStreamSynchronize(sf));
         const int r2 = hip_err(hipStreamSynchronize(sb));
         if (!rc) rc = r1 ? r1 : r2;
-        for (sim *h : fw)
-            if (!rc) rc = mw_check(h);
         if (rc) return rc;
+        for (sim *h : bw) {                      // whatever became of the forward chunks
+            h->cursor = h->hd.step_begin;
+            if (h->cursor == 0) h->phase = 4;
+        }
+        // chunks that gave up at a barrier: once more, on one workgroup, from the
+        // state that they began with
+        std::vector<sim *> done, again;
+        int failed = SIM_OK;
         for (sim *h : fw) {
+            const bool used = h->mw_used;
+            h->mw_used = false;
+            if (used) {
+                rc = read_counters(h);
+                if (rc) return rc;
+            }
+            if (!used || !h->counters_host[7]) {
+                done.push_back(h);
+                continue;
+            }
+            rc = restore_chunk(h);
+            if (rc) return rc;
+            if (mw_give_up(h)) again.push_back(h);
+            else failed = SIM_ESYNC;
+        }
+        if (!again.empty()) {
+            df.clear();
+            for (sim *h : again) {
+                arm_forward(h);
+                df.push_back(h->hd);
+            }
+            rc = launch_batch_forward(again.data(), (int)again.size(), df, dfd, sf);
+            const int r3 = hip_err(hipStreamSynchronize(sf));
+            if (!rc) rc = r3;
+            if (rc) return rc;
+            done.insert(done.end(), again.begin(), again.end());
+        }
+        for (sim *h : done) {
             h->cursor = h->hd.step_end;
             if (h->cursor == h->target) {
                 rc = read_counters(h);
@@ -2701,10 +2771,7 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
                 h->phase = 2;
             }
         }
-        for (sim *h : bw) {
-            h->cursor = h->hd.step_begin;
-            if (h->cursor == 0) h->phase = 4;
-        }
+        if (failed) return failed;
         if (left)
             for (int i = 0; i < n; ++i)
                 left[i] = sims[i]->phase == 1 ? sims[i]->target - sims[i]->cursor

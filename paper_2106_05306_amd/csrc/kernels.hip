@@ -1544,7 +1544,8 @@ template <bool MIXED, bool km>
 __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restrict__ sims, const int32_t *__restrict__ map) {
     const SimDev &S = sims[map ? map[2 * blockIdx.x] : 0];
     const int W = S.mw, w = map ? map[2 * blockIdx.x + 1] : (int)blockIdx.x;
-    if (w >= W || (S.mw_absent && W > 1 && w == W - 1)) return;
+    const int absent = W > 1 && w == W - 1 ? S.mw_absent : 0;
+    if (w >= W || absent == 1 || absent == 2) return;
     extern __shared__ double dyn[];
     __shared__ double red[kMwThreads / 64];
     __shared__ MwLevel lv[kMwLevels];
@@ -1675,6 +1676,7 @@ __global__ __launch_bounds__(kMwThreads) void k_forward_mw(const SimDev *__restr
 
     int64_t iters_total = 0;
     for (int n = S.step_begin; n < S.step_end; ++n) {
+        if (absent == 3 && n > S.step_begin) return;
         const int slot = S.rec_ring ? 0 : n - S.rec_step0;
         const double t1 = (n + 1) * h;
         auto xrec = G(S.rec_x) + (int64_t)slot * 3 * m;

@@ -290,8 +290,9 @@ struct SimDev {
     int mw_off_t, mw_off_x, mw_off_own;   // dynamic LDS (doubles): gathered vectors, results, owned nodes' state
     int64_t mw_spin;                  // wall-clock ticks (100 MHz) a barrier waits before giving up
     int mw_absent;                    // failure-handling tests only (0: off): the last of several workgroups
-                                      //   returns at once, so every barrier wait ends at its limit; 1: the
-                                      //   failure is reported, 2: the pass is run again on one workgroup
+                                      //   returns (3: after the first step, else at once), so the others'
+                                      //   next barrier wait ends at its limit; 1: the failure is reported,
+                                      //   else the pass is run again on one workgroup
 
     // node-node self-collision (off when self_on == 0): pairs of mutually
     // nearest eligible nodes found on the predictor each step; the pair's

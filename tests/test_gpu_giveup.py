@@ -95,22 +95,29 @@ def test_a_handle_that_gave_up_keeps_to_one_workgroup(monkeypatch):
     s.close()
 
 
-def _batch(monkeypatch):
-    """Scenes for a batch, their results on one workgroup, and handles of which the larger two will give up."""
+def _batch(monkeypatch, **kw):
+    """Scenes for a batch, in contact from the first steps on, their results on
+    one workgroup, and handles of which the second never waits for others."""
     scs = [scenes.c2_sphere_drop(0, n=n, steps=st) for n, st in ((28, 7), (10, 9), (40, 5))]
-    ref = [_one_workgroup(sc, monkeypatch) for sc in scs]
+    for sc in scs:
+        sc.X = sc.X - np.array([0.0, 0.27, 0.0])
+    ref = [_one_workgroup(sc, monkeypatch, **kw) for sc in scs]
     monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
     sims = []
     for sc in scs:
-        monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "2" if sc.n_nodes > 100 else "0")
-        sims.append(_sim(sc))
+        with monkeypatch.context() as mp:
+            if sc.n_nodes <= 100:
+                mp.setenv("DIFFCLOTH_FWD_WGS", "1")
+            sims.append(_sim(sc, **kw))
     assert [s.stats()["fwd_workgroups"] > 1 for s in sims] == [True, False, True]
     return scs, ref, sims
 
 
-def test_batch_members_that_gave_up_run_again(monkeypatch):
+@pytest.mark.parametrize("absent", ["2", "3"])      # at the first barrier, or in the second step
+def test_batch_members_that_gave_up_run_again(monkeypatch, absent):
     from paper_2106_05306_amd.sim import batch_backward, batch_forward
     scs, ref, sims = _batch(monkeypatch)
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", absent)
     for _ in range(2):
         outs = batch_forward(sims, [sc.steps for sc in scs])
         for sc, (traj, _), s, (x, _) in zip(scs, ref, sims, outs):
@@ -119,4 +126,52 @@ def test_batch_members_that_gave_up_run_again(monkeypatch):
     for s, (_, g), out in zip(sims, ref, batch_backward(sims, [_seed(sc) for sc in scs])):
         for k in KEYS:
             assert torch.equal(out[k], g[k]), k
+        s.close()
+
+
+@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("at", [0, 1])
+def test_job_chunks_that_gave_up_run_again(monkeypatch, warm, at):
+    # the larger two give up in the second step of their chunk number `at`, while an adjoint job
+    # advances beside them; each chunk counts once
+    from paper_2106_05306_amd.sim import batch_advance
+    scs, ref, sims = _batch(monkeypatch, warm_start=warm)
+    iters = []
+    for sc in scs:
+        with monkeypatch.context() as mp:
+            mp.setenv("DIFFCLOTH_FWD_WGS", "0")
+            s = _sim(sc, warm_start=warm)
+            s.forward(sc.steps)
+            iters.append(s.stats()["fwd_iters_total"])
+            s.close()
+    adj = _sim(scs[1], warm_start=warm)
+    adj.job_forward(scs[1].steps)
+    while batch_advance([adj], [16])[0] > 0:
+        pass
+    adj.job_backward(_seed(scs[1]))
+    for sc, s in zip(scs, sims):
+        s.job_forward(sc.steps)
+    left = batch_advance(sims, [2, 2, 2]) if at else [sc.steps for sc in scs]
+    assert [s.stats()["fwd_workgroups"] > 1 for s in sims] == [True, False, True]
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "3")
+    n = 0
+    while sum(left) > 0:
+        on = [i for i in range(3) if left[i] > 0]
+        group = [sims[i] for i in on] + ([adj] if n < 3 else [])
+        got = batch_advance(group, [2] * len(on) + ([3] if n < 3 else []))
+        for i, k in zip(on, got):
+            assert k == max(0, left[i] - 2)
+            left[i] = k
+        if n < 3:
+            assert got[-1] == 9 - 3 * (n + 1)
+        n += 1
+    assert n >= 3
+    assert [s.stats()["fwd_workgroups"] for s in sims] == [1, 1, 1]
+    g = adj.job_grads()
+    for k in KEYS:
+        assert torch.equal(g[k], ref[1][1][k]), k
+    adj.close()
+    for sc, s, (traj, _), it in zip(scs, sims, ref, iters):
+        assert all(torch.equal(s.state(j)[0], traj[j]) for j in range(sc.steps + 1))
+        assert s.stats()["fwd_iters_total"] == it
         s.close()
