@@ -1467,7 +1467,7 @@ int run_forward_range(sim *s, int a, int b) {
 }
 
 // A multi-workgroup forward launch since the last check gave up at a barrier
-// (a workgroup waited longer than mw_spin): SIM_ESYNC.
+// (a workgroup waited longer than mw_spin): SIM_ESYNC, and its flag is cleared.
 int mw_check(sim *s) {
     if (!s->mw_used) return SIM_OK;
     int64_t flag = 0;
@@ -1475,7 +1475,9 @@ int mw_check(sim *s) {
     if (!rc) rc = hip_err(hipStreamSynchronize(s->stream));
     if (rc) return rc;
     s->mw_used = false;
-    return flag ? SIM_ESYNC : SIM_OK;
+    if (!flag) return SIM_OK;
+    rc = hip_err(launch_fill((double *)(s->hd.counters + 7), 0.0, 1, s->stream));
+    return rc ? rc : SIM_ESYNC;
 }
 
 // After SIM_ESYNC: the handle's workgroups were not all resident in time (the
@@ -1789,6 +1791,19 @@ int load_ckpt(sim *s, int seg) {
     if (!rc) rc = copy_d2d(s, s->hd.v, c + v3, b);
     if (!rc) rc = copy_d2d(s, s->hd.f, c + 2 * v3, b);
     return rc;
+}
+
+// The records of checkpoint segment seg (steps [a, b)) once more, for a caller
+// that reads them next.
+int replay_segment(sim *s, int seg, int a, int b) {
+    auto run = [&] {
+        int rc = load_ckpt(s, seg);
+        if (!rc) rc = run_forward_range(s, a, b);
+        if (!rc) rc = mw_check(s);
+        return rc;
+    };
+    const int rc = run();
+    return rc == SIM_ESYNC && mw_give_up(s) ? run() : rc;
 }
 
 int factor_pairs(sim *owner, const SimDev *d_descs, const std::vector<sim *> &hs, const std::vector<int32_t> &pairs,
@@ -2109,8 +2124,7 @@ int write_grads(sim *s, const sim_grads_t *out) {
 // Warnings of the last backward pass, the most severe first: non-finite state
 // gradients, a missed tolerance, a fallback.
 int backward_status(sim *s) {
-    int rc = mw_check(s);                   // checkpoint segments replayed by the forward kernel
-    if (!rc) rc = read_counters(s);
+    int rc = read_counters(s);
     if (rc) return rc;
     {
         const size_t v3 = 3 * (size_t)s->hd.m;
@@ -2153,10 +2167,16 @@ int sim_backward(sim_t *s, const double *dL_dxT_dev, const double *dL_dvT_dev, c
     if (!s) return SIM_EINVAL;
     if (s->T < 1) return SIM_ESTATE;
     return guarded([&] {
-        int rc = prepare_backward(s, dL_dxT_dev, dL_dvT_dev, dL_dx_steps_dev);
-        if (!rc) rc = time_mark(s, 2);
-        if (!rc) rc = backward_all(s);
-        if (!rc) rc = time_mark(s, 3);
+        auto pass = [&] {
+            int rc = prepare_backward(s, dL_dxT_dev, dL_dvT_dev, dL_dx_steps_dev);
+            if (!rc) rc = time_mark(s, 2);
+            if (!rc) rc = backward_all(s);
+            if (!rc) rc = time_mark(s, 3);
+            if (!rc) rc = mw_check(s);      // checkpoint segments replayed by the forward kernel
+            return rc;
+        };
+        int rc = pass();
+        if (rc == SIM_ESYNC && mw_give_up(s)) rc = pass();
         if (!rc) rc = write_grads(s, out);
         if (!rc) rc = backward_status(s);
         s->tev_bwd = rc >= 0;
@@ -2208,9 +2228,7 @@ int sim_state(const sim_t *cs, int32_t n, double *x_dev, double *v_dev) {
         int slot = n;
         if (k > 0) {
             const int seg = std::min(n / k, (s->T - 1) / k), a = seg * k, b = std::min(s->T, a + k);
-            rc = load_ckpt(s, seg);
-            if (!rc) rc = run_forward_range(s, a, b);
-            if (!rc) rc = mw_check(s);
+            rc = replay_segment(s, seg, a, b);
             slot = n - a;
         }
         if (!rc && x_dev) rc = hip_err(launch_permute3(s->hd.rec_x + slot * v3, x_dev, s->d_perm, m, true, s->stream));
@@ -2231,9 +2249,7 @@ int sim_modes(const sim_t *cs, int32_t n, uint8_t *modes_host) {
         int slot = n;
         if (k > 0) {                        // recompute the segment holding step n
             const int seg = n / k, a = seg * k, b = std::min(s->T, a + k);
-            rc = load_ckpt(s, seg);
-            if (!rc) rc = run_forward_range(s, a, b);
-            if (!rc) rc = mw_check(s);
+            rc = replay_segment(s, seg, a, b);
             slot = n - a;
         }
         if (!rc) rc = hip_err(launch_modes(s->hd.rec_mode + (size_t)slot * m, s->d_modes_tmp, s->d_perm, m, s->stream));
@@ -2259,9 +2275,7 @@ int sim_self_pairs(const sim_t *cs, int32_t n, int32_t *partner_host) {
         int slot = n;
         if (k > 0) {                        // recompute the segment holding step n
             const int seg = n / k, a = seg * k, b = std::min(s->T, a + k);
-            rc = load_ckpt(s, seg);
-            if (!rc) rc = run_forward_range(s, a, b);
-            if (!rc) rc = mw_check(s);
+            rc = replay_segment(s, seg, a, b);
             slot = n - a;
         }
         std::vector<int32_t> p(m);

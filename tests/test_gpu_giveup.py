@@ -175,3 +175,33 @@ def test_job_chunks_that_gave_up_run_again(monkeypatch, warm, at):
         assert all(torch.equal(s.state(j)[0], traj[j]) for j in range(sc.steps + 1))
         assert s.stats()["fwd_iters_total"] == it
         s.close()
+
+
+@pytest.mark.parametrize("solver", ["iterative", "direct"])
+@pytest.mark.parametrize("first", ["backward", "state", "modes"])
+def test_replayed_segments_that_gave_up_run_again(monkeypatch, solver, first):
+    sc = scenes.c2_sphere_drop(0, n=24, steps=11)
+    sc.X = sc.X - np.array([0.0, 0.27, 0.0])        # in contact from the first steps on
+    kw = dict(adj_solver=solver, adj_tol=1e-9, adj_max_iters=40)
+    traj, g = _one_workgroup(sc, monkeypatch, **kw)
+    with monkeypatch.context() as mp:
+        mp.setenv("DIFFCLOTH_FWD_WGS", "0")
+        r = _sim(sc, **kw)
+        r.forward(sc.steps)
+        modes = [r.modes(n) for n in range(sc.steps)]
+        r.close()
+    assert any((m != 0).any() for m in modes)
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "16")
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    s = _sim(sc, checkpoint_every=4, **kw)
+    assert torch.equal(s.forward(sc.steps, trajectory=True)[2], traj)
+    assert s.stats()["fwd_workgroups"] == 16
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "3")
+    seed = _seed(sc)
+    check = {"backward": lambda: [torch.equal(v, g[k]) for o in [s.backward(seed)] for k, v in o.items() if k in KEYS],
+             "state": lambda: [torch.equal(s.state(n)[0], traj[n]) for n in range(sc.steps + 1)],
+             "modes": lambda: [np.array_equal(s.modes(n), modes[n]) for n in range(sc.steps)]}
+    assert all(check[first]())
+    assert s.stats()["fwd_workgroups"] == 1
+    assert all(all(c()) for c in check.values())
+    s.close()
