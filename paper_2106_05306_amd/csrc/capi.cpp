@@ -548,6 +548,13 @@ bool mw_plan(const sim *s, int W, SimDev &d, size_t &bytes) {
     return true;
 }
 
+// Workgroups of multi-workgroup launches wait for each other, so all of them
+// have to be resident at the same time, one per compute unit (their LDS may be
+// all of it): an allocation-free forward gets at most a quarter of the device,
+// all other launches together (MwAdmission) the rest.
+int mw_noalloc_limit(const sim *s) { return std::min(kMwNoalloc, s->cus / 4); }
+int mw_limit(const sim *s) { return s->cus - mw_noalloc_limit(s); }
+
 // Build every device table from the host model and upload it.
 void build_device(sim *s) {
     HostModel &hm = s->hm;
@@ -1190,6 +1197,8 @@ void build_device(sim *s) {
     if (kernel_static_lds(&s->static_fwd, &s->static_bwd) != hipSuccess) throw std::runtime_error("hip attribute");
     if (hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         throw std::runtime_error("hip attribute");
+    if (const char *e = std::getenv("DIFFCLOTH_TEST_CUS"))   // tests: as on a device with fewer
+        s->cus = std::min(s->cus, std::max(std::atoi(e), 1));
     s->max_lds = (size_t)maxlds;
     if (configure_lds(s->max_lds - s->static_fwd, s->max_lds - s->static_bwd) != hipSuccess) s->max_lds = 0;
     plan_lds(s, s->flags_fwd, s->lds_fwd, true);
@@ -1202,7 +1211,7 @@ void build_device(sim *s) {
         mw_static_lds(&mw_static) == hipSuccess && mw_static < (size_t)maxlds &&
         configure_mw_lds((size_t)maxlds - mw_static) == hipSuccess)
         s->mw_max_lds = (size_t)maxlds - mw_static;
-    const int want = mw_workgroups_default(s->factor_bytes);
+    const int want = std::min(mw_workgroups_default(s->factor_bytes), mw_limit(s));
     if (want >= 2 && mw_plan(s, want, D, s->mw_lds)) s->mw_cap = want;
     s->mw_wgs = m >= kMwMinNodes || std::getenv("DIFFCLOTH_FWD_WGS") ? s->mw_cap : 0;
     D.mw = s->mw_wgs;
@@ -1239,7 +1248,6 @@ size_t batch_lds(sim *const *sims, int n, bool fwd, int &flags) {
 }
 
 int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, bool mesh, size_t lds, hipStream_t st);
-int mw_limit(const sim *s);
 
 // Workgroups of each handle of a batched forward launch (empty: one each,
 // k_forward).  A PD iteration of a handle takes about 2.5 us per level and
@@ -1380,12 +1388,11 @@ std::vector<int> overlap_chunks(const sim *s, int n_steps) {
     return ends;
 }
 
-// Workgroups of multi-workgroup launches wait for each other, so all of them
-// have to be resident: on one device at most the compute units, less
-// kMwNoalloc for an allocation-free forward (which may be captured and is not
-// counted here), may belong to launches that can run at the same time.  A
-// launch of W workgroups on st first waits (on the device) for the oldest ones
-// still in flight that would exceed this; their events are kept in launch order.
+// On one device at most mw_limit workgroups may belong to multi-workgroup
+// launches that can run at the same time (allocation-free forwards, which may be
+// captured, have a share of their own and are not counted here).  A launch of W
+// workgroups on st first waits (on the device) for the oldest ones still in
+// flight that would exceed this; their events are kept in launch order.
 struct MwAdmission {
     std::mutex mu;
     struct Entry { hipEvent_t ev; int W; };
@@ -1426,10 +1433,10 @@ MwAdmission &mw_admission() {
     (void)hipGetDevice(&dev);
     return per_device[dev >= 0 && dev < kMaxDevices ? dev : 0];
 }
-int mw_limit(const sim *s) { return std::max(s->cus - kMwNoalloc, 2); }
 
 // A multi-workgroup launch of `blocks` workgroups (see MwAdmission).
 int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, bool mesh, size_t lds, hipStream_t st) {
+    if (blocks > mw_limit(s)) return SIM_EINVAL;
     MwAdmission &adm = mw_admission();
     std::lock_guard<std::mutex> lock(adm.mu);
     int rc = adm.before(blocks, mw_limit(s), st);
@@ -2464,7 +2471,7 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
     // (a mesh whose rest fits the scratch but not the barrier block: one workgroup)
     size_t mw_lds = 0;
     const bool mw = s->mw_wgs >= 2 && L.mw_total <= kNoallocScratchBytes &&
-                    mw_plan(s, std::min(s->mw_wgs, kMwNoalloc), d, mw_lds);
+                    mw_noalloc_limit(s) >= 2 && mw_plan(s, std::min(s->mw_wgs, mw_noalloc_limit(s)), d, mw_lds);
     if (mw) {
         // a barrier block of its own, cleared below: the handle's block holds the
         // counts of the handle's own launches

@@ -92,7 +92,7 @@ constexpr int kMwMax = 192, kMwLevels = 24, kMwPad = 8;
 constexpr int kMwSyncWords = kMwPad * (kMwMax + 1) + 3 * kMwMax;
 constexpr int kMwThreads = 512;     // threads per workgroup, at most (1024 leave 128 registers: 88 spilled)
 constexpr int kMwNodeDoubles = 16;  // LDS of a workgroup per owned node (see MwNodes)
-constexpr int kMwNoalloc = 64;      // most workgroups of the allocation-free forward (see capi: mw_admit)
+constexpr int kMwNoalloc = 64;      // most workgroups of the allocation-free forward (see capi: mw_limit)
 constexpr int kTeamNodes = 1200;    // large meshes: larger leaves, lanes per item sized for a share of a level
 constexpr int kTeamShare = 16;      //   (one per subtree of the root, at most this many)
 constexpr size_t kNoallocScratchBytes = size_t(16) << 20;   // device scratch of the allocation-free forward
