@@ -429,7 +429,9 @@ int sim_job_grads(sim_t *sim, const sim_grads_t *out);
  * modes and frames, the running state) lives in one 16 MiB device array per
  * GPU that the library holds until the process ends; no call of this function
  * allocates, frees, synchronises or issues a memset (it only enqueues copies
- * and kernels on the handle's stream and returns).  Every call on one GPU uses
+ * and kernels on the handle's stream and returns).  Where its workgroups do not
+ * become resident together in time (the device shared with other long launches),
+ * the enqueued kernels run the pass again on one.  Every call on one GPU uses
  * that GPU's array: calls that overlap on one GPU (other streams, other
  * threads) race and their results are undefined.  Returns SIM_ESCRATCH when
  * the mesh needs more than the array holds (sim_noalloc_scratch_bytes tells

@@ -36,7 +36,7 @@ hipError_t launch_forward_mw(const SimDev *d, const int32_t *map, int blocks, bo
                              hipStream_t st);
 hipError_t mw_static_lds(size_t *bytes);
 hipError_t configure_mw_lds(size_t bytes);
-hipError_t launch_poison(const int64_t *flag, double *x, double *v, int64_t n, hipStream_t st);
+hipError_t launch_again(SimDev *d, const double *x0, const double *v0, int64_t n, hipStream_t st);
 }  // namespace dc
 
 using namespace dc;
@@ -2480,6 +2480,8 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
         // records, which is written before the first barrier and not read
         d.ysol = d.rec_x;
         d.bsep = d.rec_v;
+    } else {
+        d.mw = 0;
     }
     d.mw_epoch = uint64_t(1) << 40;
     d.mw_absent = mw_absent_default();
@@ -2497,11 +2499,14 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
         if (!rc)
             rc = hip_err(launch_forward_mw(dd, nullptr, d.mw, s->hd.mixed != 0, has_mesh(&s, 1), mw_lds, mw_threads_default(),
                                            s->stream));
-        // a launch that gave up at a barrier must not pass for a result
-        if (!rc) rc = hip_err(launch_poison(d.counters + 7, d.x, d.v, 3 * (int64_t)m, s->stream));
-    } else if (!rc) {
-        rc = hip_err(launch_forward(dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, 0, has_mesh(&s, 1), s->stream));
+        // nobody waits for the outcome: the one-workgroup kernel follows, with no
+        // steps left unless this one gave up
+        if (!rc) rc = hip_err(launch_again(dd, s->start_x, s->start_v, 3 * (int64_t)m, s->stream));
     }
+    // (a captured pass reads the descriptor of the handle's latest call when it is
+    // replayed: whichever kernels either call chose, the last one here completes it)
+    if (!rc)
+        rc = hip_err(launch_forward(dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, 0, has_mesh(&s, 1), s->stream));
     if (!rc) rc = hip_err(launch_permute3(d.x, xT_dev, s->d_perm, m, true, s->stream));
     if (!rc) rc = hip_err(launch_permute3(d.v, vT_dev, s->d_perm, m, true, s->stream));
     return rc;

@@ -3460,10 +3460,17 @@ __global__ void k_fill(double *p, double v, int64_t n) {
     if (i < n) p[i] = v;
 }
 
-// NaN everywhere if flag is set (a forward launch that gave up)
-__global__ void k_poison(const int64_t *__restrict__ flag, double *__restrict__ x, double *__restrict__ v, int64_t n) {
+// Between the multi-workgroup launch of an allocation-free forward and a
+// one-workgroup launch of the same descriptor: the state of 3 m = n entries as at
+// the start for the latter when the former gave up at a barrier (or had nothing
+// to do: mw < 2), else no steps are left for it.
+__global__ void k_again(SimDev *__restrict__ d, const double *__restrict__ x0, const double *__restrict__ v0, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && *flag != 0) x[i] = v[i] = __builtin_nan("");
+    if (d->mw < 2 || d->counters[7] != 0) {
+        if (i < n) { d->x[i] = x0[i]; d->v[i] = v0[i]; d->f[i] = 0.0; }
+    } else if (i == 0) {
+        d->step_end = d->step_begin;
+    }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -3641,8 +3648,8 @@ hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_poison(const int64_t *flag, double *x, double *v, int64_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_poison, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, flag, x, v, n);
+hipError_t launch_again(SimDev *d, const double *x0, const double *v0, int64_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_again, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, x0, v0, n);
     return hipGetLastError();
 }
 

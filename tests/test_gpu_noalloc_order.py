@@ -20,9 +20,9 @@ def _sim(sc, **kw):
     return Sim.from_scene(sc, device=DEV, precision="mixed", **kw)
 
 
-def _one_workgroup(sc, monkeypatch):
+def _one_workgroup(sc, monkeypatch, **kw):
     monkeypatch.setenv("DIFFCLOTH_FWD_WGS", "0")
-    s = _sim(sc)
+    s = _sim(sc, **kw)
     assert s.stats()["fwd_workgroups"] == 1
     xT, vT, _ = s.forward(sc.steps)
     out = xT.clone(), vT.clone()
@@ -94,4 +94,54 @@ def test_captured_pass_replayed_while_the_handle_runs(monkeypatch):
         side.synchronize()
         assert torch.equal(xT, rx) and torch.equal(vT, rv)
     torch.cuda.synchronize()
+    s.close()
+
+
+@pytest.mark.parametrize("absent", ["2", "3"])      # at the first barrier, or in the second step
+@pytest.mark.parametrize("warm", [False, True])
+def test_pass_that_gave_up_runs_again(monkeypatch, absent, warm):
+    # (a workgroup withheld by the host: the others' waits end at their limit)
+    sc = scenes.c2_sphere_drop(0, n=24, steps=6)
+    sc.X = sc.X - np.array([0.0, 0.27, 0.0])        # in contact from the first steps on
+    rx, rv = _one_workgroup(sc, monkeypatch, warm_start=warm)
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    s = _sim(sc, warm_start=warm)
+    assert s.stats()["fwd_workgroups"] > 1
+    for a in (absent, "0", absent):
+        monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", a)
+        xT, vT = _noalloc(s, sc.steps)
+        torch.cuda.synchronize()
+        assert torch.equal(xT, rx) and torch.equal(vT, rv)
+    s.close()
+
+
+def test_captured_pass_of_a_handle_that_keeps_to_one_workgroup_since(monkeypatch):
+    # a replay takes the descriptor of the handle's latest call, which then chose another kernel
+    sc = scenes.c2_sphere_drop(0, n=24, steps=6)
+    rx, rv = _one_workgroup(sc, monkeypatch)
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = _sim(sc, stream=st)
+        xT, vT = (torch.zeros((s.m, 3), dtype=torch.float64, device=DEV) for _ in range(2))
+        s.forward_noalloc(sc.steps, xT, vT)
+        st.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        s.forward_noalloc(sc.steps, xT, vT)
+    for later in range(3):
+        with torch.cuda.stream(st):
+            if later == 1:
+                monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "2")
+                s.forward(sc.steps)
+                monkeypatch.delenv("DIFFCLOTH_MW_TEST_ABSENT")
+                assert s.stats()["fwd_workgroups"] == 1
+            if later == 2:
+                s.forward_noalloc(sc.steps, xT, vT)
+            for _ in range(2):
+                xT.zero_()
+                vT.zero_()
+                g.replay()
+                st.synchronize()
+                assert torch.equal(xT, rx) and torch.equal(vT, rv)
     s.close()
