@@ -504,11 +504,16 @@ void spring_incidence(const HostModel &hm, const std::vector<int32_t> &corder, i
     }
 }
 
+// Whether the tree has a root supernode at the leaves' level.  On several
+// workgroups the contact update of its nodes would overtake the local step of
+// others there; on one, a __syncthreads lies between them.
+bool leaf_root(const sim *s) { return s->lvl_root[0] < s->lvl_items[1]; }
+
 // Multi-workgroup forward of handle s on W workgroups: the LDS layout (into d)
 // and the dynamic LDS it takes (bytes); false: not available.  The factor goes
 // into LDS when every workgroup's share fits beside its vectors.
 bool mw_plan(const sim *s, int W, SimDev &d, size_t &bytes) {
-    if (s->mw_max_lds == 0 || W < 1 || W > kMwMax) return false;
+    if (s->mw_max_lds == 0 || W < 1 || W > kMwMax || (W > 1 && leaf_root(s))) return false;
     int64_t pairs = 0, vec = 3, res = 3, own = 1;
     auto share = [&](int a, int b, int w) { return a + (int)((int64_t)(b - a) * w / W); };
     for (int w = 0; w < W; ++w) {
@@ -1203,12 +1208,10 @@ void build_device(sim *s) {
     if (configure_lds(s->max_lds - s->static_fwd, s->max_lds - s->static_bwd) != hipSuccess) s->max_lds = 0;
     plan_lds(s, s->flags_fwd, s->lds_fwd, true);
     plan_lds(s, s->flags_bwd, s->lds_bwd, false);
-    // the multi-workgroup forward: a tree of at least two levels without a root
-    // at the leaves' level (a root node's contact update would overtake the
-    // local step of other workgroups there)
+    // the multi-workgroup forward (a mesh with a root among the leaves: as a
+    // member of a batch only, see batch_workgroups)
     size_t mw_static = 0;
-    if (hm.n_levels >= 2 && hm.n_levels <= kMwLevels && s->lvl_root[0] == s->lvl_items[1] &&
-        mw_static_lds(&mw_static) == hipSuccess && mw_static < (size_t)maxlds &&
+    if (hm.n_levels <= kMwLevels && mw_static_lds(&mw_static) == hipSuccess && mw_static < (size_t)maxlds &&
         configure_mw_lds((size_t)maxlds - mw_static) == hipSuccess)
         s->mw_max_lds = (size_t)maxlds - mw_static;
     const int want = std::min(mw_workgroups_default(s->factor_bytes), mw_limit(s));
@@ -1253,12 +1256,14 @@ int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, boo
 // k_forward).  A PD iteration of a handle takes about 2.5 us per level and
 // direction of its solves (a barrier and the loads after it) and 0.7 ns per pair
 // of factor entries on one workgroup; the workgroups the device can hold go to
-// whichever handle would finish last.
+// whichever handle would finish last.  A mesh that is one dense block (a tree of
+// one level) keeps to one; a larger one with a root among its leaves could not
+// be split either and would be the last for that, so the batch is left as it is.
 std::vector<int> batch_workgroups(sim *const *sims, int n) {
     const int limit = mw_limit(sims[0]);
     bool want = false;
     for (int i = 0; i < n; ++i) {
-        if (sims[i]->mw_max_lds == 0) return {};
+        if (sims[i]->mw_max_lds == 0 || (leaf_root(sims[i]) && sims[i]->hm.n_levels > 1)) return {};
         want = want || sims[i]->mw_wgs >= 2;
     }
     if (!want || 2 * n > limit) return {};

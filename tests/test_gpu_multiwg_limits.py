@@ -57,3 +57,38 @@ def test_workgroups_that_wait_for_each_other_fit_the_device(monkeypatch, cus):
         assert torch.equal(x, rx) and torch.equal(v, rv)
     for s in sims:
         s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kw", [{}, dict(warm_start=True), dict(fwd_tol=1e-7, fwd_max_iters=4000)],
+                         ids=["", "warm", "converged"])
+def test_one_block_members_leave_a_batch_on_many_workgroups(monkeypatch, precision, kw):
+    # sheets of one to 32 nodes (a tree of one level) beside larger ones: all of
+    # them on the multi-workgroup kernel, which gives up where the larger
+    # one's last workgroup is withheld
+    from paper_2106_05306_amd import _binding as B
+    from paper_2106_05306_amd.sim import batch_advance, batch_forward
+    scs = [_low(scenes.c2_sphere_drop(0, n=n, steps=st)) for n, st in ((2, 3), (5, 9), (28, 4))]
+    scs.append(scenes.tiny_scene(4, steps=7, obstacle="plane", height=0.002))
+    ref = [_one_workgroup(sc, monkeypatch, precision=precision, **kw) for sc in scs]
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    sims = [_sim(sc, precision=precision, **kw) for sc in scs]
+    assert [s.stats()["fwd_workgroups"] > 1 for s in sims] == [False, False, True, False]
+    for (x, v), (rx, rv) in zip(batch_forward(sims, [sc.steps for sc in scs]), ref):
+        assert torch.equal(x, rx) and torch.equal(v, rv)
+    for sc, s in zip(scs, sims):
+        s.job_forward(sc.steps)
+    left = [sc.steps for sc in scs]
+    while sum(left) > 0:
+        on = [i for i in range(4) if left[i] > 0]
+        for i, k in zip(on, batch_advance([sims[i] for i in on], [2] * len(on))):
+            left[i] = k
+    for sc, s, (rx, rv) in zip(scs, sims, ref):
+        x, v = s.state(sc.steps)
+        assert torch.equal(x, rx) and torch.equal(v, rv)
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "1")
+    with pytest.raises(B.SimError) as e:
+        batch_forward(sims, [sc.steps for sc in scs])
+    assert e.value.code == B.SIM_ESYNC
+    for s in sims:
+        s.close()
