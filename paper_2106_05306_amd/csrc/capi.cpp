@@ -1132,6 +1132,8 @@ void build_device(sim *s) {
     D.ysol = zeros<double>(s, v3);
     D.bsep = zeros<double>(s, v3);
     D.mw_sync = zeros<uint64_t>(s, kMwSyncWords);
+    if (const char *e = std::getenv("DIFFCLOTH_TEST_LAUNCHES"))   // tests: as after so many launches
+        D.mw_epoch = (uint64_t)std::atoll(e) << 40;
     D.f = zeros<double>(s, v3);
     D.wp = zeros<double>(s, 3 * (size_t)std::max(nca, 1));
     D.mode = zeros<uint8_t>(s, m);
@@ -1451,10 +1453,18 @@ int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, boo
 }
 
 // Tags the next forward launch of the handle (before its descriptor is copied).
-void arm_forward(sim *s) {
+// Its barriers count from the tag's base, above every count of earlier launches;
+// after 2^24 - 1 of them, when there is no higher base, the block is cleared.
+int arm_forward(sim *s) {
+    int rc = SIM_OK;
     ++s->hd.fwd_epoch;
     s->hd.mw_epoch += uint64_t(1) << 40;
+    if (s->hd.mw_epoch < uint64_t(1) << 40) {
+        s->hd.mw_epoch = uint64_t(1) << 40;
+        rc = hip_err(launch_fill((double *)s->hd.mw_sync, 0.0, kMwSyncWords, s->stream));
+    }
     s->hd.mw_absent = mw_absent_default();
+    return rc;
 }
 
 // Forward launch of one handle (descriptor already pushed).
@@ -1472,8 +1482,8 @@ int run_forward_range(sim *s, int a, int b) {
     s->hd.step_begin = a;
     s->hd.step_end = b;
     s->hd.rec_step0 = a;
-    arm_forward(s);
-    int rc = push_desc(s);
+    int rc = arm_forward(s);
+    if (!rc) rc = push_desc(s);
     if (rc) return rc;
     return launch_single_forward(s);
 }
@@ -1858,8 +1868,8 @@ int forward_overlapped(sim *s, int n_steps, const std::vector<int> &ends) {
         s->hd.step_begin = a;
         s->hd.step_end = b;
         s->hd.rec_step0 = 0;
-        arm_forward(s);
-        rc = push_desc(s);
+        rc = arm_forward(s);
+        if (!rc) rc = push_desc(s);
         if (!rc) rc = launch_single_forward(s);
         if (!rc && pa >= 0) {                // the previous chunk, queued behind this one's launch
             std::vector<int32_t> pairs;
@@ -2544,7 +2554,7 @@ int sim_batch_forward(sim_t *const *sims, int32_t n, const int32_t *n_steps, dou
                 h->hd.step_begin = 0;
                 h->hd.step_end = n_steps[who[q]];
                 h->hd.rec_step0 = 0;
-                arm_forward(h);
+                if (!rc) rc = arm_forward(h);
                 descs[q] = h->hd;
                 if (!rc) rc = push_desc(h);
             }
@@ -2718,7 +2728,7 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
                 h->hd.step_begin = h->cursor;
                 h->hd.step_end = std::min(h->target, h->cursor + steps[i]);
                 h->hd.rec_step0 = 0;
-                arm_forward(h);
+                if (!rc) rc = arm_forward(h);
                 if (h->chunk_f && h->mw_cap >= 2 && h->cursor > 0 && !rc)
                     rc = copy_d2d(h, h->chunk_f, h->hd.f, 3 * (size_t)h->hd.m * sizeof(double));
                 fw.push_back(h);
@@ -2784,7 +2794,8 @@ int sim_batch_advance(sim_t *const *sims, int32_t n, const int32_t *steps, void 
         if (!again.empty()) {
             df.clear();
             for (sim *h : again) {
-                arm_forward(h);
+                rc = arm_forward(h);
+                if (rc) return rc;
                 df.push_back(h->hd);
             }
             rc = launch_batch_forward(again.data(), (int)again.size(), df, dfd, sf);

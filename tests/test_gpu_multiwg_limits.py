@@ -92,3 +92,28 @@ def test_one_block_members_leave_a_batch_on_many_workgroups(monkeypatch, precisi
     assert e.value.code == B.SIM_ESYNC
     for s in sims:
         s.close()
+
+
+def test_barrier_counts_after_16_million_launches(monkeypatch):
+    # a launch's counts start 2^40 above the last one's: the 2^24th would start below them
+    from paper_2106_05306_amd.sim import batch_advance, batch_forward
+    sc = _low(scenes.c2_sphere_drop(0, n=28, steps=4))
+    rx, rv = _one_workgroup(sc, monkeypatch)
+    monkeypatch.setenv("DIFFCLOTH_TEST_LAUNCHES", str(2 ** 24 - 3))
+    passes = {"forward": lambda s: s.forward(sc.steps)[:2], "batch": lambda s: batch_forward([s], [sc.steps])[0]}
+
+    def job(s):
+        s.job_forward(sc.steps)
+        while batch_advance([s], [1])[0] > 0:
+            pass
+        return s.state(sc.steps)
+
+    passes["job"] = job
+    for run in passes.values():
+        s = _sim(sc)
+        assert s.stats()["fwd_workgroups"] > 1
+        for _ in range(6):
+            x, v = run(s)
+            assert torch.equal(x, rx) and torch.equal(v, rv)
+        assert s.stats()["fwd_workgroups"] > 1
+        s.close()
