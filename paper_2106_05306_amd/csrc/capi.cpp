@@ -36,7 +36,6 @@ hipError_t launch_forward_mw(const SimDev *d, const int32_t *map, int blocks, bo
                              hipStream_t st);
 hipError_t mw_static_lds(size_t *bytes);
 hipError_t configure_mw_lds(size_t bytes);
-hipError_t launch_again(SimDev *d, const double *x0, const double *v0, int64_t n, hipStream_t st);
 }  // namespace dc
 
 using namespace dc;
@@ -2495,6 +2494,8 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
         // records, which is written before the first barrier and not read
         d.ysol = d.rec_x;
         d.bsep = d.rec_v;
+        d.again_x = s->start_x;
+        d.again_v = s->start_v;
     } else {
         d.mw = 0;
     }
@@ -2514,12 +2515,12 @@ int sim_forward_noalloc(sim_t *s, int32_t n_steps, double *xT_dev, double *vT_de
         if (!rc)
             rc = hip_err(launch_forward_mw(dd, nullptr, d.mw, s->hd.mixed != 0, has_mesh(&s, 1), mw_lds, mw_threads_default(),
                                            s->stream));
-        // nobody waits for the outcome: the one-workgroup kernel follows, with no
-        // steps left unless this one gave up
-        if (!rc) rc = hip_err(launch_again(dd, s->start_x, s->start_v, 3 * (int64_t)m, s->stream));
     }
-    // (a captured pass reads the descriptor of the handle's latest call when it is
-    // replayed: whichever kernels either call chose, the last one here completes it)
+    // Nobody waits for that one's outcome: the one-workgroup kernel follows and
+    // runs the pass again if it gave up.  (A captured pass reads the descriptor of
+    // the handle's latest call when it is replayed.  Such a call may have taken one
+    // workgroup, never more than the captured one: a handle that gave up stays on
+    // one.  The launch above then does nothing and this one the whole pass.)
     if (!rc)
         rc = hip_err(launch_forward(dd, 1, s->hd.mixed != 0, s->lds_fwd, s->flags_fwd, 0, has_mesh(&s, 1), s->stream));
     if (!rc) rc = hip_err(launch_permute3(d.x, xT_dev, s->d_perm, m, true, s->stream));

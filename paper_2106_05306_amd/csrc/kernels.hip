@@ -1,11 +1,13 @@
 // gfx950 kernels of the DiffCloth hot path.
 //
-// One workgroup of 1024 threads (16 wavefronts) owns one cloth handle for a
-// whole launch: it runs every time step of a forward segment (PD local/global
-// iterations with the contact update) or every adjoint step of a backward
-// segment without returning to the host.  A batched launch gives each handle
-// its own workgroup.  All vectors stay in HBM / L2; workgroup barriers order
-// the phases, so results do not depend on scheduling (no floating-point
+// A launch runs every time step of a forward segment (PD local/global iterations
+// with the contact update) or every adjoint step of a backward segment without
+// returning to the host.  In k_forward and k_backward one workgroup of 1024
+// threads owns a cloth handle, in k_forward_mw several workgroups share one; a
+// batched launch holds many handles.  The factorisation of the adjoint's steps
+// (k_adj_*) runs over steps and blocks, a launch per kind of work and level.
+// Vectors lie in LDS where they fit, else in HBM / L2; barriers order the
+// phases, so results do not depend on scheduling (no floating-point additions by
 // atomics anywhere: every sum has a fixed order).
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -1082,6 +1084,15 @@ __global__ __launch_bounds__(kBlock) void k_forward(const SimDev *__restrict__ s
     auto XN = pick<kx>(dyn + off_x, G(S.x));
     auto Vprev = G(S.vk1);
     int64_t iters_total = 0, it_run = 0;
+    if (S.again_x) {            // behind a multi-workgroup launch of the same pass: again from the start, if that gave up
+        if (G(S.counters)[7] == 0) return;
+        for (int i = threadIdx.x; i < 3 * m; i += (int)blockDim.x) {
+            G(S.x)[i] = G(S.again_x)[i];
+            G(S.v)[i] = G(S.again_v)[i];
+            G(S.f)[i] = 0.0;
+        }
+        __syncthreads();
+    }
     for (int n = S.step_begin; n < S.step_end; ++n) {
         const int slot = S.rec_ring ? 0 : n - S.rec_step0;
         const double t1 = (n + 1) * h;
@@ -2292,9 +2303,9 @@ __device__ __forceinline__ int gmres_solve(const SimDev &S, auto mode, auto prt,
 // Each adjoint step solves A zeta = gbar with A = M + H T^T (H = h^2 K_s (x) I_3
 // - Delta P at x_{n+1}, T the contact Jacobian blocks; Sec. 4.2).  The paper
 // solves it by a fixed point with the prefactored P and falls back to a direct
-// solve; here every step's A is factored up front, all steps at once (one
-// workgroup each), on the supernodes of P at the level of degrees of freedom
-// (left-looking, children first).  Supernode s keeps D_s^{-1} (its diagonal
+// solve; here every step's A is factored up front, all steps at once (a
+// workgroup per step and block or tile), on the supernodes of P at the level of
+// degrees of freedom (left-looking, children first).  Supernode s keeps D_s^{-1} (its diagonal
 // block after the Schur updates, inverted by Gauss-Jordan with row pivoting
 // inside the block), B_s = A(R_s, s) and V_s = D_s^{-1} A(s, R_s); the Schur
 // update of descendant d onto the blocks it reaches is B_d V_d.
@@ -3460,19 +3471,6 @@ __global__ void k_fill(double *p, double v, int64_t n) {
     if (i < n) p[i] = v;
 }
 
-// Between the multi-workgroup launch of an allocation-free forward and a
-// one-workgroup launch of the same descriptor: the state of 3 m = n entries as at
-// the start for the latter when the former gave up at a barrier (or had nothing
-// to do: mw < 2), else no steps are left for it.
-__global__ void k_again(SimDev *__restrict__ d, const double *__restrict__ x0, const double *__restrict__ v0, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d->mw < 2 || d->counters[7] != 0) {
-        if (i < n) { d->x[i] = x0[i]; d->v[i] = v0[i]; d->f[i] = 0.0; }
-    } else if (i == 0) {
-        d->step_end = d->step_begin;
-    }
-}
-
 // ------------------------------------------------------------------ launchers
 
 template <bool MIXED, int FL>
@@ -3645,11 +3643,6 @@ hipError_t launch_scatter_bend(const double *dw, const int32_t *centers, int n_e
 hipError_t launch_fill(double *p, double v, int64_t n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_again(SimDev *d, const double *x0, const double *v0, int64_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_again, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d, x0, v0, n);
     return hipGetLastError();
 }
 

@@ -1,7 +1,8 @@
 // Device-side descriptor of one cloth handle.  Every array lives in HBM and
 // uses the nested-dissection node order ("new" order); vectors of 3D
-// quantities are node-major [node][xyz].  One workgroup owns one handle for
-// the duration of a launch, so work buffers are private to it.
+// quantities are node-major [node][xyz].  One workgroup, or the several of a
+// multi-workgroup forward, owns a handle for the duration of a launch: work
+// buffers are private to them.
 #pragma once
 
 #include <cstddef>
@@ -285,9 +286,11 @@ struct SimDev {
     const int32_t *lvl_root;          // [n_levels] first forward item of a root supernode (the level's last ones)
     double *bsep;                     // [3m] right-hand side of the rows above the leaves
     uint64_t *mw_sync;                // barrier block (kMwSyncWords words)
-    uint64_t mw_epoch;                // base of this launch's barrier counts (never decreases per block)
+    uint64_t mw_epoch;                // base of this launch's barrier counts (above every count in the block)
     int mw_lds;                       // 1: each workgroup copies its share of the factor into LDS once per launch
     int mw_off_t, mw_off_x, mw_off_own;   // dynamic LDS (doubles): gathered vectors, results, owned nodes' state
+    const double *again_x, *again_v;  // one-workgroup launch behind a multi-workgroup one (else null): the state to
+                                      //   start from if that gave up; if not, nothing is left to do
     int64_t mw_spin;                  // wall-clock ticks (100 MHz) a barrier waits before giving up
     int mw_absent;                    // failure-handling tests only (0: off): the last of several workgroups
                                       //   returns (3: after the first step, else at once), so the others'
