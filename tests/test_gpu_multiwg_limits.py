@@ -117,3 +117,20 @@ def test_barrier_counts_after_16_million_launches(monkeypatch):
             assert torch.equal(x, rx) and torch.equal(v, rv)
         assert s.stats()["fwd_workgroups"] > 1
         s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("lds,threads,wgs", [("1", "64", 2), ("0", "64", 2), ("0", "256", 5), ("1", "256", 16),
+                                             ("0", "512", 16), ("1", "448", 7)])
+def test_factor_from_lds_or_memory_on_any_number_of_threads(monkeypatch, precision, lds, threads, wgs):
+    # 24 x 24: two workgroups of 64 threads have more rows, items and nodes than threads
+    sc = _low(scenes.c2_sphere_drop(0, n=24, steps=4))
+    rx, rv = _one_workgroup(sc, monkeypatch, precision=precision)
+    monkeypatch.setenv("DIFFCLOTH_FWD_WGS", str(wgs))
+    monkeypatch.setenv("DIFFCLOTH_MW_LDS", lds)
+    monkeypatch.setenv("DIFFCLOTH_MW_THREADS", threads)
+    s = _sim(sc, precision=precision)
+    assert s.stats()["fwd_workgroups"] == wgs
+    x, v, _ = s.forward(sc.steps)
+    assert torch.equal(x, rx) and torch.equal(v, rv)
+    s.close()
