@@ -53,7 +53,10 @@ extern "C" {
                                     sim_forward_noalloc has (16 MiB)                   */
 #define SIM_ESYNC           -8   /* a multi-workgroup forward launch gave up waiting at
                                     a barrier (its workgroups were not all resident
-                                    in time); the rollout is not recorded              */
+                                    in time) and was not run again; the rollout is
+                                    not recorded.  Every call runs such passes again
+                                    on one workgroup, where the handle then stays, so
+                                    that callers should not see this                   */
 #define SIM_WADJ_FALLBACK    1   /* >= 1 adjoint step needed the fallback solver        */
 #define SIM_WADJ_NOCONV      2   /* >= 1 adjoint step did not reach its tolerance       */
 #define SIM_WADJ_NONFINITE   3   /* the state gradients overflowed (not finite)         */
