@@ -169,9 +169,10 @@ int mw_workgroups_default(int64_t factor_bytes) {
 
 // Nodes from which a handle's own launches (and batches with such a handle) take
 // the multi-workgroup forward unless DIFFCLOTH_FWD_WGS says otherwise.  Below,
-// one workgroup needs less time than the barriers; us per PD iteration on one
-// workgroup / split: 14 x 14 17.2 / 16.9, 16 x 16 18.3 / 17.6, 18 x 18 19.4 /
-// 17.9, 24 x 24 25.7 / 19.3, 34 x 34 60.6 / 46.1, 48 x 48 200 / 53.
+// one workgroup needs hardly more time than the barriers, and leaves the other
+// compute units free; us per PD iteration (mixed precision) on one workgroup /
+// split over 32 to 128: 14 x 14 12.6 / 12.9, 16 x 16 14.3 / 13.0, 18 x 18 15.0 /
+// 13.2, 24 x 24 20.3 / 14.6, 34 x 34 46 / 37, 48 x 48 153 / 41, 72 x 72 568 / 58.
 constexpr int kMwMinNodes = 324;
 
 // Whether the workgroups of a multi-workgroup forward may copy their shares of
@@ -1254,10 +1255,12 @@ size_t batch_lds(sim *const *sims, int n, bool fwd, int &flags) {
 int mw_launch(const sim *s, const SimDev *d, const int32_t *map, int blocks, bool mesh, size_t lds, hipStream_t st);
 
 // Workgroups of each handle of a batched forward launch (empty: one each,
-// k_forward).  A PD iteration of a handle takes about 2.5 us per level and
+// k_forward).  A PD iteration of a handle is taken as 2.5 us per level and
 // direction of its solves (a barrier and the loads after it) and 0.7 ns per pair
 // of factor entries on one workgroup; the workgroups the device can hold go to
-// whichever handle would finish last.  A mesh that is one dense block (a tree of
+// whichever handle would finish last.  (Fitted to 24 x 24 ... 100 x 100 on 4 to 64
+// workgroups: 4 - 7 us and 0.5 - 0.9 ns.  With 4.5 us, 32 meshes of 16 x 16 to
+// 64 x 64 took 1 % and 8 requests of 20 x 20 to 80 x 80 2 % longer.)  A mesh that is one dense block (a tree of
 // one level) keeps to one; a larger one with a root among its leaves could not
 // be split either and would be the last for that, so the batch is left as it is.
 std::vector<int> batch_workgroups(sim *const *sims, int n) {

@@ -1547,7 +1547,7 @@ __device__ __forceinline__ void mw_contact(const MwNodes &N, int t, const double
 // workgroups (descriptors, offsets, positions, earlier results) between its
 // arrival at a barrier and the wait.  Per PD iteration, against one XCD's 16
 // workgroups with a subtree each (40 x 40, 72 x 72) or one workgroup (100 x 100
-// without allocations): 43 -> 29 us, 174 -> 61 us, 1.2 ms -> 121 us.
+// without allocations): 43 -> 25 us, 174 -> 58 us, 1.2 ms -> 122 us.
 // Every node, row and item is computed with the arithmetic of k_forward (same
 // items, teams and summation orders), so results are bitwise those of the
 // one-workgroup kernel for any number of workgroups.

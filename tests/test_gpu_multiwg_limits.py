@@ -134,3 +134,26 @@ def test_factor_from_lds_or_memory_on_any_number_of_threads(monkeypatch, precisi
     x, v, _ = s.forward(sc.steps)
     assert torch.equal(x, rx) and torch.equal(v, rv)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("scs", [
+    [scenes.stacked_sheets(3, steps=9), scenes.stacked_sheets(14, steps=5), scenes.stacked_sheets(4, steps=7, ground=True)],
+    [_low(scenes.discretized_sphere_drop(0, n=5, steps=9, level=1)), scenes.wind_napkin(0, n=4, steps=8),
+     _low(scenes.discretized_sphere_drop(0, n=21, steps=5, level=1))],
+], ids=["pairs", "mesh"])
+def test_one_block_members_with_pairs_mesh_obstacles_and_forces(monkeypatch, scs, precision):
+    from paper_2106_05306_amd import _binding as B
+    from paper_2106_05306_amd.sim import batch_forward
+    ref = [_one_workgroup(sc, monkeypatch, precision=precision) for sc in scs]
+    monkeypatch.setenv("DIFFCLOTH_MW_SPIN", "2000000")
+    sims = [_sim(sc, precision=precision) for sc in scs]
+    assert sum(s.stats()["fwd_workgroups"] > 1 for s in sims) == 1
+    for (x, v), (rx, rv) in zip(batch_forward(sims, [sc.steps for sc in scs]), ref):
+        assert torch.equal(x, rx) and torch.equal(v, rv)
+    monkeypatch.setenv("DIFFCLOTH_MW_TEST_ABSENT", "1")
+    with pytest.raises(B.SimError) as e:
+        batch_forward(sims, [sc.steps for sc in scs])
+    assert e.value.code == B.SIM_ESYNC
+    for s in sims:
+        s.close()
